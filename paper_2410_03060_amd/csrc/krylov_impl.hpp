@@ -1662,10 +1662,104 @@ static SolveLayout carve_solve(void* ws, size_t ws_bytes, const SolveShape& sh) 
     return L;
 }
 
+// ------------------------------------------------------------------ wires without neighbours
+// A wire whose block row is its self block alone is a system of its own: its
+// currents are Z_ii^-1 u_i, which the block-diagonal preconditioner holds.
+// Where at most LONE_SHARE of the wires can have a neighbour (bounded from the
+// pair count: n_coupled <= 2 n_pairs), the solve takes the others out of the
+// iteration: k_lone_solve solves them in one pass, and the Krylov cycles run on
+// a compact cloud of the coupled wires.
+//   The line: the compaction costs a copy of the coupled blocks and two host
+// synchronisations (about 100 us); the iteration saves every vector pass of the
+// wires taken out.  MI355X, whole step before and after: 17 clouds of 62,500
+// wires, 360 incidences (at most 26 % coupled) 65.2 -> 18.6 ms; 10^5 wires of
+// 19 unknowns, 64 incidences (5 %) 63.5 -> 13.1 ms; Gaussian clouds (19 %) of
+// 100,000 wires, one incidence 5.79 -> 3.37 ms, of 8,000 wires 2.00 -> 1.99 ms,
+// 8 incidences 2.40 -> 2.19; of 2,000 wires 1.60 -> 1.74 ms and 1,000 wires of
+// 19 unknowns 1.46 -> 1.53 ms: from LONE_ROWS unknowns on.  Above three
+// quarters little is left to save, below it the passes saved outweigh the copy
+// (a block row is copied once, the vectors pass tens of times).
+constexpr double LONE_SHARE = 0.75;
+constexpr int64_t LONE_ROWS = 40000;
+static bool lone_wires(const Cloud* c, const chaff_solve_opts* o) {
+    // a caller's own guess (use_x0 = 1) is left as it is given
+    return o->precond == CHAFF_PRECOND_BLOCK && o->use_x0 != 1 && c->n * NB >= LONE_ROWS &&
+           2.0 * (double)c->n_pairs <= LONE_SHARE * (double)c->n;
+}
+
+constexpr int LONE_BLOCK = 256;   // wires per counting block
+static int64_t lone_blocks(int64_t n) { return (n + LONE_BLOCK - 1) / LONE_BLOCK; }
+
+// Device arrays of the compact cloud, before the solver's own workspace.
+struct LoneLayout {
+    int32_t* cmap;      // [n] compact index of a coupled wire, -1 for the others
+    int32_t* lone;      // [n] wires without neighbours, ascending
+    int32_t* blk;       // [blocks + 1] coupled wires before each counting block
+    int32_t* at;        // [n_clouds + 1] coupled wires before each cloud
+    Wire* wires;        // the compact cloud: wires, caller indices, clouds, pattern
+    int32_t *perm, *wire_cloud, *src;   // src: its wire in the full cloud
+    int64_t* row_ptr;
+    int32_t* col_idx;
+    void *Z, *Pinv;
+    Chunk* chunks;      // runs of lone wires of one cloud
+    int32_t* cloud_chunk_off;
+    c128 *part, *sums;  // [chunk][2][s], [2][n_clouds][s]
+    size_t bytes;
+};
+constexpr int LONE_CHUNK = 64;   // lone wires per chunk
+
+static LoneLayout carve_lone(void* ws, size_t cap, const Cloud* c, int64_t s, size_t csize) {
+    Carve cv(ws, cap);
+    LoneLayout l;
+    const int64_t n = c->n, nc = std::min<int64_t>(n, 2 * c->n_pairs), nzc = nc + 2 * c->n_pairs;
+    const int64_t nch = n / LONE_CHUNK + c->n_clouds + 1;
+    l.cmap = cv.take<int32_t>(n);
+    l.lone = cv.take<int32_t>(n);
+    l.blk = cv.take<int32_t>(lone_blocks(n) + 1);
+    l.at = cv.take<int32_t>((size_t)c->n_clouds + 1);
+    l.wires = cv.take<Wire>(nc);
+    l.perm = cv.take<int32_t>(nc);
+    l.wire_cloud = cv.take<int32_t>(nc);
+    l.src = cv.take<int32_t>(nc);
+    l.row_ptr = cv.take<int64_t>(nc + 1);
+    l.col_idx = cv.take<int32_t>(nzc);
+    l.Z = cv.take<char>((size_t)nzc * NB2 * csize);
+    l.Pinv = cv.take<char>((size_t)nc * NB2 * csize);
+    l.chunks = cv.take<Chunk>(nch);
+    l.cloud_chunk_off = cv.take<int32_t>((size_t)c->n_clouds + 1);
+    l.part = cv.take<c128>((size_t)nch * 2 * s);
+    l.sums = cv.take<c128>((size_t)2 * c->n_clouds * s);
+    l.bytes = align_up(cv.off, 256);
+    return l;
+}
+
+// Solver workspace for at most nc coupled wires in n_clouds clouds, however
+// they are spread (chunks and tiles are cut at cloud boundaries).
+static size_t compact_solve_bytes(const Cloud* c, const chaff_solve_opts* o, int64_t s, int64_t nc) {
+    Cloud cc = *c;
+    cc.n = nc;
+    cc.n_clouds = 1;
+    cc.cloud_off = {0, nc};
+    SolveShape sh = solve_shape(&cc, o->restart, s, (chaff_prec)o->prec, o->method);
+    sh.n_clouds = c->n_clouds;
+    sh.nsys = (int64_t)c->n_clouds * s;
+    sh.n_chunks = (int)std::min<int64_t>((nc + 31) / 32, 2048) + c->n_clouds;   // chunk_wires: at least 32 wires, 2048 chunks
+    if (sh.n_tiles > 0) {
+        sh.n_tiles += c->n_clouds;
+        sh.n_groups = (int)(sh.n_tiles / TILE_GROUP) + c->n_clouds + 1;
+    }
+    return carve_solve(nullptr, 0, sh).bytes;
+}
+
 size_t solve_workspace_bytes(const Cloud* c, const chaff_solve_opts* o, int64_t s) {
     const int m = o->restart;
     SolveShape sh = solve_shape(c, m, s, (chaff_prec)o->prec, o->method);
-    return carve_solve(nullptr, 0, sh).bytes;
+    size_t bytes = carve_solve(nullptr, 0, sh).bytes;
+    if (lone_wires(c, o)) {
+        const int64_t nc = std::min<int64_t>(c->n, 2 * c->n_pairs);
+        bytes = std::max(bytes, carve_lone(nullptr, 0, c, s, sh.csize).bytes + compact_solve_bytes(c, o, s, nc));
+    }
+    return bytes;
 }
 
 // COCG product tiles of tile_w wires (cloud-aligned) and their groups of
@@ -2293,10 +2387,17 @@ static chaff_status gcr_cycle(Cloud* c, const chaff_solve_opts* o, const SolveSh
     return CHAFF_OK;
 }
 
+// u and its residual on the wires without neighbours, squared norms per
+// system: what solve_impl adds to the norms of the coupled rows it iterates on.
+struct LoneSums {
+    std::vector<double> b2, r2;   // [n_clouds * s]
+};
+
 template <typename C, typename CZ>
 static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z, const CZ* Pinv,
                                const double* k_hat, const double* e_hat, int64_t s, c128* Xout, void* ws,
-                               size_t ws_bytes, chaff_solve_stats* stats, double* rel_res_out, hipStream_t st) {
+                               size_t ws_bytes, chaff_solve_stats* stats, double* rel_res_out, hipStream_t st,
+                               const LoneSums* lone = nullptr) {
     auto t_start = std::chrono::steady_clock::now();
     const int m = o->restart;
     SolveShape sh = solve_shape(c, m, s, (chaff_prec)o->prec, o->method);
@@ -2404,7 +2505,7 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
     CHAFF_HIP(hipMemcpyAsync(hb.data(), L.red, nsys * sizeof(c128), hipMemcpyDeviceToHost, st));
     CHAFF_HIP(hipStreamSynchronize(st));
     std::vector<double> bnorm(nsys), rel(nsys, 0.0);
-    for (int64_t i = 0; i < nsys; ++i) bnorm[i] = std::sqrt(std::max(hb[i].re, 0.0));
+    for (int64_t i = 0; i < nsys; ++i) bnorm[i] = std::sqrt(std::max(hb[i].re, 0.0) + (lone ? lone->b2[i] : 0.0));
 
     const bool refine = std::is_same<C, c64>::value;
     int cycles = 0, iters = 0;
@@ -2434,7 +2535,7 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
         broken = false;
         for (int64_t i = 0; i < nsys; ++i) {
             double rn = std::sqrt(std::max(hr[i].re, 0.0));
-            rel[i] = bnorm[i] > 0 ? rn / bnorm[i] : 0.0;
+            rel[i] = bnorm[i] > 0 ? std::sqrt(rn * rn + (lone ? lone->r2[i] : 0.0)) / bnorm[i] : 0.0;
             if (!std::isfinite(hr[i].re)) {   // a recurrence broke down and left x non-finite
                 rel[i] = INFINITY;
                 broken = true;
@@ -2619,14 +2720,342 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
     return CHAFF_OK;
 }
 
+// ------------------------------------------------------------------ the coupled wires as a cloud of their own
+
+// blk[b] = coupled wires (more than one block in their row) of counting block b
+__global__ __launch_bounds__(LONE_BLOCK) void k_lone_count(const int64_t* __restrict__ row_ptr, int64_t n,
+                                                           int32_t* __restrict__ blk) {
+    __shared__ int32_t cnt[LONE_BLOCK / 64];
+    const int64_t i = (int64_t)blockIdx.x * LONE_BLOCK + threadIdx.x;
+    const bool on = i < n && row_ptr[i + 1] - row_ptr[i] > 1;
+    const uint64_t b = __ballot(on);
+    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = __popcll(b);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+        for (int w = 0; w < LONE_BLOCK / 64; ++w) t += cnt[w];
+        blk[blockIdx.x] = t;
+    }
+}
+
+// exclusive prefix of blk[0..nb) in place, the total in blk[nb]; one workgroup
+__global__ __launch_bounds__(1024) void k_lone_scan(int32_t* __restrict__ blk, int64_t nb) {
+    __shared__ int32_t ws[16];
+    __shared__ int32_t base_s;
+    if (threadIdx.x == 0) base_s = 0;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int64_t i0 = 0; i0 < nb; i0 += 1024) {
+        const int64_t i = i0 + threadIdx.x;
+        const int32_t v = i < nb ? blk[i] : 0;
+        int32_t x = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) ws[w] = x;
+        __syncthreads();
+        int32_t before = base_s;
+        for (int k = 0; k < w; ++k) before += ws[k];
+        if (i < nb) blk[i] = before + x - v;
+        __syncthreads();
+        if (threadIdx.x == 1023) base_s = before + x;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) blk[nb] = base_s;
+}
+
+// The compact arrays of the coupled wires, in the cloud's order, the list of
+// the others, and the coupled wires before each cloud.  A wire without
+// neighbours holds one block, so row_ptr of compact wire ci = i - (lone wires
+// before i) is row_ptr[i] less their number.
+__global__ __launch_bounds__(LONE_BLOCK) void k_lone_place(const int64_t* __restrict__ row_ptr, int64_t n, int n_clouds,
+                                                           const Wire* __restrict__ wires,
+                                                           const int32_t* __restrict__ perm,
+                                                           const int32_t* __restrict__ wire_cloud, LoneLayout l) {
+    __shared__ int32_t cnt[LONE_BLOCK / 64];
+    const int64_t i = (int64_t)blockIdx.x * LONE_BLOCK + threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t e0 = i < n ? row_ptr[i] : 0, e1 = i < n ? row_ptr[i + 1] : 0;
+    const bool on = e1 - e0 > 1;
+    const uint64_t b = __ballot(on);
+    if (lane == 0) cnt[w] = __popcll(b);
+    __syncthreads();
+    if (i >= n) return;
+    int32_t ci = l.blk[blockIdx.x] + __popcll(b & ((1ull << lane) - 1));
+    for (int k = 0; k < w; ++k) ci += cnt[k];
+    const int32_t cl = wire_cloud[i];
+    for (int k = i > 0 ? wire_cloud[i - 1] + 1 : 0; k <= cl; ++k) l.at[k] = ci;
+    const int32_t after = ci + (on ? 1 : 0);
+    if (i == n - 1)
+        for (int k = cl + 1; k <= n_clouds; ++k) l.at[k] = after;
+    l.cmap[i] = on ? ci : -1;
+    if (on) {
+        l.wires[ci] = wires[i];
+        l.perm[ci] = perm[i];
+        l.wire_cloud[ci] = cl;
+        l.src[ci] = (int32_t)i;
+        l.row_ptr[ci] = e0 - (i - ci);
+    } else {
+        l.lone[i - ci] = (int32_t)i;
+    }
+    if (i == n - 1) l.row_ptr[after] = e1 - (n - after);   // nnzb less the lone wires
+}
+
+// Blocks, columns and inverse self blocks of the coupled wires: one wave per wire.
+template <typename CZ>
+__global__ __launch_bounds__(256) void k_lone_blocks(int64_t nc, const int64_t* __restrict__ row_ptr,
+                                                     const int32_t* __restrict__ col_idx, const CZ* __restrict__ Z,
+                                                     const CZ* __restrict__ Pinv, LoneLayout l) {
+    const int64_t ci = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (ci >= nc) return;
+    const int64_t i = l.src[ci], e0 = row_ptr[i], f0 = l.row_ptr[ci];
+    const int64_t ne = row_ptr[i + 1] - e0;
+    CZ* Zc = static_cast<CZ*>(l.Z);
+    CZ* Pc = static_cast<CZ*>(l.Pinv);
+    for (int64_t t = lane; t < ne; t += 64) l.col_idx[f0 + t] = l.cmap[col_idx[e0 + t]];
+    for (int64_t t = lane; t < ne * NB2; t += 64) Zc[f0 * NB2 + t] = Z[e0 * NB2 + t];
+    for (int t = lane; t < NB2; t += 64) Pc[ci * NB2 + t] = Pinv[i * NB2 + t];
+}
+
+// a^T v over one row of a stored block, FP64, four independent chains
+template <typename CZ>
+__device__ __forceinline__ c128 row_times(const CZ* __restrict__ row, const c128 (&v)[NB]) {
+    double r0 = 0.0, r1 = 0.0, i0 = 0.0, i1 = 0.0;
+#pragma unroll
+    for (int m = 0; m < NB; ++m) {
+        const c128 a = ccast<c128>(row[m]);
+        r0 = fma(a.re, v[m].re, r0);
+        r1 = fma(a.im, v[m].im, r1);
+        i0 = fma(a.re, v[m].im, i0);
+        i1 = fma(a.im, v[m].re, i1);
+    }
+    return c128{r0 - r1, i0 + i1};
+}
+
+// The wires without neighbours, start to end: u (eq. 4), x = P u, then sweeps
+// of r = u - Z_ii x, x += P r in FP64 over the stored blocks until ||r|| of the
+// wire is below thr ||u|| (at most four), x to the caller's rows, and the
+// chunk's sums of |u|^2 and |r|^2 (r the residual of the x that is written).
+// A thread owns one (wire, right-hand side); with 64 columns the wire is
+// uniform over the wave and its blocks come through the scalar cache.
+//   Bound: FP64 arithmetic, four NB x NB complex products with the usual one
+// sweep.  One vector at a time is held in registers and the product's rows are
+// walked by a rolled loop through the lane's own column of LDS: with every
+// product unrolled (NB^2 terms each) the 19-unknown form ran out of registers
+// and instruction cache: 75.7 ms for 95,000 wires x 64 columns, rolled 3.2 ms
+// (16 TFLOP/s, 1.9 GB written); 7 unknowns, 46,000 wires x 360: 3.1 -> 1.9 ms.
+// u is formed again where it is needed, each rooftop's phase from the last by
+// one complex product.
+template <typename CZ, int ST>
+__global__ __launch_bounds__(256) void k_lone_solve(LoneLayout l, const Wire* __restrict__ wires,
+                                                    const int32_t* __restrict__ perm,
+                                                    const int64_t* __restrict__ row_ptr, const CZ* __restrict__ Z,
+                                                    const CZ* __restrict__ Pinv, const double* __restrict__ k_hat,
+                                                    const double* __restrict__ e_hat, double k, int64_t s, double thr,
+                                                    c128* __restrict__ X) {
+    __shared__ c128 vs[4][NB][64];   // at least 7 x 256 entries: also the column reduction's
+    const Chunk ch = l.chunks[blockIdx.x];
+    const int rsub = ST == 64 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x / ST);
+    const int64_t r = (int64_t)blockIdx.y * ST + threadIdx.x % ST;
+    c128(*lv)[64] = vs[threadIdx.x >> 6];   // this wave's; a lane reads what it wrote itself
+    const int lane = threadIdx.x & 63;
+    double u2 = 0.0, r2 = 0.0;
+    if (r < s) {
+        const double kx = k_hat[3 * r], ky = k_hat[3 * r + 1], kz = k_hat[3 * r + 2];
+        const double ex = e_hat[3 * r], ey = e_hat[3 * r + 1], ez = e_hat[3 * r + 2];
+        for (int64_t t = ch.w0 + rsub; t < ch.w1; t += 256 / ST) {
+            const int64_t i = l.lone[t];
+            const Wire w = wires[i];
+            const CZ* zb = Z + row_ptr[i] * NB2;
+            const CZ* pb = Pinv + i * NB2;
+            const double tp = w.tx * ex + w.ty * ey + w.tz * ez;
+            const double beta = k * (kx * w.tx + ky * w.ty + kz * w.tz);
+            const double ph0 = k * (kx * w.cx + ky * w.cy + kz * w.cz);
+            const double D = w.len / NSEG;
+            const double sc = sinc(0.5 * beta * D);
+            const double env = tp * D * sc * sc;
+            c128 first, step;   // u_0 and the phase step of one rooftop
+            {
+                double sn, cs;
+                sincos(ph0 - (double)(NB / 2) * beta * D, &sn, &cs);
+                first = c128{env * cs, -env * sn};
+                sincos(beta * D, &sn, &cs);
+                step = c128{cs, -sn};
+            }
+            c128 x[NB];
+            double w2 = 0.0;
+            x[0] = first;
+#pragma unroll
+            for (int q = 1; q < NB; ++q) x[q] = cmul(x[q - 1], step);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) w2 += x[q].re * x[q].re + x[q].im * x[q].im;
+#pragma unroll 1
+            for (int q = 0; q < NB; ++q) lv[q][lane] = row_times(pb + q * NB, x);
+            double e2 = w2;
+#pragma unroll 1
+            for (int sweep = 0;; ++sweep) {
+#pragma unroll
+                for (int q = 0; q < NB; ++q) x[q] = lv[q][lane];
+                e2 = 0.0;
+                c128 uq = first;
+#pragma unroll 1
+                for (int q = 0; q < NB; ++q) {   // r = u - Z x, over x in LDS
+                    const c128 rq = csub(uq, row_times(zb + q * NB, x));
+                    e2 += rq.re * rq.re + rq.im * rq.im;
+                    lv[q][lane] = rq;
+                    uq = cmul(uq, step);
+                }
+                if (!(e2 > thr * thr * w2) || sweep == 4) break;
+                c128 rv[NB];
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    rv[q] = lv[q][lane];
+                    lv[q][lane] = x[q];
+                }
+#pragma unroll 1
+                for (int q = 0; q < NB; ++q) lv[q][lane] = cadd(lv[q][lane], row_times(pb + q * NB, rv));
+            }
+            const int64_t o = (int64_t)perm[i] * NB * s + r;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) X[o + q * s] = x[q];
+            u2 += w2;
+            r2 += e2;
+        }
+    }
+    __syncthreads();
+    const c128 v = block_col_reduce(c128{u2, r2}, ST, &vs[0][0][0]);
+    if (threadIdx.x < ST && r < s) {
+        l.part[((int64_t)blockIdx.x * 2) * s + r] = c128{v.re, 0.0};
+        l.part[((int64_t)blockIdx.x * 2 + 1) * s + r] = c128{v.im, 0.0};
+    }
+}
+
+// The solve with the wires without neighbours taken out (lone_wires).  *done
+// says whether the call was answered; it is not where the block inverses do
+// not solve those wires (a caller's own Pinv, a non-finite block), and the
+// caller then takes every wire through the iteration.
+template <typename C, typename CZ>
+static chaff_status solve_compact(Cloud* c, const chaff_solve_opts* o, const CZ* Z, const CZ* Pinv,
+                                  const double* k_hat, const double* e_hat, int64_t s, c128* X, void* ws,
+                                  size_t ws_bytes, chaff_solve_stats* stats, double* rel_res, hipStream_t st,
+                                  bool* done) {
+    auto t_start = std::chrono::steady_clock::now();
+    *done = false;
+    const int64_t n = c->n, nsys = (int64_t)c->n_clouds * s;
+    LoneLayout l = carve_lone(ws, ws_bytes, c, s, sizeof(CZ));
+    const int64_t nb = lone_blocks(n);
+    hipLaunchKernelGGL(k_lone_count, dim3((unsigned)nb), dim3(LONE_BLOCK), 0, st, (const int64_t*)c->row_ptr, n, l.blk);
+    hipLaunchKernelGGL(k_lone_scan, dim3(1), dim3(1024), 0, st, l.blk, nb);
+    hipLaunchKernelGGL(k_lone_place, dim3((unsigned)nb), dim3(LONE_BLOCK), 0, st, (const int64_t*)c->row_ptr, n,
+                       c->n_clouds, (const Wire*)c->wires, (const int32_t*)c->perm, (const int32_t*)c->wire_cloud, l);
+    CHAFF_LAUNCH_CHECK();
+    std::vector<int32_t> at(c->n_clouds + 1);
+    CHAFF_HIP(hipMemcpyAsync(at.data(), l.at, at.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    CHAFF_HIP(hipStreamSynchronize(st));
+    const int64_t nc = at[c->n_clouds], n_lone = n - nc;
+    std::vector<Chunk> ch;
+    std::vector<int32_t> off(c->n_clouds + 1, 0);
+    for (int k = 0; k < c->n_clouds; ++k) {
+        off[k] = (int32_t)ch.size();
+        const int64_t a = c->cloud_off[k] - at[k], b = c->cloud_off[k + 1] - at[k + 1];
+        for (int64_t w0 = a; w0 < b; w0 += LONE_CHUNK) ch.push_back(Chunk{w0, std::min<int64_t>(w0 + LONE_CHUNK, b), k, 0});
+    }
+    off[c->n_clouds] = (int32_t)ch.size();
+    LoneSums sums;
+    sums.b2.assign(nsys, 0.0);
+    sums.r2.assign(nsys, 0.0);
+    if (n_lone > 0) {
+        CHAFF_HIP(hipMemcpyAsync(l.chunks, ch.data(), ch.size() * sizeof(Chunk), hipMemcpyHostToDevice, st));
+        CHAFF_HIP(hipMemcpyAsync(l.cloud_chunk_off, off.data(), off.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+        const int w = spmm_tile_width(s);
+        const dim3 grid((unsigned)ch.size(), (unsigned)((s + w - 1) / w));
+        {
+            ProfScope ps("lone_solve", st, 4.0 * 8.0 * NB2 * (double)n_lone * s, true);
+#define CHAFF_LONE(W)                                                                                            \
+    case W:                                                                                                      \
+        hipLaunchKernelGGL((k_lone_solve<CZ, W>), grid, dim3(256), 0, st, l, (const Wire*)c->wires,              \
+                           (const int32_t*)c->perm, (const int64_t*)c->row_ptr, Z, Pinv, k_hat, e_hat,           \
+                           2.0 * PI_K / c->wavelength, s, 0.01 * o->tol, X);                                     \
+        break;
+            switch (w) {
+                CHAFF_LONE(1) CHAFF_LONE(2) CHAFF_LONE(4) CHAFF_LONE(8) CHAFF_LONE(16) CHAFF_LONE(32) CHAFF_LONE(64)
+            }
+#undef CHAFF_LONE
+        }
+        CHAFF_LAUNCH_CHECK();
+        chunk_sum((const c128*)l.part, (const int32_t*)l.cloud_chunk_off, c->n_clouds, 2, 0, 2, s, l.sums, st);
+        CHAFF_LAUNCH_CHECK();
+        std::vector<c128> h(2 * nsys);
+        CHAFF_HIP(hipMemcpyAsync(h.data(), l.sums, h.size() * sizeof(c128), hipMemcpyDeviceToHost, st));
+        CHAFF_HIP(hipStreamSynchronize(st));
+        for (int64_t i = 0; i < nsys; ++i) {
+            sums.b2[i] = h[i].re;
+            sums.r2[i] = h[nsys + i].re;
+            // the stated residual is kept with room for the coupled wires' part
+            if (!(sums.r2[i] <= 0.01 * o->tol * o->tol * sums.b2[i])) return CHAFF_OK;
+        }
+    }
+    *done = true;
+    if (g_verbose)
+        std::fprintf(stderr, "[chaff] %lld of %lld wires have no neighbour\n", (long long)n_lone, (long long)n);
+    if (nc == 0) {
+        double worst = 0.0;
+        for (int64_t i = 0; i < nsys; ++i) {
+            const double rel = sums.b2[i] > 0 ? std::sqrt(sums.r2[i] / sums.b2[i]) : 0.0;
+            worst = std::max(worst, rel);
+            if (rel_res) rel_res[i] = rel;
+        }
+        if (stats) {
+            *stats = chaff_solve_stats{};
+            stats->max_rel_residual = worst;
+            stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+        }
+        return CHAFF_OK;
+    }
+    hipLaunchKernelGGL((k_lone_blocks<CZ>), dim3((unsigned)((nc + 3) / 4)), dim3(256), 0, st, nc,
+                       (const int64_t*)c->row_ptr, (const int32_t*)c->col_idx, Z, Pinv, l);
+    CHAFF_LAUNCH_CHECK();
+    Cloud cc = *c;
+    cc.n = nc;
+    cc.nnzb = c->nnzb - n_lone;
+    for (int k = 0; k <= c->n_clouds; ++k) cc.cloud_off[k] = at[k];
+    cc.wires = l.wires;
+    cc.perm = l.perm;
+    cc.wire_cloud = l.wire_cloud;
+    cc.row_ptr = l.row_ptr;
+    cc.col_idx = l.col_idx;
+    cc.iperm = nullptr;   // not read by the solver
+    cc.diag_pos = nullptr;
+    cc.pairs = nullptr;
+    const chaff_status e = solve_impl<C, CZ>(&cc, o, (const CZ*)l.Z, (const CZ*)l.Pinv, k_hat, e_hat, s, X,
+                                             static_cast<char*>(ws) + l.bytes, ws_bytes - l.bytes, stats, rel_res, st,
+                                             &sums);
+    if (stats) stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+    return e;
+}
+
+template <typename C>
+static chaff_status solve_any(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv, const double* k_hat,
+                              const double* e_hat, int64_t s, void* X, void* ws, size_t ws_bytes,
+                              chaff_solve_stats* st_out, double* rel_res, hipStream_t st) {
+    if (lone_wires(c, o)) {
+        bool done = false;
+        const chaff_status e = solve_compact<C, C>(c, o, (const C*)Z, (const C*)Pinv, k_hat, e_hat, s, (c128*)X, ws,
+                                                   ws_bytes, st_out, rel_res, st, &done);
+        if (done || e != CHAFF_OK) return e;
+    }
+    return solve_impl<C, C>(c, o, (const C*)Z, (const C*)Pinv, k_hat, e_hat, s, (c128*)X, ws, ws_bytes, st_out, rel_res,
+                            st);
+}
+
 chaff_status solve(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv, const double* k_hat,
                    const double* e_hat, int64_t s, void* X, void* ws, size_t ws_bytes, chaff_solve_stats* st_out,
                    double* rel_res, hipStream_t st) {
     if (o->prec == CHAFF_C64)
-        return solve_impl<c64, c64>(c, o, (const c64*)Z, (const c64*)Pinv, k_hat, e_hat, s, (c128*)X, ws,
-                                    ws_bytes, st_out, rel_res, st);
-    return solve_impl<c128, c128>(c, o, (const c128*)Z, (const c128*)Pinv, k_hat, e_hat, s, (c128*)X, ws,
-                                  ws_bytes, st_out, rel_res, st);
+        return solve_any<c64>(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, st_out, rel_res, st);
+    return solve_any<c128>(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, st_out, rel_res, st);
 }
 
 // Time every product variant on the caller's Z, X, Y and record the fastest.
