@@ -8,10 +8,10 @@
 //    hand-written LSD radix sort (8-bit digits, wave64 ballot ranking), which
 //    gives the block pattern spatial locality for the sparse products;
 //  * dense per-cloud tables map a linear cell index to its run of sorted wires;
-//  * two passes over the 27 neighbouring cells per wire: count, exclusive scan,
-//    then write the column indices in ascending order (cells are visited in
-//    the order of their run start, runs are disjoint), the diagonal position
-//    and the unique pair list (i < j) used by the fill.
+//  * two passes over the 27 neighbouring cells per wire, 32 lanes of a wave each:
+//    count, exclusive scan, then write the column indices in ascending order
+//    (the runs are disjoint and laid end to end in the order of their start), the
+//    diagonal position and the unique pair list (i < j) used by the fill.
 #include "common.hpp"
 #include "prof.hpp"
 
@@ -270,12 +270,150 @@ static chaff_status exclusive_scan(const TI* in, int64_t n, TO* out, TO* block_s
     return CHAFF_OK;
 }
 
+// Row and pair offsets in one pass: exclusive prefixes of both counts of every
+// wire, the totals at [n] of each.
+struct Count2 {
+    int32_t all, up;   // near wires of a wire (itself included), those above it
+};
+struct Sum2 {
+    int64_t all, up;
+};
+__device__ __forceinline__ Sum2 add2(Sum2 a, Sum2 b) { return Sum2{a.all + b.all, a.up + b.up}; }
+
+// inclusive prefix over the 1024 threads of a workgroup
+__device__ __forceinline__ Sum2 block_scan2(Sum2 v, Sum2* ws) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const Sum2 y = {__shfl_up(v.all, o, 64), __shfl_up(v.up, o, 64)};
+        if (lane >= o) v = add2(v, y);
+    }
+    if (lane == 63) ws[w] = v;
+    __syncthreads();
+    for (int k = 0; k < w; ++k) v = add2(v, ws[k]);
+    __syncthreads();
+    return v;
+}
+
+__global__ __launch_bounds__(SCAN_BLOCK) void k_scan2_sums(const Count2* __restrict__ in, int64_t n,
+                                                           Sum2* __restrict__ sums) {
+    __shared__ Sum2 ws[SCAN_BLOCK / 64];
+    const int64_t i = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x;
+    const Count2 c = i < n ? in[i] : Count2{0, 0};
+    const Sum2 v = block_scan2(Sum2{c.all, c.up}, ws);
+    if (threadIdx.x == SCAN_BLOCK - 1) sums[blockIdx.x] = v;
+}
+
+// prefixes of the nb block sums by one workgroup, in place; the total in sums[nb]
+__global__ __launch_bounds__(SCAN_BLOCK) void k_scan2_blocks(Sum2* __restrict__ sums, int64_t nb) {
+    __shared__ Sum2 ws[SCAN_BLOCK / 64];
+    __shared__ Sum2 carry_s;
+    Sum2 carry = {0, 0};
+    for (int64_t b0 = 0; b0 < nb; b0 += SCAN_BLOCK) {
+        const int64_t b = b0 + threadIdx.x;
+        const Sum2 v = b < nb ? sums[b] : Sum2{0, 0};
+        const Sum2 x = add2(carry, block_scan2(v, ws));
+        if (b < nb) sums[b] = Sum2{x.all - v.all, x.up - v.up};
+        if (threadIdx.x == SCAN_BLOCK - 1) carry_s = x;
+        __syncthreads();
+        carry = carry_s;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) sums[nb] = carry;
+}
+
+// sums == nullptr: one workgroup walks all the wires itself and leaves the total in *total
+__global__ __launch_bounds__(SCAN_BLOCK) void k_scan2_apply(const Count2* __restrict__ in, int64_t n,
+                                                            const Sum2* __restrict__ sums, int64_t nb,
+                                                            int64_t* __restrict__ row_ptr, int64_t* __restrict__ pair_ptr,
+                                                            Sum2* __restrict__ total) {
+    __shared__ Sum2 ws[SCAN_BLOCK / 64];
+    __shared__ Sum2 carry_s;
+    Sum2 carry = sums ? sums[blockIdx.x] : Sum2{0, 0};
+    const int64_t b_end = sums ? (int64_t)blockIdx.x + 1 : nb;
+    for (int64_t b = blockIdx.x; b < b_end; ++b) {
+        const int64_t i = b * SCAN_BLOCK + threadIdx.x;
+        const Count2 c = i < n ? in[i] : Count2{0, 0};
+        const Sum2 x = add2(carry, block_scan2(Sum2{c.all, c.up}, ws));
+        if (i < n) {
+            row_ptr[i] = x.all - c.all;
+            pair_ptr[i] = x.up - c.up;
+        }
+        if (i == n - 1) {
+            row_ptr[n] = x.all;
+            pair_ptr[n] = x.up;
+        }
+        if (!sums) {
+            if (threadIdx.x == SCAN_BLOCK - 1) carry_s = x;
+            __syncthreads();
+            carry = carry_s;
+            __syncthreads();
+            if (b == nb - 1 && threadIdx.x == 0) *total = carry;
+        }
+    }
+}
+
+// A workgroup walks 1024 wires in about 3 us; three launches cost about 20 us with their gaps.
+constexpr int64_t SCAN_ONE_BLOCK = 8 * SCAN_BLOCK;
+static chaff_status scan2(const Count2* in, int64_t n, int64_t* row_ptr, int64_t* pair_ptr, Sum2* sums, Sum2** total,
+                          hipStream_t st) {
+    const int64_t nb = (n + SCAN_BLOCK - 1) / SCAN_BLOCK;
+    *total = sums + nb;
+    if (n <= SCAN_ONE_BLOCK) {
+        hipLaunchKernelGGL(k_scan2_apply, dim3(1), dim3(SCAN_BLOCK), 0, st, in, n, (const Sum2*)nullptr, nb, row_ptr,
+                           pair_ptr, *total);
+        CHAFF_LAUNCH_CHECK();
+        return CHAFF_OK;
+    }
+    hipLaunchKernelGGL(k_scan2_sums, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, st, in, n, sums);
+    CHAFF_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_scan2_blocks, dim3(1), dim3(SCAN_BLOCK), 0, st, sums, nb);
+    CHAFF_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_scan2_apply, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, st, in, n, (const Sum2*)sums, nb, row_ptr,
+                       pair_ptr, (Sum2*)nullptr);
+    CHAFF_LAUNCH_CHECK();
+    return CHAFF_OK;
+}
+
+// ------------------------------------------------------------------ few wires: one launch sorts them
+// Stable order of n keys by counting: wire p goes to the number of keys below
+// its own plus the equal keys before p.  32 lanes count for one wire, the keys
+// come from L1.  At n wires the LSD passes take five launches each (about 20 us,
+// two or three passes); this takes 10 us for 2,000 wires and grows as n^2.
+constexpr int64_t RANK_SORT_MAX = 4096;
+__global__ __launch_bounds__(256) void k_rank_sort(const uint64_t* __restrict__ keys, int32_t n,
+                                                   uint64_t* __restrict__ keys_out, int32_t* __restrict__ perm) {
+    const int32_t p = (int32_t)(blockIdx.x * 8 + (threadIdx.x >> 5));
+    const int l = threadIdx.x & 31;
+    const uint64_t key = keys[p < n ? p : 0];
+    int32_t at = 0;
+#pragma unroll 8
+    for (int32_t j = l; j < n; j += 32) {
+        const uint64_t kj = keys[j];
+        at += (kj < key || (kj == key && j < p)) ? 1 : 0;
+    }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) at += __shfl_xor(at, o, 32);
+    if (p < n && l == 0) {
+        keys_out[at] = key;
+        perm[at] = p;
+    }
+}
+
 // ------------------------------------------------------------------ cells and geometry
 
 __global__ void k_fill_i32(int32_t* __restrict__ a, int64_t n, int32_t v) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         a[i] = v;
+}
+
+// the empty cell table: every cell starts and ends at 0
+__global__ void k_clear_cells(int32_t* __restrict__ start, int32_t* __restrict__ end, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        start[i] = 0;
+        end[i] = 0;
+    }
 }
 
 __global__ void k_gather(const double* __restrict__ center, const double* __restrict__ tangent,
@@ -320,99 +458,106 @@ __global__ void k_cells(const Wire* __restrict__ wires, const int32_t* __restric
     }
 }
 
-// Neighbour cell runs of wire i, sorted by run start.  Returns the count.
-__device__ __forceinline__ int neighbour_runs(const CloudGrid& g, const Wire& w,
-                                              const int32_t* __restrict__ cell_start,
-                                              const int32_t* __restrict__ cell_end,
-                                              int32_t* rs, int32_t* re) {
-    int ix, iy, iz;
-    cell_of(g, w.cx, w.cy, w.cz, ix, iy, iz);
-    int nr = 0;
-    for (int dz = -1; dz <= 1; ++dz) {
-        int z = iz + dz;
-        if (z < 0 || z >= g.nz) continue;
-        for (int dy = -1; dy <= 1; ++dy) {
-            int y = iy + dy;
-            if (y < 0 || y >= g.ny) continue;
-            for (int dx = -1; dx <= 1; ++dx) {
-                int x = ix + dx;
-                if (x < 0 || x >= g.nx) continue;
-                int64_t lin = g.cell_base + ((int64_t)z * g.ny + y) * g.nx + x;
-                int32_t s = cell_start[lin], e = cell_end[lin];
-                if (e > s) {
-                    int k = nr++;
-                    while (k > 0 && rs[k - 1] > s) {  // insertion by run start
-                        rs[k] = rs[k - 1];
-                        re[k] = re[k - 1];
-                        --k;
-                    }
-                    rs[k] = s;
-                    re[k] = e;
-                }
-            }
+// Near set of every wire, 32 lanes per wire (two wires per wave): lane l < 27
+// looks up neighbouring cell l, the runs found are laid end to end in ascending
+// order of their start, and the 32 lanes then test 32 candidates at a time, so
+// the candidates are walked in ascending order whatever the cells hold.
+// WRITE 0 counts the near wires (and those above i); WRITE 1 writes columns,
+// diagonal position and the unique pairs, placed by ballots.
+//   Bound: latency of two dependent gathers (cell table, candidate).  One lane
+// per wire, its candidates one after the other and its runs in a private array,
+// took 385 us (count) and 397 us (pattern) for 300,000 wires of 8 neighbours and
+// 175 us each for 2,000 wires, where few waves hide nothing; this form 153 and
+// 180 us, and 9 us each.
+constexpr int NEAR_WIRES = 8;   // wires per workgroup of 256
+template <int WRITE>
+__global__ __launch_bounds__(32 * NEAR_WIRES) void k_near(const Wire* __restrict__ wires,
+                                                         const int32_t* __restrict__ wire_cloud,
+                                                         const CloudGrid* __restrict__ grids,
+                                                         const int32_t* __restrict__ cell_start,
+                                                         const int32_t* __restrict__ cell_end, int64_t n, double dc2,
+                                                         Count2* __restrict__ cnt, const int64_t* __restrict__ row_ptr,
+                                                         const int64_t* __restrict__ pair_ptr,
+                                                         int32_t* __restrict__ col_idx, int64_t* __restrict__ diag_pos,
+                                                         Pair* __restrict__ pairs) {
+    __shared__ int2 cell[NEAR_WIRES][32];   // {start, wires} of each neighbouring cell
+    __shared__ int2 run[NEAR_WIRES][32];    // {first candidate, start} of each run, ascending
+    const int g = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int shift = (g & 1) * 32;         // this wire's half of the wave's ballots
+    const int64_t i = (int64_t)blockIdx.x * NEAR_WIRES + g;
+    const bool live = i < n;
+    const Wire& w = wires[live ? i : 0];
+    const double ci[3] = {w.cx, w.cy, w.cz};
+    int32_t start = 0, len = 0;
+    if (live && l < 27) {
+        const CloudGrid gr = grids[wire_cloud[i]];
+        int x, y, z;
+        cell_of(gr, ci[0], ci[1], ci[2], x, y, z);
+        x += l % 3 - 1;
+        y += l / 3 % 3 - 1;
+        z += l / 9 - 1;
+        if (x >= 0 && x < gr.nx && y >= 0 && y < gr.ny && z >= 0 && z < gr.nz) {
+            const int64_t lin = gr.cell_base + ((int64_t)z * gr.ny + y) * gr.nx + x;
+            start = cell_start[lin];
+            len = cell_end[lin] - start;
         }
     }
-    return nr;
-}
-
-__global__ void k_count(const Wire* __restrict__ wires, const int32_t* __restrict__ wire_cloud,
-                        const CloudGrid* __restrict__ grids, const int32_t* __restrict__ cell_start,
-                        const int32_t* __restrict__ cell_end, int64_t n, double dc2,
-                        int32_t* __restrict__ cnt, int32_t* __restrict__ cnt_up) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const Wire w = wires[i];
-        const CloudGrid g = grids[wire_cloud[i]];
-        int32_t rs[27], re[27];
-        int nr = neighbour_runs(g, w, cell_start, cell_end, rs, re);
-        double ci[3] = {w.cx, w.cy, w.cz};
-        int32_t c = 0, cu = 0;
-        for (int r = 0; r < nr; ++r)
-            for (int32_t j = rs[r]; j < re[r]; ++j) {
-                double cj[3] = {wires[j].cx, wires[j].cy, wires[j].cz};
-                if (j == i || within(ci, cj, dc2)) {
-                    ++c;
-                    cu += (j > i);
-                }
-            }
-        cnt[i] = c;
-        cnt_up[i] = cu;
+    cell[g][l] = make_int2(start, len);
+    const uint32_t full = (uint32_t)(__ballot(len > 0) >> shift);
+    const int n_runs = __popc(full);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // rank of this run and candidates before it: every run starts at a different wire
+    int rank = 0, before = 0, total = 0;
+#pragma unroll
+    for (int m = 0; m < 27; ++m) {
+        const int2 c = cell[g][m];   // the same entry for the 32 lanes
+        const bool first = c.y > 0 && c.x < start;
+        rank += first ? 1 : 0;
+        before += first ? c.y : 0;
+        total += c.y;
     }
-}
-
-__global__ void k_pattern(const Wire* __restrict__ wires, const int32_t* __restrict__ wire_cloud,
-                          const CloudGrid* __restrict__ grids, const int32_t* __restrict__ cell_start,
-                          const int32_t* __restrict__ cell_end, int64_t n, double dc2,
-                          const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ pair_ptr,
-                          int32_t* __restrict__ col_idx, int64_t* __restrict__ diag_pos,
-                          Pair* __restrict__ pairs) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const Wire w = wires[i];
-        const CloudGrid g = grids[wire_cloud[i]];
-        int32_t rs[27], re[27];
-        int nr = neighbour_runs(g, w, cell_start, cell_end, rs, re);
-        double ci[3] = {w.cx, w.cy, w.cz};
-        int64_t pos = row_ptr[i];
-        int64_t up = pair_ptr[i];
-        for (int r = 0; r < nr; ++r)
-            for (int32_t j = rs[r]; j < re[r]; ++j) {
-                double cj[3] = {wires[j].cx, wires[j].cy, wires[j].cz};
-                if (j == i || within(ci, cj, dc2)) {
-                    col_idx[pos] = j;
-                    if (j == i) diag_pos[i] = pos;
-                    if (j > i) {
-                        Pair pr;
-                        pr.i = (int32_t)i;
-                        pr.j = j;
-                        pr.pos_ij = pos;
-                        pr.pos_ji = -1;
-                        pairs[up++] = pr;
-                    }
-                    ++pos;
-                }
-            }
+    if (len > 0) run[g][rank] = make_int2(before, start);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    int32_t c = 0, cu = 0;
+    int64_t pos = 0, up = 0;
+    if (WRITE && live) {
+        pos = row_ptr[i];
+        up = pair_ptr[i];
     }
+    const uint32_t lower = (1u << l) - 1u;
+    int k = 0;   // run of this lane's candidate: it only moves forwards
+    for (int t0 = 0; t0 < total; t0 += 32) {
+        const int t = t0 + l;
+        bool hit = false;
+        int32_t j = 0;
+        if (t < total) {
+            while (k + 1 < n_runs && run[g][k + 1].x <= t) ++k;
+            const int2 r = run[g][k];
+            j = r.y + (t - r.x);
+            const double cj[3] = {wires[j].cx, wires[j].cy, wires[j].cz};
+            hit = j == i || within(ci, cj, dc2);
+        }
+        const uint32_t hits = (uint32_t)(__ballot(hit) >> shift);
+        const uint32_t ups = (uint32_t)(__ballot(hit && j > i) >> shift);
+        if (WRITE && hit) {
+            const int64_t p = pos + __popc(hits & lower);
+            col_idx[p] = j;
+            if (j == i) diag_pos[i] = p;
+            if (j > i) pairs[up + __popc(ups & lower)] = Pair{(int32_t)i, j, p, -1};
+        }
+        if (WRITE) {
+            pos += __popc(hits);
+            up += __popc(ups);
+        } else {
+            c += __popc(hits);
+            cu += __popc(ups);
+        }
+    }
+    if (!WRITE && live && l == 0) cnt[i] = Count2{c, cu};
 }
 
 __global__ void k_pair_transpose(Pair* __restrict__ pairs, int64_t n_pairs,
@@ -440,8 +585,8 @@ struct BuildLayout {
     int64_t* row_ptr; int32_t* col_idx; int64_t* diag_pos; Pair* pairs; int32_t* status;
     // temporaries
     uint64_t* keys_a; uint64_t* keys_b; int32_t* vals_b;
-    int32_t* hist; int32_t* hist_scan; int32_t* sums32; int64_t* sums64;
-    int32_t* cnt; int32_t* cnt_up; int64_t* pair_ptr;
+    int32_t* hist; int32_t* hist_scan; int32_t* sums32; Sum2* sums64;
+    Count2* cnt; int64_t* pair_ptr;
     int32_t* cell_start; int32_t* cell_end; double* bbox_part; CloudGrid* grids;
     int64_t* d_off; int32_t* bad;
     size_t bytes;
@@ -471,16 +616,15 @@ static BuildLayout carve_build(void* ws, size_t ws_bytes, int64_t n, int32_t n_c
     L.hist = cv.take<int32_t>(hist_n);
     L.hist_scan = cv.take<int32_t>(hist_n + 1);
     L.sums32 = cv.take<int32_t>(nsum);
-    L.sums64 = cv.take<int64_t>(nsum);
-    L.cnt = cv.take<int32_t>(n);
-    L.cnt_up = cv.take<int32_t>(n);
+    L.sums64 = cv.take<Sum2>(nsum);
+    L.cnt = cv.take<Count2>(n);
     L.pair_ptr = cv.take<int64_t>(n + 1);
     L.cell_start = cv.take<int32_t>(total_cells);
     L.cell_end = cv.take<int32_t>(total_cells);
-    L.bbox_part = cv.take<double>((int64_t)n_clouds * BBOX_BLOCKS * 6);
+    L.bbox_part = cv.take<double>((int64_t)n_clouds * BBOX_BLOCKS * 6 + 1);   // the count of bad wires behind the boxes
+    L.bad = reinterpret_cast<int32_t*>(L.bbox_part + (int64_t)n_clouds * BBOX_BLOCKS * 6);
     L.grids = cv.take<CloudGrid>(n_clouds);
     L.d_off = cv.take<int64_t>(n_clouds + 1);
-    L.bad = cv.take<int32_t>(1);
     L.bytes = cv.off;
     return L;
 }
@@ -518,11 +662,11 @@ chaff_status build_cloud(const chaff_params* p, const int64_t* cloud_off, const 
     hipLaunchKernelGGL(k_bbox, dim3(BBOX_BLOCKS, nc), dim3(256), 0, st, center, tangent, length, radius,
                        (const int64_t*)L.d_off, L.bbox_part, L.bad, (int)p->n_seg);
     CHAFF_LAUNCH_CHECK();
-    std::vector<double> part((size_t)nc * BBOX_BLOCKS * 6);
-    int32_t bad = 0;
+    std::vector<double> part((size_t)nc * BBOX_BLOCKS * 6 + 1);
     CHAFF_HIP(hipMemcpyAsync(part.data(), L.bbox_part, part.size() * sizeof(double), hipMemcpyDeviceToHost, st));
-    CHAFF_HIP(hipMemcpyAsync(&bad, L.bad, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     CHAFF_HIP(hipStreamSynchronize(st));
+    int32_t bad = 0;
+    std::memcpy(&bad, &part.back(), sizeof(bad));
     if (bad)
         return fail(CHAFF_EINVAL, std::to_string(bad) +
                                       " wires have a non-finite centre, a tangent that is not unit "
@@ -588,38 +732,45 @@ chaff_status build_cloud(const chaff_params* p, const int64_t* cloud_off, const 
     hipLaunchKernelGGL(k_keys, dim3(grid1d(maxc, 256, 4096), nc), dim3(256), 0, st, center,
                        (const CloudGrid*)L.grids, dim_bits, L.keys_a, L.perm);
     CHAFF_LAUNCH_CHECK();
-    const int n_tiles = (int)((n + RS_TILE - 1) / RS_TILE);
-    uint64_t* kin = L.keys_a; int32_t* vin = L.perm;
-    uint64_t* kout = L.keys_b; int32_t* vout = L.vals_b;
-    const int passes = (key_bits + 7) / 8;
-    for (int ps = 0; ps < passes; ++ps) {
-        ProfScope prof_sort("nbr_sort_pass", st);
-        hipLaunchKernelGGL(k_rs_hist, dim3(n_tiles), dim3(RS_THREADS), 0, st, (const uint64_t*)kin, n,
-                           8 * ps, L.hist, n_tiles);
-        CHAFF_LAUNCH_CHECK();
-        chaff_status s = exclusive_scan<int32_t, int32_t>(L.hist, (int64_t)256 * n_tiles, L.hist_scan,
-                                                          L.sums32, st);
-        if (s != CHAFF_OK) return s;
-        hipLaunchKernelGGL(k_rs_scatter, dim3(n_tiles), dim3(RS_THREADS), 0, st, (const uint64_t*)kin,
-                           (const int32_t*)vin, kout, vout, n, 8 * ps, (const int32_t*)L.hist_scan, n_tiles);
-        CHAFF_LAUNCH_CHECK();
-        std::swap(kin, kout);
-        std::swap(vin, vout);
-    }
-    if (vin != L.perm) {  // odd pass count: bring the result home
-        CHAFF_HIP(hipMemcpyAsync(L.perm, vin, n * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
-        CHAFF_HIP(hipMemcpyAsync(L.keys_a, kin, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
-    }
     const uint64_t* keys = L.keys_a;
+    if (n <= RANK_SORT_MAX) {
+        ProfScope prof_sort("nbr_sort_pass", st);
+        hipLaunchKernelGGL(k_rank_sort, dim3((unsigned)((n + 7) / 8)), dim3(256), 0, st, (const uint64_t*)L.keys_a,
+                           (int32_t)n, L.keys_b, L.perm);
+        CHAFF_LAUNCH_CHECK();
+        keys = L.keys_b;
+    } else {
+        const int n_tiles = (int)((n + RS_TILE - 1) / RS_TILE);
+        uint64_t* kin = L.keys_a; int32_t* vin = L.perm;
+        uint64_t* kout = L.keys_b; int32_t* vout = L.vals_b;
+        const int passes = (key_bits + 7) / 8;
+        for (int ps = 0; ps < passes; ++ps) {
+            ProfScope prof_sort("nbr_sort_pass", st);
+            hipLaunchKernelGGL(k_rs_hist, dim3(n_tiles), dim3(RS_THREADS), 0, st, (const uint64_t*)kin, n,
+                               8 * ps, L.hist, n_tiles);
+            CHAFF_LAUNCH_CHECK();
+            chaff_status s = exclusive_scan<int32_t, int32_t>(L.hist, (int64_t)256 * n_tiles, L.hist_scan,
+                                                              L.sums32, st);
+            if (s != CHAFF_OK) return s;
+            hipLaunchKernelGGL(k_rs_scatter, dim3(n_tiles), dim3(RS_THREADS), 0, st, (const uint64_t*)kin,
+                               (const int32_t*)vin, kout, vout, n, 8 * ps, (const int32_t*)L.hist_scan, n_tiles);
+            CHAFF_LAUNCH_CHECK();
+            std::swap(kin, kout);
+            std::swap(vin, vout);
+        }
+        if (vin != L.perm) {  // odd pass count: bring the result home
+            CHAFF_HIP(hipMemcpyAsync(L.perm, vin, n * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
+            CHAFF_HIP(hipMemcpyAsync(L.keys_a, kin, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
+        }
+    }
 
     // --- internal geometry and cell tables
     hipLaunchKernelGGL(k_gather, dim3(grid1d(n)), dim3(256), 0, st, center, tangent, length, radius,
                        (const int32_t*)L.perm, (const CloudGrid*)L.grids, nc, n, L.wires, L.iperm,
                        L.wire_cloud);
     CHAFF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid1d(total_cells)), dim3(256), 0, st, L.cell_start, total_cells, 0);
-    CHAFF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid1d(total_cells)), dim3(256), 0, st, L.cell_end, total_cells, 0);
+    hipLaunchKernelGGL(k_clear_cells, dim3(grid1d(total_cells)), dim3(256), 0, st, L.cell_start, L.cell_end,
+                       total_cells);
     CHAFF_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_cells, dim3(grid1d(n)), dim3(256), 0, st, (const Wire*)L.wires,
                        (const int32_t*)L.wire_cloud, keys, (const CloudGrid*)L.grids, n, L.cell_start,
@@ -630,20 +781,19 @@ chaff_status build_cloud(const chaff_params* p, const int64_t* cloud_off, const 
     const double dc2 = std::isfinite(p->d_c) ? p->d_c * p->d_c : INFINITY;
     {
         ProfScope pc("nbr_count", st);
-        hipLaunchKernelGGL(k_count, dim3(grid1d(n, 128)), dim3(128), 0, st, (const Wire*)L.wires,
-                           (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
-                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, dc2, L.cnt, L.cnt_up);
+        hipLaunchKernelGGL(k_near<0>, dim3((unsigned)((n + NEAR_WIRES - 1) / NEAR_WIRES)), dim3(32 * NEAR_WIRES), 0, st,
+                           (const Wire*)L.wires, (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
+                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, dc2, L.cnt,
+                           (const int64_t*)nullptr, (const int64_t*)nullptr, (int32_t*)nullptr, (int64_t*)nullptr,
+                           (Pair*)nullptr);
     }
     CHAFF_LAUNCH_CHECK();
-    chaff_status s1 = exclusive_scan<int32_t, int64_t>(L.cnt, n, L.row_ptr, L.sums64, st);
+    Sum2 *d_tot = nullptr, tot{0, 0};
+    chaff_status s1 = scan2(L.cnt, n, L.row_ptr, L.pair_ptr, L.sums64, &d_tot, st);
     if (s1 != CHAFF_OK) return s1;
-    s1 = exclusive_scan<int32_t, int64_t>(L.cnt_up, n, L.pair_ptr, L.sums64, st);
-    if (s1 != CHAFF_OK) return s1;
-    int64_t tot[2] = {0, 0};
-    CHAFF_HIP(hipMemcpyAsync(&tot[0], L.row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    CHAFF_HIP(hipMemcpyAsync(&tot[1], L.pair_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    CHAFF_HIP(hipMemcpyAsync(&tot, d_tot, sizeof(tot), hipMemcpyDeviceToHost, st));
     CHAFF_HIP(hipStreamSynchronize(st));
-    const int64_t nnzb = tot[0], n_pairs = tot[1];
+    const int64_t nnzb = tot.all, n_pairs = tot.up;
     *nnzb_out = nnzb;
     if (nnzb > p->max_nnzb || n_pairs > std::max<int64_t>((p->max_nnzb - n) / 2, 1))
         return fail(CHAFF_EWORKSPACE, "pattern needs " + std::to_string(nnzb) +
@@ -653,11 +803,10 @@ chaff_status build_cloud(const chaff_params* p, const int64_t* cloud_off, const 
     // --- pass 2: column indices, diagonal positions, unique pairs
     {
         ProfScope pp("nbr_pattern", st);
-        hipLaunchKernelGGL(k_pattern, dim3(grid1d(n, 128)), dim3(128), 0, st, (const Wire*)L.wires,
-                           (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
-                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, dc2,
-                           (const int64_t*)L.row_ptr, (const int64_t*)L.pair_ptr, L.col_idx, L.diag_pos,
-                           L.pairs);
+        hipLaunchKernelGGL(k_near<1>, dim3((unsigned)((n + NEAR_WIRES - 1) / NEAR_WIRES)), dim3(32 * NEAR_WIRES), 0, st,
+                           (const Wire*)L.wires, (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
+                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, dc2, (Count2*)nullptr,
+                           (const int64_t*)L.row_ptr, (const int64_t*)L.pair_ptr, L.col_idx, L.diag_pos, L.pairs);
     }
     CHAFF_LAUNCH_CHECK();
     if (n_pairs > 0) {
