@@ -9,8 +9,9 @@
 //    chunks of one cloud, lanes split between RHS columns and wire slots, the
 //    slots folded with wavefront shuffles and the waves through LDS; a second
 //    pass sums the chunks of each cloud in order (no atomics, bit-reproducible);
-//  * bistatic: one thread per direction, the chunk's wires and currents
-//    staged in LDS, partial sums per chunk, same second pass.
+//  * bistatic: one or two directions per thread, the chunk's wires and currents,
+//    folded about each wire's centre, staged in LDS, partial sums per chunk,
+//    same second pass.
 #include "common.hpp"
 #include "prof.hpp"
 
@@ -26,6 +27,121 @@ constexpr int ff_chunk(int nb) { return nb <= 7 ? 256 : 64; }
 
 __device__ __forceinline__ double sinc_ff(double x) {
     return fabs(x) < 1e-4 ? 1.0 - x * x / 6.0 : sin(x) / x;
+}
+
+// ---- phases.  All arguments are kept in half turns (units of pi), so that the
+// range reduction is one exact subtraction of a whole number instead of the
+// library's reduction by multiples of pi/2, and the quadrant is a sign.
+// Taylor series of sin(pi x) / (pi x) and cos(pi x) in x^2: for |x| <= 1/4 the
+// first omitted terms are 6e-17 and 2e-18.
+// a t + c with the coefficient in a scalar register pair: left to itself the
+// compiler moves every coefficient into vector registers first, one move per
+// step of the series.
+__device__ __forceinline__ double horner(double a, double t, double c) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(t), "s"(c));
+    return d;
+}
+// sr = sin(pi x) / (pi x), c = cos(pi x)
+__device__ __forceinline__ void sinccospi_small(double x, double& sr, double& c) {
+    const double t = (PI_F * x) * (PI_F * x);
+    double p = horner(t, -1.0 / 1307674368000.0, 1.0 / 6227020800.0);
+    p = horner(p, t, -1.0 / 39916800.0);
+    p = horner(p, t, 1.0 / 362880.0);
+    p = horner(p, t, -1.0 / 5040.0);
+    p = horner(p, t, 1.0 / 120.0);
+    p = horner(p, t, -1.0 / 6.0);
+    sr = fma(p, t, 1.0);
+    double q = horner(t, 1.0 / 20922789888000.0, -1.0 / 87178291200.0);
+    q = horner(q, t, 1.0 / 479001600.0);
+    q = horner(q, t, -1.0 / 3628800.0);
+    q = horner(q, t, 1.0 / 40320.0);
+    q = horner(q, t, -1.0 / 720.0);
+    q = horner(q, t, 1.0 / 24.0);
+    q = fma(q, t, -0.5);
+    c = fma(q, t, 1.0);
+}
+// sin(pi x), cos(pi x) for any finite x (exact quadrant: 2 x - rint(2 x) is exact)
+__device__ __forceinline__ void sincospi_any(double x, double& s, double& c) {
+    const double n = rint(2.0 * x);
+    const double y = fma(-0.5, n, x);
+    double sn, cs;
+    sinccospi_small(y, sn, cs);
+    sn *= PI_F * y;
+    const int k = (int)(n - 4.0 * floor(0.25 * n));   // quadrant, exact below 2^53
+    const double a = (k & 1) ? cs : sn, b = (k & 1) ? sn : cs;
+    s = (k & 2) ? -a : a;
+    c = ((k + 1) & 2) ? -b : b;
+}
+
+// Far-field terms of one wire per direction, with the phases in half turns:
+// kp = 2/lambda, so kp r.c is the phase of its centre in units of pi and
+// beta = kp (r.t) D that of one segment.  The rooftops sit symmetrically about
+// the centre, s_q = (q - MID) D, so with the currents folded beforehand into
+// sums and differences (fold_currents) the sum over q is real arithmetic on
+// cos(m pi beta), sin(m pi beta), walked by their three-term recurrence, and
+// sinc^2 takes the half angle from the same evaluation.
+struct FoldDir {   // one direction, the constants pre-multiplied
+    double rx, ry, rz, ex, ey, ez;
+};
+template <int NBW>
+struct FoldWire {   // one wire: t D, kp D t, c
+    double px, py, pz, bx, by, bz, cx, cy, cz;
+};
+
+// x[q] -> f[0] = x_MID, f[2m-1] = x_{MID+m} + x_{MID-m}, f[2m] = j (x_{MID+m} - x_{MID-m})
+template <int NBW>
+__device__ __forceinline__ c128 folded(const c128* __restrict__ x, int64_t xstride, int e) {
+    constexpr int MID = NBW / 2;
+    if (e == 0) return x[MID * xstride];
+    const int m = (e + 1) / 2;
+    const c128 a = x[(MID + m) * xstride], b = x[(MID - m) * xstride];
+    return (e & 1) ? cadd(a, b) : c128{-(a.im - b.im), a.re - b.re};
+}
+
+template <int NBW>
+__device__ __forceinline__ FoldWire<NBW> fold_wire(const Wire& w, double kp) {
+    const double D = w.len / (NBW + 1);
+    return FoldWire<NBW>{w.tx * D, w.ty * D, w.tz * D, kp * D * w.tx, kp * D * w.ty, kp * D * w.tz,
+                         w.cx, w.cy, w.cz};
+}
+
+template <int NBW>
+__device__ __forceinline__ void add_folded(c128& acc, const FoldWire<NBW>& w, const c128* __restrict__ f,
+                                           const FoldDir& d, double kp) {
+    constexpr int MID = NBW / 2;
+    const double env = w.px * d.ex + w.py * d.ey + w.pz * d.ez;
+    const double b = w.bx * d.rx + w.by * d.ry + w.bz * d.rz;    // phase of a segment, half turns
+    const double ph = kp * (w.cx * d.rx + w.cy * d.ry + w.cz * d.rz);   // phase of the centre
+    double sc, sh, ch;   // half a segment: sinc, sine, cosine
+    if (!__any(fabs(b) > 0.5)) {   // segments of at most a quarter wavelength never leave the series
+        sinccospi_small(0.5 * b, sc, ch);
+        sh = sc * (PI_F * 0.5 * b);
+    } else {
+        sincospi_any(0.5 * b, sh, ch);
+        const double h = PI_F * 0.5 * b;
+        sc = fabs(h) < 1e-4 ? 1.0 - h * h / 6.0 : sh / h;
+    }
+    const double s1 = 2.0 * sh * ch, c1 = fma(-2.0 * sh, sh, 1.0);
+    c128 a = f[0];
+    double sm = s1, cm = c1, s0 = 0.0, c0 = 1.0;
+#pragma unroll
+    for (int m = 1; m <= MID; ++m) {
+        const c128 p = f[2 * m - 1], q = f[2 * m];
+        a.re = fma(p.re, cm, fma(q.re, sm, a.re));
+        a.im = fma(p.im, cm, fma(q.im, sm, a.im));
+        const double sn = fma(2.0 * c1, sm, -s0), cn = fma(2.0 * c1, cm, -c0);
+        s0 = sm;
+        c0 = cm;
+        sm = sn;
+        cm = cn;
+    }
+    double ps, pc;
+    sincospi_any(ph, ps, pc);
+    const double g = env * sc * sc;
+    const double gr = g * pc, gi = g * ps;
+    acc.re = fma(gr, a.re, fma(-gi, a.im, acc.re));
+    acc.im = fma(gr, a.im, fma(gi, a.re, acc.im));
 }
 
 // one wire's contribution for direction (rx,ry,rz), polarisation (ex,ey,ez)
@@ -110,43 +226,106 @@ static void launch_mono(dim3 grid_x, int64_t R, hipStream_t st, const Wire* wire
     }
 }
 
-// partial[chunk][r][m] for every (rhs r, direction m)
-template <int NBW>
+// partial[chunk][r][m] for every (rhs r, direction m).  A workgroup stages its
+// chunk's folded wires and currents in LDS; a thread takes DPT directions, and
+// the wires are dealt to SL slots of 256 / SL threads, whose sums are added in
+// slot order.
+//   Bound: FP64 arithmetic, about 85 operations per wire and direction (the
+// reference form, two sincos and a sine of the library and a complex phase
+// product per rooftop, takes about 250): 2,000 wires x 65,160 directions
+// 1,015 -> 450 us, the whole call.  Two directions per thread halve the LDS reads (23 broadcast doubles
+// per wire) and are taken where they leave four workgroups per CU; four slots
+// where the directions alone leave CUs idle (2,000 wires: 360 directions 233 ->
+// 60 us, 8,000 directions 225 -> 97 us).
+template <int NBW, int DPT, int SL>
 __global__ __launch_bounds__(256) void k_bistatic(const Wire* __restrict__ wires, const int32_t* __restrict__ perm,
                                                   const int64_t* __restrict__ chunk_w0, int64_t R, int64_t M,
                                                   const c128* __restrict__ X, const double* __restrict__ dir,
-                                                  const double* __restrict__ pol, double k, c128* __restrict__ part) {
+                                                  const double* __restrict__ pol, double kp, c128* __restrict__ part) {
     constexpr int CH = ff_chunk(NBW);
-    __shared__ Wire sw[CH];
+    constexpr int TD = 256 / SL;   // threads along the directions
+    static_assert(SL == 1 || DPT == 1, "slots are for few directions");
+    __shared__ FoldWire<NBW> sw[CH];
     __shared__ c128 sx[CH * NBW];
     const int ch = blockIdx.y;
     const int64_t r = blockIdx.z;
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int slot = threadIdx.x / TD;
+    const int64_t m0 = (int64_t)blockIdx.x * TD * DPT + threadIdx.x % TD;
     const int64_t w0 = chunk_w0[ch], w1 = chunk_w0[ch + 1];
     const int nw = (int)(w1 - w0);
-    for (int t = threadIdx.x; t < nw; t += blockDim.x) {
-        sw[t] = wires[w0 + t];
-        const int64_t p = perm[w0 + t];
-        for (int q = 0; q < NBW; ++q) sx[t * NBW + q] = X[(p * NBW + q) * R + r];
+    for (int t = threadIdx.x; t < nw; t += 256) sw[t] = fold_wire<NBW>(wires[w0 + t], kp);
+    for (int t = threadIdx.x; t < nw * NBW; t += 256) {
+        const int wl = t / NBW;
+        sx[t] = folded<NBW>(X + (int64_t)perm[w0 + wl] * NBW * R + r, R, t - wl * NBW);
     }
     __syncthreads();
-    if (m >= M) return;
-    const double rx = dir[3 * m], ry = dir[3 * m + 1], rz = dir[3 * m + 2];
-    const double ex = pol[3 * m], ey = pol[3 * m + 1], ez = pol[3 * m + 2];
-    c128 acc = {0, 0};
-    for (int t = 0; t < nw; ++t) acc = cadd(acc, wire_term<NBW>(sw[t], &sx[t * NBW], 1, k, rx, ry, rz, ex, ey, ez));
-    part[((int64_t)ch * R + r) * M + m] = acc;
+    FoldDir d[DPT];
+    c128 acc[DPT];
+#pragma unroll
+    for (int u = 0; u < DPT; ++u) {
+        const int64_t m = m0 + u * TD < M ? m0 + u * TD : M - 1;
+        d[u] = FoldDir{dir[3 * m], dir[3 * m + 1], dir[3 * m + 2], pol[3 * m], pol[3 * m + 1], pol[3 * m + 2]};
+        acc[u] = c128{0, 0};
+    }
+    for (int t = slot; t < nw; t += SL)
+#pragma unroll
+        for (int u = 0; u < DPT; ++u) add_folded<NBW>(acc[u], sw[t], &sx[t * NBW], d[u], kp);
+    if (SL > 1) {   // the staged currents are done with: their space takes the slots' sums
+        __syncthreads();
+        sx[threadIdx.x] = acc[0];
+        __syncthreads();
+        if (slot > 0) return;
+#pragma unroll
+        for (int k = 1; k < SL; ++k) acc[0] = cadd(acc[0], sx[k * TD + threadIdx.x]);
+    }
+#pragma unroll
+    for (int u = 0; u < DPT; ++u)
+        if (m0 + u * TD < M) part[((int64_t)ch * R + r) * M + m0 + u * TD] = acc[u];
 }
 
-// sigma[cloud][j] = |sum over the cloud's chunks of part[chunk][j]|^2 / (4 pi), j < J
+template <int NBW>
+static void launch_bistatic(int nch, int64_t R, int64_t M, hipStream_t st, const Wire* wires, const int32_t* perm,
+                            const int64_t* w0, const c128* X, const double* dir, const double* pol, double kp,
+                            c128* part) {
+    const double wide = (double)((M + 511) / 512) * nch * R;   // workgroups at two directions per thread
+#define CHAFF_BI(DPT, SL)                                                                                         \
+    hipLaunchKernelGGL((k_bistatic<NBW, DPT, SL>), dim3((unsigned)((M + 256 / SL * DPT - 1) / (256 / SL * DPT)),  \
+                                                        (unsigned)nch, (unsigned)R),                              \
+                       dim3(256), 0, st, wires, perm, w0, R, M, X, dir, pol, kp, part)
+    if (wide >= 1024) CHAFF_BI(2, 1);
+    else if (2.0 * wide >= 512) CHAFF_BI(1, 1);
+    else CHAFF_BI(1, 4);
+#undef CHAFF_BI
+}
+
+// part[first chunk of the group][j] = sum over a group of FF_GROUP chunks of one
+// cloud, in place (a thread reads only what it overwrites), chunks in order.
+constexpr int FF_GROUP = 32;
+__global__ __launch_bounds__(256) void k_ff_groups(c128* __restrict__ part, const int32_t* __restrict__ cloud_chunk_off,
+                                                   int64_t J) {
+    const int c = blockIdx.z;
+    const int64_t j = (int64_t)blockIdx.y * 256 + threadIdx.x;
+    const int a = cloud_chunk_off[c] + (int)blockIdx.x * FF_GROUP;
+    const int b = min(a + FF_GROUP, cloud_chunk_off[c + 1]);
+    if (a >= b || j >= J) return;
+    c128 acc = {0, 0};
+#pragma unroll 8
+    for (int ch = a; ch < b; ++ch) acc = cadd(acc, part[(int64_t)ch * J + j]);
+    part[(int64_t)a * J + j] = acc;
+}
+
+// sigma[cloud][j] = |sum over the cloud's chunks of part[chunk][j]|^2 / (4 pi), j < J;
+// step FF_GROUP after k_ff_groups, else 1
 __global__ void k_ff_finish(const c128* __restrict__ part, const int32_t* __restrict__ cloud_chunk_off,
-                            int n_clouds, int64_t J, double* __restrict__ sigma) {
+                            int n_clouds, int64_t J, int step, double* __restrict__ sigma) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)n_clouds * J) return;
     const int c = (int)(t / J);
     const int64_t j = t - (int64_t)c * J;
     c128 acc = {0, 0};
-    for (int ch = cloud_chunk_off[c]; ch < cloud_chunk_off[c + 1]; ++ch) acc = cadd(acc, part[(int64_t)ch * J + j]);
+#pragma unroll 8
+    for (int ch = cloud_chunk_off[c]; ch < cloud_chunk_off[c + 1]; ch += step)
+        acc = cadd(acc, part[(int64_t)ch * J + j]);
     sigma[t] = (acc.re * acc.re + acc.im * acc.im) / (4.0 * PI_F);
 }
 
@@ -204,19 +383,30 @@ chaff_status rcs(Cloud* c, const void* Xv, int64_t R, const double* dir, const d
                 launch_mono<NSEG_PAPER - 1>(dim3(nch), R, st, (const Wire*)c->wires, (const int32_t*)c->perm,
                                             (const int64_t*)d_w0, nch, X, dir, pol, k, part);
         } else {
-            dim3 grid((unsigned)((M + 255) / 256), nch, (unsigned)R);
             if (c->nseg == NSEG)
-                hipLaunchKernelGGL(k_bistatic<NSEG - 1>, grid, dim3(256), 0, st, (const Wire*)c->wires,
-                                   (const int32_t*)c->perm, (const int64_t*)d_w0, R, M, X, dir, pol, k, part);
+                launch_bistatic<NSEG - 1>(nch, R, M, st, (const Wire*)c->wires, (const int32_t*)c->perm,
+                                          (const int64_t*)d_w0, X, dir, pol, 2.0 / c->wavelength, part);
             else
-                hipLaunchKernelGGL(k_bistatic<NSEG_PAPER - 1>, grid, dim3(256), 0, st, (const Wire*)c->wires,
-                                   (const int32_t*)c->perm, (const int64_t*)d_w0, R, M, X, dir, pol, k, part);
+                launch_bistatic<NSEG_PAPER - 1>(nch, R, M, st, (const Wire*)c->wires, (const int32_t*)c->perm,
+                                                (const int64_t*)d_w0, X, dir, pol, 2.0 / c->wavelength, part);
         }
         CHAFF_LAUNCH_CHECK();
     }
     const int64_t tot = (int64_t)c->n_clouds * J;
+    // A thread sums the chunks of its (cloud, column) one after the other; more
+    // than two groups of them are summed by groups first (64 columns, 3,907
+    // chunks: 1,509 -> 14 us).
+    int most = 0;
+    for (int k = 0; k < c->n_clouds; ++k) most = std::max(most, coff[k + 1] - coff[k]);
+    const int step = most > 2 * FF_GROUP && c->n_clouds <= 65535 && (J + 255) / 256 <= 65535 ? FF_GROUP : 1;
+    if (step > 1) {
+        hipLaunchKernelGGL(k_ff_groups, dim3((unsigned)((most + FF_GROUP - 1) / FF_GROUP), (unsigned)((J + 255) / 256),
+                                             (unsigned)c->n_clouds),
+                           dim3(256), 0, st, part, (const int32_t*)d_coff, J);
+        CHAFF_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL(k_ff_finish, dim3((unsigned)std::max<int64_t>(1, (tot + 255) / 256)), dim3(256), 0, st,
-                       (const c128*)part, (const int32_t*)d_coff, c->n_clouds, J, sigma);
+                       (const c128*)part, (const int32_t*)d_coff, c->n_clouds, J, step, sigma);
     CHAFF_LAUNCH_CHECK();
     CHAFF_HIP(hipStreamSynchronize(st));  // host staging vectors go out of scope
     return CHAFF_OK;
