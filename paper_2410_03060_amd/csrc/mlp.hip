@@ -9,10 +9,8 @@
 // tile of A (rows = samples) by a 32 x 16 tile of B into a 16 x 16 FP32
 // accumulator.  Each lane supplies 8 consecutive k of one row of A and of
 // one column of B (A and B stored k-contiguous), and receives 4 consecutive
-// rows of one output column.  Every intermediate of the backward pass is
-// written in the layout its consumer needs (row-major for the next data
-// product, transposed for the weight-gradient product), so no product reads
-// strided memory.
+// rows of one output column.  The operands of the weight gradients are written
+// transposed, so no product reads strided memory.
 #include <algorithm>
 
 #include "common.hpp"
@@ -53,24 +51,6 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {
 }
 __device__ __forceinline__ bf16x8 zero8() { return __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0)); }
 
-// acc[mt][nt] += A rows ap[mt] (k-contiguous, nullptr = zero row) x B rows bp[nt], k in [k0, k1).
-template <int MT, int NT>
-__device__ __forceinline__ void mma_rows(const uint16_t* const (&ap)[MT], const uint16_t* const (&bp)[NT],
-                                         int64_t k0, int64_t k1, f32x4 (&acc)[MT][NT]) {
-    const int kb = ((threadIdx.x & 63) >> 4) * 8;
-    for (int64_t k = k0; k < k1; k += 32) {
-        bf16x8 a[MT], b[NT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) a[i] = ap[i] ? ld8(ap[i] + k + kb) : zero8();
-#pragma unroll
-        for (int j = 0; j < NT; ++j) b[j] = ld8(bp[j] + k + kb);
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-}
-
 // logistic function with the hardware exponential and reciprocal (about 1 ulp each;
 // the result is rounded to BF16 or enters a BF16 product)
 __device__ __forceinline__ float sigmoidf(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
@@ -109,106 +89,6 @@ __global__ void k_pack(const float* __restrict__ th, Packed pk) {
     if (tr) { o = (int)(t / nin); i = (int)(t % nin); }
     else { i = (int)(t / pad); o = (int)(t % pad); }
     dst[t] = o < nout ? f2bf(th[off + i * nout + o]) : (uint16_t)0;
-}
-
-// ------------------------------------------------------------------ forward layers
-struct FwdArgs {
-    const uint16_t* A;      // [*][lda] BF16 layer input (row m at idx[m] for the first layer)
-    int lda;
-    const int64_t* a_idx;   // optional row gather of A (first layer)
-    const int64_t* t_idx;   // optional row gather of the targets
-    int64_t M, Mpad;        // valid rows, padded rows
-    const uint16_t* Wt;     // [N][K]
-    int K;
-    const float* bias;
-    // hidden layers
-    uint16_t* a_out;        // [Mpad][128] BF16 SiLU(z)
-    float* z_out;           // [Mpad][128] FP32 pre-activation (training)
-    uint16_t* aT_out;       // [128][Mpad] BF16 SiLU(z) transposed (training)
-    // output layer
-    float* Y;               // [M][14] (inference)
-    const float* T;         // [*][14] targets (training)
-    uint16_t* dY;           // [Mpad][32] BF16 2 (y - t) (training)
-    uint16_t* dYT;          // [16][Mpad]
-    float* loss_part;       // [Mpad/32] per-wave sums of (y - t)^2
-};
-
-template <bool LAST, bool TRAIN>
-__global__ __launch_bounds__(256) void k_fwd(FwdArgs g) {
-    constexpr int NT = LAST ? 1 : NH / 16;
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t m0 = wave * 32;
-    const uint16_t* ap[2];
-    const uint16_t* bp[NT];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int64_t m = m0 + 16 * i + (lane & 15);
-        const int64_t src = m < g.M ? (g.a_idx ? g.a_idx[m] : m) : -1;
-        ap[i] = src >= 0 ? g.A + src * g.lda : nullptr;
-    }
-#pragma unroll
-    for (int j = 0; j < NT; ++j) bp[j] = g.Wt + (int64_t)(16 * j + (lane & 15)) * g.K;
-    f32x4 acc[2][NT];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mma_rows<2, NT>(ap, bp, 0, g.K, acc);
-
-    const int col = lane & 15;
-    const int rq = (lane >> 4) * 4;
-    if constexpr (!LAST) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int n = 16 * j + col;
-                const float b = g.bias[n];
-                const int64_t mb = m0 + 16 * i + rq;
-                uint16_t h[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float z = acc[i][j][r] + b;
-                    h[r] = f2bf(z * sigmoidf(z));
-                    g.a_out[(mb + r) * NH + n] = h[r];
-                    if (TRAIN) g.z_out[(mb + r) * NH + n] = z;
-                }
-                if (TRAIN)
-                    *reinterpret_cast<uint2*>(g.aT_out + (int64_t)n * g.Mpad + mb) =
-                        make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-            }
-    } else {
-        const float b = col < NO ? g.bias[col] : 0.f;
-        float sq = 0.f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int64_t mb = m0 + 16 * i + rq;
-            uint16_t h[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t m = mb + r;
-                const float y = acc[i][0][r] + b;
-                if (!TRAIN) {
-                    if (m < g.M && col < NO) g.Y[m * NO + col] = y;
-                } else {
-                    float d = 0.f;
-                    if (m < g.M && col < NO) d = y - g.T[(g.t_idx ? g.t_idx[m] : m) * NO + col];
-                    sq += d * d;
-                    h[r] = f2bf(2.0f * d);
-                    g.dY[m * DYLD + col] = h[r];
-                    g.dY[m * DYLD + NOP + col] = 0;
-                }
-            }
-            if (TRAIN)
-                *reinterpret_cast<uint2*>(g.dYT + (int64_t)col * g.Mpad + mb) =
-                    make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-        }
-        if (TRAIN) {
-            sq = wave_sum(sq);
-            if (lane == 0) g.loss_part[wave] = sq;
-        }
-    }
 }
 
 // ------------------------------------------------------------------ fused inference
@@ -359,145 +239,289 @@ __global__ __launch_bounds__(256) void k_fwd_fused(const uint16_t* __restrict__ 
     }
 }
 
-// ------------------------------------------------------------------ backward
-// dZ_prev = (dZ W^T) * SiLU'(z_prev): A = dZ [Mpad][lda], B = Wn [128][K].
-struct BwdArgs {
-    const uint16_t* dZ;
-    int lda, K;
-    int64_t Mpad;
-    const uint16_t* Wn;
-    const float* z_prev;     // [Mpad][128]
-    uint16_t* dZ_out;        // [Mpad][128] or nullptr
-    uint16_t* dZT_out;       // [128][Mpad]
+// ------------------------------------------------------------------ training
+// One step is four launches: the BF16 operands (k_pack), forward and backward
+// of every row (k_train_rows), the partial weight and bias gradients
+// (k_train_wgrad), their sum and Adam (k_reduce).
+//   Rows: a workgroup takes 16 MT rows through all four layers and back.  Wave w
+// owns 32 of the 128 columns of every hidden layer; pre-activations stay in its
+// registers for the backward pass, activations and layer gradients pass through
+// LDS, and only the transposed operands of the weight gradients are written.
+//   Bound: latency at training batches (seven dependent layer products with
+// weights from L2), so the rows are spread as thinly as 512 workgroups allow:
+// the layers as separate launches of 32 rows per wave left 4,096 rows on 32 of
+// the 256 CUs and took 17 launches: 210 us a step, now 31 us (rows 18, weight
+// gradients 11, sum and Adam 4 us).
+struct RowsArgs {
+    const uint16_t* feat;   // [*][192] BF16, row m at idx[m]
+    const int64_t* idx;     // optional row gather of feat and T
+    const float* T;         // [*][14] targets
+    int64_t M, Mpad;
+    Packed pk;
+    const float* th;
+    uint16_t *fT, *aT1, *aT2, *aT3;           // [features or units][Mpad] BF16
+    uint16_t *dYT, *dZT3, *dZT2, *dZT1;       // [units][Mpad] BF16 (dYT: 16 rows)
+    float* loss_part;       // [workgroups] sums of (y - t)^2
 };
 
-__global__ __launch_bounds__(256) void k_bwd(BwdArgs g) {
-    constexpr int NT = NH / 16;
-    const int lane = threadIdx.x & 63;
-    const int64_t m0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
-    const uint16_t* ap[2];
-    const uint16_t* bp[NT];
+constexpr int FLDY = DYLD + 8;   // padded LDS row stride of dL/dy
+
+template <int MT>
+__global__ __launch_bounds__(256) void k_train_rows(RowsArgs g) {
+    constexpr int NTW = NH / 64;   // 16-column tiles per wave
+    __shared__ __align__(16) uint16_t act[2][16 * MT * FLDH];
+    __shared__ __align__(16) uint16_t dy[16 * MT * FLDY];
+    __shared__ float sq_s[4];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int l16 = lane & 15, rq = (lane >> 4) * 4, kb = (lane >> 4) * 8;
+    const int64_t m0 = (int64_t)blockIdx.x * (16 * MT);
+    f32x4 z[3][MT][NTW];
+
+    // acc += A B^T over K, A [16 MT][lda] in LDS, B the rows n of a packed operand [*][K]
+    auto product = [&](const uint16_t* A, int lda, const uint16_t* Bn, int K, f32x4 (&acc)[MT][NTW]) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) ap[i] = g.dZ + (m0 + 16 * i + (lane & 15)) * g.lda;
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) bp[j] = g.Wn + (int64_t)(16 * j + (lane & 15)) * g.K;
-    f32x4 acc[2][NT];
+            for (int j = 0; j < NTW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int k = 0; k < K; k += 32) {
+            bf16x8 a[MT], b[NTW];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mma_rows<2, NT>(ap, bp, 0, g.K, acc);
-    const int col = lane & 15;
-    const int rq = (lane >> 4) * 4;
+            for (int j = 0; j < NTW; ++j) b[j] = ld8(Bn + (int64_t)(16 * (NTW * w + j) + l16) * K + k + kb);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < MT; ++i) a[i] = ld8(A + (16 * i + l16) * lda + k + kb);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int n = 16 * j + col;
-            const int64_t mb = m0 + 16 * i + rq;
-            uint16_t h[4];
+            for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float z = g.z_prev[(mb + r) * NH + n];
-                const float s = sigmoidf(z);
-                h[r] = f2bf(acc[i][j][r] * (s * (1.0f + z * (1.0f - s))));
-                if (g.dZ_out) g.dZ_out[(mb + r) * NH + n] = h[r];
-            }
-            *reinterpret_cast<uint2*>(g.dZT_out + (int64_t)n * g.Mpad + mb) =
-                make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+                for (int j = 0; j < NTW; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         }
+    };
+    // four consecutive rows of column n: into the LDS tile (or nullptr) and the transposed operand
+    auto put = [&](uint16_t* tile, uint16_t* T, int i, int n, const uint16_t (&h)[4]) {
+        if (tile)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tile[(16 * i + rq + r) * FLDH + n] = h[r];
+        *reinterpret_cast<uint2*>(T + (int64_t)n * g.Mpad + m0 + 16 * i + rq) =
+            make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+    };
+    // z += bias, SiLU(z) to the tile and the transposed operand
+    auto activate = [&](f32x4 (&zz)[MT][NTW], const float* bias, uint16_t* tile, uint16_t* T) {
+#pragma unroll
+        for (int j = 0; j < NTW; ++j) {
+            const int n = 16 * (NTW * w + j) + l16;
+            const float b = bias[n];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                uint16_t h[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float v = zz[i][j][r] + b;
+                    zz[i][j][r] = v;
+                    h[r] = f2bf_hw(v * sigmoidf(v));
+                }
+                put(tile, T, i, n, h);
+            }
+        }
+        __syncthreads();
+    };
+    // dZ = (product) SiLU'(z), to the tile and the transposed operand
+    auto back = [&](const f32x4 (&acc)[MT][NTW], const f32x4 (&zz)[MT][NTW], uint16_t* tile, uint16_t* T) {
+#pragma unroll
+        for (int j = 0; j < NTW; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                uint16_t h[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float v = zz[i][j][r], sg = sigmoidf(v);
+                    h[r] = f2bf_hw(acc[i][j][r] * (sg * (1.0f + v * (1.0f - sg))));
+                }
+                put(tile, T, i, 16 * (NTW * w + j) + l16, h);
+            }
+    };
+
+    {   // layer 1: the features come from HBM; wave w also writes k-steps w, w + 4 of their transpose
+        const uint16_t* src[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int64_t m = m0 + 16 * i + l16;
+            src[i] = m < g.M ? g.feat + (g.idx ? g.idx[m] : m) * NF : nullptr;
+#pragma unroll
+            for (int j = 0; j < NTW; ++j) z[0][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int ks = 0; ks < NF / 32; ++ks) {
+            bf16x8 a[MT], b[NTW];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = src[i] ? ld8(src[i] + ks * 32 + kb) : zero8();
+#pragma unroll
+            for (int j = 0; j < NTW; ++j) b[j] = ld8(g.pk.wt1 + (16 * (NTW * w + j) + l16) * NF + ks * 32 + kb);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NTW; ++j)
+                    z[0][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], z[0][i][j], 0, 0, 0);
+            if ((ks & 3) == w)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const __bf16 f = a[i][e];
+                        g.fT[(int64_t)(ks * 32 + kb + e) * g.Mpad + m0 + 16 * i + l16] = __builtin_bit_cast(uint16_t, f);
+                    }
+        }
+    }
+    activate(z[0], g.th + OB1, act[0], g.aT1);
+    product(act[0], FLDH, g.pk.wt2, NH, z[1]);
+    activate(z[1], g.th + OB2, act[1], g.aT2);
+    product(act[1], FLDH, g.pk.wt3, NH, z[2]);
+    activate(z[2], g.th + OB3, act[0], g.aT3);
+    // output layer: 14 of 16 columns, one 16-row tile per wave; dL/dy = 2 (y - t)
+    float sq = 0.f;
+    for (int i = w; i < MT; i += 4) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < NH; k += 32)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(act[0] + (16 * i + l16) * FLDH + k + kb),
+                                                          ld8(g.pk.wt4 + l16 * NH + k + kb), acc, 0, 0, 0);
+        const float b = l16 < NO ? g.th[OB4 + l16] : 0.f;
+        uint16_t h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t m = m0 + 16 * i + rq + r;
+            float d = 0.f;
+            if (m < g.M && l16 < NO) d = (acc[r] + b) - g.T[(g.idx ? g.idx[m] : m) * NO + l16];
+            sq += d * d;
+            h[r] = f2bf_hw(2.0f * d);
+            dy[(16 * i + rq + r) * FLDY + l16] = h[r];
+            dy[(16 * i + rq + r) * FLDY + NOP + l16] = 0;
+        }
+        *reinterpret_cast<uint2*>(g.dYT + (int64_t)l16 * g.Mpad + m0 + 16 * i + rq) =
+            make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+    }
+    sq = wave_sum(sq);
+    if (lane == 0) sq_s[w] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) g.loss_part[blockIdx.x] = (sq_s[0] + sq_s[1]) + (sq_s[2] + sq_s[3]);
+    f32x4 acc[MT][NTW];
+    product(dy, FLDY, g.pk.wn4, DYLD, acc);
+    back(acc, z[2], act[1], g.dZT3);
+    __syncthreads();
+    product(act[1], FLDH, g.pk.wn3, NH, acc);
+    back(acc, z[1], act[0], g.dZT2);
+    __syncthreads();
+    product(act[0], FLDH, g.pk.wn2, NH, acc);
+    back(acc, z[0], nullptr, g.dZT1);
 }
 
-// Partial weight gradients over one split of SPLIT_ROWS rows:
-// part[s][w_off + i*n_out + o] = sum_m aT[i][m] dZT[o][m].
+// Partial gradients over one split of SPLIT_ROWS rows, one wave per unit:
+// part[s][w_off + i*n_out + o] = sum_m aT[i][m] dZT[o][m] for a 16 x 64 tile of
+// a layer's weights (16 x 14 of the last), or one bias part[s][off] = sum_m dZT[o][m].
+constexpr int WG_L1 = NF / 16 * (NH / 64), WG_L = NH / 16 * (NH / 64), WG_L4 = NH / 16;
+constexpr int WG_TILES = WG_L1 + 2 * WG_L + WG_L4, WG_UNITS = WG_TILES + NO + 3 * NH;
+
 template <int NT>
-__global__ __launch_bounds__(64) void k_wgrad(const uint16_t* __restrict__ aT, const uint16_t* __restrict__ dZT,
-                                              int64_t Mpad, int n_out, int w_off, float* __restrict__ part) {
-    const int lane = threadIdx.x;
-    const int i0 = blockIdx.x * 16, o0 = blockIdx.y * 16 * NT;
-    const int64_t s = blockIdx.z;
-    const uint16_t* ap[1] = {aT + (int64_t)(i0 + (lane & 15)) * Mpad};
+__device__ __forceinline__ void wgrad_tile(const uint16_t* __restrict__ aT, const uint16_t* __restrict__ dZT,
+                                           int64_t Mpad, int i0, int o0, int n_out, int64_t s, float* __restrict__ dst) {
+    const int lane = threadIdx.x & 63;
+    const int kb = (lane >> 4) * 8;
+    const uint16_t* ap = aT + (int64_t)(i0 + (lane & 15)) * Mpad + s * SPLIT_ROWS + kb;
     const uint16_t* bp[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) bp[j] = dZT + (int64_t)(o0 + 16 * j + (lane & 15)) * Mpad;
-    f32x4 acc[1][NT];
+    for (int j = 0; j < NT; ++j) bp[j] = dZT + (int64_t)(o0 + 16 * j + (lane & 15)) * Mpad + s * SPLIT_ROWS + kb;
+    f32x4 acc[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mma_rows<1, NT>(ap, bp, s * SPLIT_ROWS, (s + 1) * SPLIT_ROWS, acc);
-    float* dst = part + s * NPARAM + w_off;
+    for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int k = 0; k < SPLIT_ROWS; k += 32) {
+        const bf16x8 a = ld8(ap + k);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ld8(bp[j] + k), acc[j], 0, 0, 0);
+    }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int o = o0 + 16 * j + (lane & 15);
         if (o >= n_out) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dst[(int64_t)(i0 + (lane >> 4) * 4 + r) * n_out + o] = acc[0][j][r];
+        for (int r = 0; r < 4; ++r) dst[(int64_t)(i0 + (lane >> 4) * 4 + r) * n_out + o] = acc[j][r];
     }
 }
 
-// Partial bias gradients: one wave per (output unit, split).
-__global__ __launch_bounds__(64) void k_bgrad(const uint16_t* __restrict__ dYT, const uint16_t* __restrict__ dZT3,
-                                              const uint16_t* __restrict__ dZT2, const uint16_t* __restrict__ dZT1,
-                                              int64_t Mpad, float* __restrict__ part) {
-    const int u = blockIdx.x;  // 0..13: b4, then b3, b2, b1 (128 each)
-    const int64_t s = blockIdx.y;
-    const uint16_t* row;
-    int off;
-    if (u < NO) { row = dYT + (int64_t)u * Mpad; off = OB4 + u; }
-    else if (u < NO + NH) { row = dZT3 + (int64_t)(u - NO) * Mpad; off = OB3 + (u - NO); }
-    else if (u < NO + 2 * NH) { row = dZT2 + (int64_t)(u - NO - NH) * Mpad; off = OB2 + (u - NO - NH); }
-    else { row = dZT1 + (int64_t)(u - NO - 2 * NH) * Mpad; off = OB1 + (u - NO - 2 * NH); }
-    row += s * SPLIT_ROWS;
-    float v = 0.f;
-    for (int k = threadIdx.x; k < SPLIT_ROWS; k += 64) v += bf2f(row[k]);
-    v = wave_sum(v);
-    if (threadIdx.x == 0) part[s * NPARAM + off] = v;
+__global__ __launch_bounds__(64) void k_train_wgrad(RowsArgs g, float* __restrict__ part) {
+    const int64_t s = blockIdx.x / WG_UNITS;
+    int u = (int)(blockIdx.x - s * WG_UNITS);
+    float* dst = part + s * NPARAM;
+    if (u < WG_L1) {
+        wgrad_tile<4>(g.fT, g.dZT1, g.Mpad, u / 2 * 16, u % 2 * 64, NH, s, dst + OW1);
+    } else if (u < WG_L1 + WG_L) {
+        u -= WG_L1;
+        wgrad_tile<4>(g.aT1, g.dZT2, g.Mpad, u / 2 * 16, u % 2 * 64, NH, s, dst + OW2);
+    } else if (u < WG_L1 + 2 * WG_L) {
+        u -= WG_L1 + WG_L;
+        wgrad_tile<4>(g.aT2, g.dZT3, g.Mpad, u / 2 * 16, u % 2 * 64, NH, s, dst + OW3);
+    } else if (u < WG_TILES) {
+        wgrad_tile<1>(g.aT3, g.dYT, g.Mpad, (u - WG_L1 - 2 * WG_L) * 16, 0, NO, s, dst + OW4);
+    } else {
+        u -= WG_TILES;   // 0..13: b4, then b3, b2, b1 (128 each)
+        const uint16_t* row;
+        int off;
+        if (u < NO) { row = g.dYT + (int64_t)u * g.Mpad; off = OB4 + u; }
+        else if (u < NO + NH) { row = g.dZT3 + (int64_t)(u - NO) * g.Mpad; off = OB3 + (u - NO); }
+        else if (u < NO + 2 * NH) { row = g.dZT2 + (int64_t)(u - NO - NH) * g.Mpad; off = OB2 + (u - NO - NH); }
+        else { row = g.dZT1 + (int64_t)(u - NO - 2 * NH) * g.Mpad; off = OB1 + (u - NO - 2 * NH); }
+        row += s * SPLIT_ROWS;
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < SPLIT_ROWS; k += 64) v += bf2f(row[k + threadIdx.x]);
+        v = wave_sum(v);
+        if (threadIdx.x == 0) dst[off] = v;
+    }
 }
 
-// grad = scale * sum over splits (fixed order); the last block also reduces the loss.
-__global__ void k_reduce(const float* __restrict__ part, int64_t nsplit, float scale, float* __restrict__ grad,
-                         const float* __restrict__ loss_part, int64_t nloss, float* __restrict__ loss) {
+__device__ __forceinline__ void adam_one(float& th, float& m, float& v, float gj, float lr, float b1, float b2,
+                                         float eps, float bc1, float bc2) {
+    const float mj = b1 * m + (1.0f - b1) * gj;
+    const float vj = b2 * v + (1.0f - b2) * gj * gj;
+    m = mj;
+    v = vj;
+    th -= lr * (mj / bc1) / (sqrtf(vj / bc2) + eps);
+}
+
+struct AdamArgs {
+    float *th, *m, *v;   // th nullptr: the gradient alone
+    float lr, b1, b2, eps, bc1, bc2;
+};
+
+// grad = scale * sum over splits (fixed order), then Adam on it; the last block also reduces the loss.
+__global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ part, int64_t nsplit, float scale,
+                                                float* __restrict__ grad, const float* __restrict__ loss_part,
+                                                int64_t nloss, float* __restrict__ loss, AdamArgs a) {
     if (blockIdx.x == gridDim.x - 1) {
-        if (threadIdx.x == 0 && loss) {
+        if (threadIdx.x < 64 && loss) {   // one wave, fixed order
             double acc = 0.0;
-            for (int64_t i = 0; i < nloss; ++i) acc += loss_part[i];
-            *loss = (float)(acc * (double)scale);
+            for (int64_t i = threadIdx.x; i < nloss; i += 64) acc += loss_part[i];
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
+            if (threadIdx.x == 0) *loss = (float)(acc * (double)scale);
         }
         return;
     }
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= NPARAM) return;
     float acc = 0.f;
+#pragma unroll 8
     for (int64_t s = 0; s < nsplit; ++s) acc += part[s * NPARAM + j];
-    grad[j] = acc * scale;
-}
-
-// Input features transposed (and gathered): fT[f][m] = feat[idx[m]][f], zero for m >= M.
-__global__ __launch_bounds__(256) void k_feat_t(const uint16_t* __restrict__ feat, const int64_t* __restrict__ idx,
-                                                int64_t M, int64_t Mpad, uint16_t* __restrict__ fT) {
-    __shared__ uint16_t tile[64][NF + 2];
-    const int64_t m0 = (int64_t)blockIdx.x * 64;
-    for (int t = threadIdx.x; t < 64 * NF; t += 256) {
-        const int r = t / NF, f = t % NF;
-        const int64_t m = m0 + r;
-        tile[r][f] = m < M ? feat[(idx ? idx[m] : m) * NF + f] : (uint16_t)0;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < 64 * NF; t += 256) {
-        const int f = t / 64, r = t % 64;
-        fT[(int64_t)f * Mpad + m0 + r] = tile[r][f];
-    }
+    const float gj = acc * scale;
+    grad[j] = gj;
+    if (a.th) adam_one(a.th[j], a.m[j], a.v[j], gj, a.lr, a.b1, a.b2, a.eps, a.bc1, a.bc2);
 }
 
 __global__ void k_adam(float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
                        const float* __restrict__ g, float lr, float b1, float b2, float eps, float bc1, float bc2) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= NPARAM) return;
-    const float gj = g[j];
-    const float mj = b1 * m[j] + (1.0f - b1) * gj;
-    const float vj = b2 * v[j] + (1.0f - b2) * gj * gj;
-    m[j] = mj;
-    v[j] = vj;
-    th[j] -= lr * (mj / bc1) / (sqrtf(vj / bc2) + eps);
+    adam_one(th[j], m[j], v[j], g[j], lr, b1, b2, eps, bc1, bc2);
 }
 
 // ------------------------------------------------------------------ features
@@ -964,8 +988,8 @@ inline int64_t pad_rows(int64_t m, int64_t a) { return (m + a - 1) / a * a; }
 
 struct TrainBufs {
     Packed pk;
-    uint16_t *fT, *a1, *a2, *a3, *aT1, *aT2, *aT3, *dY, *dYT, *dZ3, *dZ2, *dZT3, *dZT2, *dZT1;
-    float *z1, *z2, *z3, *part, *loss_part, *grad;
+    uint16_t *fT, *aT1, *aT2, *aT3, *dYT, *dZT3, *dZT2, *dZT1;
+    float *part, *loss_part, *grad;
 };
 
 void carve_packed(Carve& cv, Packed& pk) {
@@ -982,24 +1006,15 @@ TrainBufs carve_train(Carve& cv, int64_t Mpad) {
     TrainBufs b{};
     carve_packed(cv, b.pk);
     b.fT = cv.take<uint16_t>(NF * Mpad);
-    b.a1 = cv.take<uint16_t>(Mpad * NH);
-    b.a2 = cv.take<uint16_t>(Mpad * NH);
-    b.a3 = cv.take<uint16_t>(Mpad * NH);
     b.aT1 = cv.take<uint16_t>(NH * Mpad);
     b.aT2 = cv.take<uint16_t>(NH * Mpad);
     b.aT3 = cv.take<uint16_t>(NH * Mpad);
-    b.z1 = cv.take<float>(Mpad * NH);
-    b.z2 = cv.take<float>(Mpad * NH);
-    b.z3 = cv.take<float>(Mpad * NH);
-    b.dY = cv.take<uint16_t>(Mpad * DYLD);
     b.dYT = cv.take<uint16_t>(NOP * Mpad);
-    b.dZ3 = cv.take<uint16_t>(Mpad * NH);
-    b.dZ2 = cv.take<uint16_t>(Mpad * NH);
     b.dZT3 = cv.take<uint16_t>(NH * Mpad);
     b.dZT2 = cv.take<uint16_t>(NH * Mpad);
     b.dZT1 = cv.take<uint16_t>(NH * Mpad);
     b.part = cv.take<float>((size_t)(Mpad / SPLIT_ROWS) * NPARAM);
-    b.loss_part = cv.take<float>(Mpad / 32);
+    b.loss_part = cv.take<float>(Mpad / 16);
     b.grad = cv.take<float>(NPARAM);
     return b;
 }
@@ -1061,8 +1076,10 @@ chaff_status mlp_forward(const float* theta, const uint16_t* feat, int64_t M, fl
     return forward_fused(theta, b.pk, feat, M, Y, st);
 }
 
-chaff_status mlp_grad(const float* theta, const uint16_t* feat, const float* T, const int64_t* idx, int64_t M,
-                      float* grad, float* loss, void* ws, size_t ws_bytes, hipStream_t st) {
+// Gradient, loss and (with ad.th) the Adam step; see k_train_rows.
+static chaff_status train_pass(const float* theta, const uint16_t* feat, const float* T, const int64_t* idx, int64_t M,
+                               float* grad, float* loss, const AdamArgs& ad, void* ws, size_t ws_bytes,
+                               hipStream_t st) {
     const int64_t Mpad = pad_rows(M, SPLIT_ROWS);
     Carve cv(ws, ws_bytes);
     TrainBufs b = carve_train(cv, Mpad);
@@ -1070,64 +1087,48 @@ chaff_status mlp_grad(const float* theta, const uint16_t* feat, const float* T, 
     if (!grad) grad = b.grad;
     chaff_status s = launch_pack(theta, b.pk, st);
     if (s != CHAFF_OK) return s;
-    const unsigned grid = (unsigned)(Mpad / ROWS_WG);
     const int64_t nsplit = Mpad / SPLIT_ROWS;
-    {
-        ProfScope ps("mlp_grad", st, 3.0 * (layer_flops(M, NF, NH) + 2 * layer_flops(M, NH, NH) + layer_flops(M, NH, NO)),
-                     true);
-        hipLaunchKernelGGL(k_feat_t, dim3((unsigned)(Mpad / 64)), dim3(256), 0, st, feat, idx, M, Mpad, b.fT);
-        FwdArgs a{};
-        a.M = M;
-        a.Mpad = Mpad;
-        a.a_idx = idx;
-        a.A = feat; a.lda = NF; a.Wt = b.pk.wt1; a.K = NF; a.bias = theta + OB1;
-        a.a_out = b.a1; a.z_out = b.z1; a.aT_out = b.aT1;
-        hipLaunchKernelGGL((k_fwd<false, true>), dim3(grid), dim3(256), 0, st, a);
-        a.a_idx = nullptr;
-        a.A = b.a1; a.lda = NH; a.Wt = b.pk.wt2; a.K = NH; a.bias = theta + OB2;
-        a.a_out = b.a2; a.z_out = b.z2; a.aT_out = b.aT2;
-        hipLaunchKernelGGL((k_fwd<false, true>), dim3(grid), dim3(256), 0, st, a);
-        a.A = b.a2; a.Wt = b.pk.wt3; a.bias = theta + OB3;
-        a.a_out = b.a3; a.z_out = b.z3; a.aT_out = b.aT3;
-        hipLaunchKernelGGL((k_fwd<false, true>), dim3(grid), dim3(256), 0, st, a);
-        a.A = b.a3; a.Wt = b.pk.wt4; a.bias = theta + OB4; a.a_out = nullptr; a.z_out = nullptr; a.aT_out = nullptr;
-        a.t_idx = idx; a.T = T; a.dY = b.dY; a.dYT = b.dYT; a.loss_part = b.loss_part;
-        hipLaunchKernelGGL((k_fwd<true, true>), dim3(grid), dim3(256), 0, st, a);
-
-        BwdArgs d{};
-        d.Mpad = Mpad;
-        d.dZ = b.dY; d.lda = DYLD; d.K = DYLD; d.Wn = b.pk.wn4; d.z_prev = b.z3; d.dZ_out = b.dZ3; d.dZT_out = b.dZT3;
-        hipLaunchKernelGGL(k_bwd, dim3(grid), dim3(256), 0, st, d);
-        d.dZ = b.dZ3; d.lda = NH; d.K = NH; d.Wn = b.pk.wn3; d.z_prev = b.z2; d.dZ_out = b.dZ2; d.dZT_out = b.dZT2;
-        hipLaunchKernelGGL(k_bwd, dim3(grid), dim3(256), 0, st, d);
-        d.dZ = b.dZ2; d.Wn = b.pk.wn2; d.z_prev = b.z1; d.dZ_out = nullptr; d.dZT_out = b.dZT1;
-        hipLaunchKernelGGL(k_bwd, dim3(grid), dim3(256), 0, st, d);
-
-        const unsigned ns = (unsigned)nsplit;
-        hipLaunchKernelGGL((k_wgrad<4>), dim3(NF / 16, NH / 64, ns), dim3(64), 0, st, (const uint16_t*)b.fT,
-                           (const uint16_t*)b.dZT1, Mpad, NH, OW1, b.part);
-        hipLaunchKernelGGL((k_wgrad<4>), dim3(NH / 16, NH / 64, ns), dim3(64), 0, st, (const uint16_t*)b.aT1,
-                           (const uint16_t*)b.dZT2, Mpad, NH, OW2, b.part);
-        hipLaunchKernelGGL((k_wgrad<4>), dim3(NH / 16, NH / 64, ns), dim3(64), 0, st, (const uint16_t*)b.aT2,
-                           (const uint16_t*)b.dZT3, Mpad, NH, OW3, b.part);
-        hipLaunchKernelGGL((k_wgrad<1>), dim3(NH / 16, 1, ns), dim3(64), 0, st, (const uint16_t*)b.aT3,
-                           (const uint16_t*)b.dYT, Mpad, NO, OW4, b.part);
-        hipLaunchKernelGGL(k_bgrad, dim3(NO + 3 * NH, ns), dim3(64), 0, st, (const uint16_t*)b.dYT,
-                           (const uint16_t*)b.dZT3, (const uint16_t*)b.dZT2, (const uint16_t*)b.dZT1, Mpad, b.part);
-        const float scale = (float)(1.0 / ((double)M * NO));
-        hipLaunchKernelGGL(k_reduce, dim3(nblk(NPARAM, 256) + 1), dim3(256), 0, st, (const float*)b.part, nsplit,
-                           scale, grad, (const float*)b.loss_part, Mpad / 32, loss);
+    ProfScope ps("mlp_grad", st, 3.0 * (layer_flops(M, NF, NH) + 2 * layer_flops(M, NH, NH) + layer_flops(M, NH, NO)),
+                 true);
+    RowsArgs g{feat, idx, T, M, Mpad, b.pk, theta, b.fT, b.aT1, b.aT2, b.aT3, b.dYT, b.dZT3, b.dZT2, b.dZT1, b.loss_part};
+    // 64 rows per workgroup re-read the weights a quarter as often, 16 spread the
+    // rows over four times as many CUs: the larger tile once two workgroups per CU remain.
+    // Steps of 4,096 / 16,384 / 32,768 / 262,144 rows: 16 rows 51 / 86 / 135 / 1,084 us,
+    // 32 rows 55 / 80 / 122 / 892 us, 64 rows 60 / 80 / 120 / 842 us.
+    const int mt = Mpad / 64 >= 512 ? 4 : Mpad / 32 >= 512 ? 2 : 1;
+    const unsigned rows_grid = (unsigned)(Mpad / (16 * mt));
+    switch (mt) {
+        case 4: hipLaunchKernelGGL(k_train_rows<4>, dim3(rows_grid), dim3(256), 0, st, g); break;
+        case 2: hipLaunchKernelGGL(k_train_rows<2>, dim3(rows_grid), dim3(256), 0, st, g); break;
+        default: hipLaunchKernelGGL(k_train_rows<1>, dim3(rows_grid), dim3(256), 0, st, g); break;
     }
+    CHAFF_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_train_wgrad, dim3((unsigned)(WG_UNITS * nsplit)), dim3(64), 0, st, g, b.part);
+    CHAFF_LAUNCH_CHECK();
+    const float scale = (float)(1.0 / ((double)M * NO));
+    hipLaunchKernelGGL(k_reduce, dim3(nblk(NPARAM, 256) + 1), dim3(256), 0, st, (const float*)b.part, nsplit, scale,
+                       grad, (const float*)b.loss_part, (int64_t)rows_grid, loss, ad);
     CHAFF_LAUNCH_CHECK();
     return CHAFF_OK;
 }
 
+chaff_status mlp_grad(const float* theta, const uint16_t* feat, const float* T, const int64_t* idx, int64_t M,
+                      float* grad, float* loss, void* ws, size_t ws_bytes, hipStream_t st) {
+    return train_pass(theta, feat, T, idx, M, grad, loss, AdamArgs{}, ws, ws_bytes, st);
+}
+
+static void bias_corrections(int32_t t, float b1, float b2, float& bc1, float& bc2) {
+    bc1 = (float)(1.0 - std::pow((double)b1, (double)t));
+    bc2 = (float)(1.0 - std::pow((double)b2, (double)t));
+}
+
 chaff_status mlp_adam(float* theta, float* m, float* v, const float* grad, int32_t t, float lr, float b1, float b2,
                       float eps, hipStream_t st) {
-    const double bc1 = 1.0 - std::pow((double)b1, (double)t), bc2 = 1.0 - std::pow((double)b2, (double)t);
+    float bc1, bc2;
+    bias_corrections(t, b1, b2, bc1, bc2);
     ProfScope ps("mlp_adam", st, 4.0 * 7 * NPARAM);
     hipLaunchKernelGGL(k_adam, dim3(nblk(NPARAM, 256)), dim3(256), 0, st, theta, m, v, grad, lr, b1, b2, eps,
-                       (float)bc1, (float)bc2);
+                       bc1, bc2);
     CHAFF_LAUNCH_CHECK();
     return CHAFF_OK;
 }
@@ -1135,13 +1136,9 @@ chaff_status mlp_adam(float* theta, float* m, float* v, const float* grad, int32
 chaff_status mlp_train_step(float* theta, float* m, float* v, int32_t t, float lr, float b1, float b2, float eps,
                             const uint16_t* feat, const float* T, const int64_t* idx, int64_t M, float* loss, void* ws,
                             size_t ws_bytes, hipStream_t st) {
-    const int64_t Mpad = pad_rows(M, SPLIT_ROWS);
-    Carve cv(ws, ws_bytes);
-    TrainBufs b = carve_train(cv, Mpad);
-    if (!cv.ok()) return fail(CHAFF_EWORKSPACE, "mlp workspace too small");
-    chaff_status s = mlp_grad(theta, feat, T, idx, M, b.grad, loss, ws, ws_bytes, st);
-    if (s != CHAFF_OK) return s;
-    return mlp_adam(theta, m, v, b.grad, t, lr, b1, b2, eps, st);
+    AdamArgs ad{theta, m, v, lr, b1, b2, eps, 0.f, 0.f};
+    bias_corrections(t, b1, b2, ad.bc1, ad.bc2);
+    return train_pass(theta, feat, T, idx, M, nullptr, loss, ad, ws, ws_bytes, st);
 }
 
 chaff_status mlp_features(Cloud* c, const double* k_hat, const double* e_hat, int64_t R, int64_t row0, int64_t n_rows,
