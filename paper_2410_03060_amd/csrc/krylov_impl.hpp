@@ -268,6 +268,102 @@ __global__ __launch_bounds__(64) void k_spmm_wave_row(const int64_t* __restrict_
     }
 }
 
+// Few columns: one wave streams one block row.  Lane l < 49 owns entry l of
+// every 7x7 block (row q = l / 7, column k = l % 7): a block is one coalesced
+// 392-byte load, kept for S columns, and STREAM_U blocks with their x entries
+// are requested before the first is used, so a wave keeps several blocks in
+// flight whatever the row's length.  acc[r]: this lane's sum over the blocks of
+// z x_r.  VEC: rows of x aligned to 16 bytes, read two columns at a time.
+//   Bound: HBM (Z once).  One row per lane (variant 0) reads 49 bytes' worth of
+// every line per lane and the tiles of 4 and 8 columns wait for one block at a
+// time: one column on rows of 1,000 blocks 1,473 and 2,040 us, this 974 us
+// (4.0 TB/s); in the COCG step, where the tile of 8 columns ran, 1,523 -> 979 us.
+template <int S>
+constexpr int stream_unroll() { return S <= 2 ? 8 : 4; }
+template <typename CZ, typename CX, typename R, int S, bool VEC>
+__device__ __forceinline__ void stream_row(int64_t e0, int64_t e1, const int32_t* __restrict__ col_idx,
+                                           const CZ* __restrict__ Z, const CX* __restrict__ X, int lane,
+                                           cplx<R> (&acc)[S]) {
+    constexpr int U = stream_unroll<S>();
+    const bool on = lane < NB2;
+    const int k = lane % NB;
+#pragma unroll
+    for (int r = 0; r < S; ++r) acc[r] = cplx<R>{0, 0};
+    const CZ* zl = Z + (on ? lane : 0);
+    for (int64_t e = e0; e < e1; e += U) {
+        CZ z[U];
+        CX x[U][S];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {   // blocks behind the row's end: its last one, times zero
+            const int64_t eu = e + u < e1 ? e + u : e1 - 1;
+            z[u] = zl[eu * NB2];
+            const CX* xb = X + ((int64_t)col_idx[eu] * NB + k) * S;
+            if constexpr (VEC && S % 2 == 0 && sizeof(CX) == sizeof(c64)) {
+                const float4* xv = reinterpret_cast<const float4*>(xb);
+#pragma unroll
+                for (int r = 0; r < S; r += 2) {
+                    const float4 v = xv[r / 2];
+                    x[u][r] = CX{v.x, v.y};
+                    x[u][r + 1] = CX{v.z, v.w};
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < S; ++r) x[u][r] = xb[r];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool have = on && e + u < e1;
+            const cplx<R> zv = {have ? (R)z[u].re : (R)0, have ? (R)z[u].im : (R)0};
+#pragma unroll
+            for (int r = 0; r < S; ++r) cfma(acc[r], zv, have ? ccast<cplx<R>>(x[u][r]) : cplx<R>{0, 0});
+        }
+    }
+}
+
+constexpr int STREAM_WAVES = 4;
+// sums over the block columns k through LDS: lane o < 7 S returns entry (q, r) = (o / S, o % S)
+template <typename R, int S>
+__device__ __forceinline__ cplx<R> stream_fold(const cplx<R> (&acc)[S], cplx<R> (*lds)[NB2 + 1], int lane) {
+    if (lane < NB2)
+#pragma unroll
+        for (int r = 0; r < S; ++r) lds[r][lane] = acc[r];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    cplx<R> y = {0, 0};
+    if (lane < NB * S) {
+        const int q = lane / S, r = lane % S;
+#pragma unroll
+        for (int m = 0; m < NB; ++m) y = cadd(y, lds[r][q * NB + m]);
+    }
+    return y;
+}
+
+template <typename CZ, typename CX, typename CY, int MODE, int S, bool VEC>
+__global__ __launch_bounds__(64 * STREAM_WAVES) void k_spmm_stream(const int64_t* __restrict__ row_ptr,
+                                                                  const int32_t* __restrict__ col_idx,
+                                                                  const CZ* __restrict__ Z, const CX* __restrict__ X,
+                                                                  const CY* __restrict__ B, CY* __restrict__ Y,
+                                                                  int64_t n) {
+    using R = typename real_of<CY>::type;
+    __shared__ cplx<R> lds[STREAM_WAVES][S][NB2 + 1];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int64_t n_grp = (n + STREAM_WAVES - 1) / STREAM_WAVES, per_xcd = (n_grp + NXCD - 1) / NXCD;
+    const int64_t grp = (int64_t)(blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;   // contiguous rows per XCD
+    const int64_t i = grp * STREAM_WAVES + w;
+    if (grp >= n_grp || i >= n) return;   // wave-uniform, no barrier below
+    cplx<R> acc[S];
+    stream_row<CZ, CX, R, S, VEC>(row_ptr[i], row_ptr[i + 1], col_idx, Z, X, lane, acc);
+    const cplx<R> y = stream_fold<R, S>(acc, lds[w], lane);
+    if (lane < NB * S) {
+        const int64_t o = i * NB * S + lane;
+        if (MODE == 0) Y[o] = ccast<CY>(y);
+        if (MODE == 1) Y[o] = ccast<CY>(csub(ccast<cplx<R>>(B[o]), y));
+        if (MODE == 2) Y[o] = ccast<CY>(cadd(ccast<cplx<R>>(Y[o]), y));
+    }
+}
+
 // Variant 1: lanes -> (block row sub-index, RHS column); ST columns per row,
 // each thread produces the 7 outputs of its (row, column).
 template <typename CZ, typename CX, typename CY, int MODE, bool DIAG, int ST>
@@ -359,22 +455,46 @@ __global__ __launch_bounds__(256) void k_spmm_xcd(const int64_t* __restrict__ ro
     }
 }
 
-// default when nothing was tuned: one row per lane for a single RHS, else the
-// XCD-aware tile order
-static int default_variant(int64_t s) { return s == 1 ? 0 : 3; }
+// Product variant when nothing was tuned (us on one MI355X, variants 0 / 3 / 6 / 7;
+// sparse: 200,003 rows of 9 blocks, long: 10,000 rows of 1,000 blocks, complex64):
+//   s = 1: sparse 192 / 681 / 224 / 216, long 1473 / 6339 / 2419 / 974;
+//   s = 2: sparse 376 / 592 / 224 / 218, long 1814 / 4302 / 2412 / 982
+//          (complex128 sparse 645 / 1681 / 318 / 402);
+//   s = 4: sparse 776 / 487 / 227 / 273, long 3623 / 3571 / 2422 / 1360;
+//   s = 8: sparse 1721 / 484 / 279 / 284 (the XCD order of the same tile);
+//   s = 16, 32, 64: variant 3 759 / 1284 / 998, variant 7 363 / 503 / 773.
+// 19 unknowns (20,000 rows of 1.05 blocks; variants 0 / 3 / 5): s = 2 35 / 107 / 40,
+// s = 4 70 / 107 / 45, s = 8 144 / 108 / 61, s = 16 309 / 117 / 204.
+constexpr double LONG_ROW = 48.0;   // blocks per row from which the streaming product wins at 1, 3 and 4 columns
+                                    // (rows of 65, s = 1: 1283 / 1295 us for variants 0 / 7)
+constexpr int64_t STREAM_MAX = 4;   // its columns
+static int default_variant(int64_t s, int64_t n, int64_t nnzb, bool c64_vectors) {
+    if (NB2 > 64) return s <= 3 ? 0 : s <= 8 ? 5 : 3;
+    const bool long_rows = (double)nnzb >= LONG_ROW * (double)n;
+    if (s == 1) return long_rows ? 7 : 0;
+    if (s <= STREAM_MAX) return long_rows || (s == 2 && c64_vectors) ? 7 : 6;
+    return s <= 8 ? 6 : 7;
+}
 
 static int spmm_tile_width(int64_t s) {
     int st = 1;
     while (st < s && st < 64) st <<= 1;
     return st;
 }
-// RHS columns per wave of the COCG product (at least 8: at most 8 groups of block columns)
-static int cocg_width(int64_t s) { return spmm_tile_width(s) < 8 ? 8 : spmm_tile_width(s); }
+// RHS columns per wave of the COCG product: the streaming row product up to
+// STREAM_COCG columns (7 unknowns), tiles of at least 8 columns (at most 8
+// groups of block columns) above.  100,000 rows of 6.3 blocks: the 8-column tile
+// takes 132 us at every width up to 8, the streaming product 60, 69 and 98 us at
+// 1, 2 and 4 columns (217 at 8).
+constexpr int STREAM_COCG = NB2 <= 64 ? 4 : 0;
+static int cocg_width(int64_t s) {
+    return s <= STREAM_COCG ? (int)s : std::max(spmm_tile_width(s), 8);
+}
 
 // variant: 0 = rowq, 1 = tile (ST from s), 2 = tile with ST halved (more rows per wave),
 // 3 = tile in XCD-aware order, 4 = XCD-aware with ST halved, 5 = rowq with up to 16
 // columns per lane, 6 = one wave per block row with the block staged in LDS, 7 = 6 in
-// XCD-aware order
+// XCD-aware order (up to STREAM_MAX columns: one wave streams one block row)
 template <typename CZ, typename CX, typename CY, int MODE, bool DIAG>
 static chaff_status spmm_launch(const int64_t* row_ptr, const int32_t* col_idx, const CZ* Z, const CX* X,
                                 const CY* B, CY* Y, int64_t n, int64_t nnzb, int64_t s, int variant,
@@ -389,11 +509,9 @@ static chaff_status spmm_launch(const int64_t* row_ptr, const int32_t* col_idx, 
         const int t = (!DIAG && MODE == 0 && std::is_same<CZ, CX>::value && std::is_same<CX, CY>::value)
                           ? tuned_variant(NB, n, nnzb, s, std::is_same<CZ, c64>::value ? CHAFF_C64 : CHAFF_C128)
                           : -1;
-        // wide products of mixed precision (the FP64 residual, the FP64 guess) are not in the
-        // tuning table: one wave per block row with the block staged in LDS, as the tuned
-        // complex64 product at these widths
-        const bool wide = !DIAG && NB2 <= 64 && s >= 32;
-        variant = t >= 0 ? t : (DIAG ? (s == 1 ? 0 : 1) : wide ? 7 : default_variant(s));
+        variant = t >= 0 ? t
+                  : DIAG ? (s == 1 ? 0 : 1)
+                         : default_variant(s, n, nnzb, std::is_same<CX, c64>::value && std::is_same<CY, c64>::value);
     }
     if (variant == 0) {
         dim3 grid((unsigned)((n * NB + 255) / 256), (unsigned)s);
@@ -406,6 +524,27 @@ static chaff_status spmm_launch(const int64_t* row_ptr, const int32_t* col_idx, 
         if (variant == 6 || variant == 7) variant = 3;
     }
     if constexpr (NB2 <= 64) if ((variant == 6 || variant == 7) && !DIAG) {
+        if (variant == 7 && s <= STREAM_MAX) {
+            const int64_t n_grp = (n + STREAM_WAVES - 1) / STREAM_WAVES;
+            const dim3 grid((unsigned)((n_grp + NXCD - 1) / NXCD * NXCD));
+            const bool vec = (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+#define CHAFF_STREAM(SW)                                                                                        \
+    case SW:                                                                                                    \
+        if (vec)                                                                                                \
+            hipLaunchKernelGGL((k_spmm_stream<CZ, CX, CY, MODE, SW, true>), grid, dim3(64 * STREAM_WAVES), 0,   \
+                               st, row_ptr, col_idx, Z, X, B, Y, n);                                            \
+        else                                                                                                    \
+            hipLaunchKernelGGL((k_spmm_stream<CZ, CX, CY, MODE, SW, false>), grid, dim3(64 * STREAM_WAVES), 0,  \
+                               st, row_ptr, col_idx, Z, X, B, Y, n);                                            \
+        break;
+            switch ((int)s) {
+                CHAFF_STREAM(1) CHAFF_STREAM(2) CHAFF_STREAM(3) CHAFF_STREAM(4)
+                default: return fail(CHAFF_EINVAL, "bad column count");
+            }
+#undef CHAFF_STREAM
+            CHAFF_LAUNCH_CHECK();
+            return CHAFF_OK;
+        }
         // S columns per tile, several block rows per wave below 32 columns; 7 = XCD-aware order
         const int sw = spmm_tile_width(s) < 4 ? 4 : spmm_tile_width(s);
         // block rows per wave (several independent gather chains per wave at small widths)
@@ -1113,6 +1252,47 @@ void k_cocg_spmm(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles
     if (threadIdx.x < S && r < s) tpart[t * s + r] = v;
 }
 
+// COCG product of up to STREAM_MAX columns on the streaming row product: the
+// same tiles and per-tile p^T q as k_cocg_spmm, one row per wave.
+template <typename CZ, typename C, int S, bool VEC>
+__global__ __launch_bounds__(RB) void k_cocg_stream(const Chunk* __restrict__ tiles, int64_t n_tiles, int xcd_order,
+                                                    const int64_t* __restrict__ row_ptr,
+                                                    const int32_t* __restrict__ col_idx, const CZ* __restrict__ Z,
+                                                    const C* __restrict__ P, C* __restrict__ Q,
+                                                    c128* __restrict__ tpart) {
+    using R = typename real_of<C>::type;
+    static_assert(STREAM_WAVES == COCG_TILE_ROWS, "one wave per row of a tile");
+    __shared__ cplx<R> lds[STREAM_WAVES][S][NB2 + 1];
+    __shared__ c128 red[STREAM_WAVES][NB * S];
+    const int64_t id = blockIdx.x;
+    int64_t t = id;
+    if (xcd_order) t = (int64_t)(id % NXCD) * ((n_tiles + NXCD - 1) / NXCD) + id / NXCD;
+    if (t >= n_tiles) return;   // uniform over the block
+    const Chunk tl = tiles[t];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int64_t i = tl.w0 + w;
+    c128 dot = {0, 0};
+    if (i < tl.w1) {   // wave-uniform
+        cplx<R> acc[S];
+        stream_row<CZ, C, R, S, VEC>(row_ptr[i], row_ptr[i + 1], col_idx, Z, P, lane, acc);
+        const cplx<R> y = stream_fold<R, S>(acc, lds[w], lane);
+        if (lane < NB * S) {
+            const int64_t o = i * NB * S + lane;
+            Q[o] = ccast<C>(y);
+            cfma(dot, ccast<c128>(P[o]), ccast<c128>(y));
+        }
+    }
+    if (lane < NB * S) red[w][lane] = dot;
+    __syncthreads();
+    if (threadIdx.x < S) {
+        c128 v = {0, 0};
+        for (int k = 0; k < STREAM_WAVES; ++k)
+#pragma unroll
+            for (int m = 0; m < NB; ++m) v = cadd(v, red[k][m * S + threadIdx.x]);
+        tpart[t * S + threadIdx.x] = v;
+    }
+}
+
 // Search direction and deferred solution update, one pass per step:
 //   x += alpha p_old (the step whose residual update ran last; skipped with
 //   pend = 0 when that update was already applied), z = P_i r, p = z + beta p_old.
@@ -1598,8 +1778,7 @@ static SolveShape solve_shape(const Cloud* c, int m, int64_t s, chaff_prec prec,
     sh.cocg_st = cocg_width(s);
     sh.cocg_xcd = 1;
     {   // the COCG product follows the tuned public variant's workgroup order (1, 2, 6: linear)
-        int v = tuned_variant(NB, c->n, c->nnzb, s, prec);
-        if (v < 0) v = default_variant(s);
+        const int v = tuned_variant(NB, c->n, c->nnzb, s, prec);
         sh.cocg_xcd = (v == 1 || v == 2 || v == 6) ? 0 : 1;
     }
     sh.tile_w = COCG_TILE_ROWS;
@@ -1833,6 +2012,22 @@ static void launch_cg_pdir_z(const SolveShape& sh, SolveLayout& L, const C* z, C
     hipLaunchKernelGGL((k_cg_pdir_z<C, ST>), grid, dim3(RB), 0, st, (const Chunk*)L.chunks, (const CgState*)L.cg,
                        z, p, x, sh.s, pend, pfirst ? 1 : 0);
 }
+template <typename CZ, typename C, int S>
+static void launch_cocg_stream(const Cloud* c, const SolveShape& sh, SolveLayout& L, const CZ* Z, const C* p, C* q,
+                               hipStream_t st) {
+    if constexpr (NB2 <= 64) {   // one lane per entry of a block
+        const int64_t per_xcd = (sh.n_tiles + NXCD - 1) / NXCD;
+        const dim3 grid((unsigned)(sh.cocg_xcd ? per_xcd * NXCD : sh.n_tiles));
+        // the vectors lie rows x (the call's columns) apart: after a compaction an even
+        // width can sit at an odd multiple of 8 bytes
+        if ((reinterpret_cast<uintptr_t>(p) & 15) == 0)
+            hipLaunchKernelGGL((k_cocg_stream<CZ, C, S, true>), grid, dim3(RB), 0, st, (const Chunk*)L.tiles, sh.n_tiles,
+                               sh.cocg_xcd, (const int64_t*)c->row_ptr, (const int32_t*)c->col_idx, Z, p, q, L.tpart);
+        else
+            hipLaunchKernelGGL((k_cocg_stream<CZ, C, S, false>), grid, dim3(RB), 0, st, (const Chunk*)L.tiles, sh.n_tiles,
+                               sh.cocg_xcd, (const int64_t*)c->row_ptr, (const int32_t*)c->col_idx, Z, p, q, L.tpart);
+    }
+}
 template <typename CZ, typename C, int ST>
 static void launch_cocg_spmm(const Cloud* c, const SolveShape& sh, SolveLayout& L, const CZ* Z, const C* p, C* q,
                              hipStream_t st) {
@@ -2059,7 +2254,11 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
                                           2.0 * rows * cs.s * sizeof(C),
                                       8.0 * NB2 * (double)c->nnzb * cs.s});
                 switch (cs.cocg_st) {
-                    case 8: launch_cocg_spmm<CZ, C, 8>(c, cs, Lc, Pinv, r, q, st); break;
+                    case 1: launch_cocg_stream<CZ, C, 1>(c, cs, Lc, Pinv, r, q, st); break;
+                case 2: launch_cocg_stream<CZ, C, 2>(c, cs, Lc, Pinv, r, q, st); break;
+                case 3: launch_cocg_stream<CZ, C, 3>(c, cs, Lc, Pinv, r, q, st); break;
+                case 4: launch_cocg_stream<CZ, C, 4>(c, cs, Lc, Pinv, r, q, st); break;
+                case 8: launch_cocg_spmm<CZ, C, 8>(c, cs, Lc, Pinv, r, q, st); break;
                     case 16: launch_cocg_spmm<CZ, C, 16>(c, cs, Lc, Pinv, r, q, st); break;
                     case 32: launch_cocg_spmm<CZ, C, 32>(c, cs, Lc, Pinv, r, q, st); break;
                     default: launch_cocg_spmm<CZ, C, 64>(c, cs, Lc, Pinv, r, q, st); break;
@@ -2188,6 +2387,10 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
                                       2.0 * rows * cs.s * sizeof(C),
                                   8.0 * NB2 * (double)c->nnzb * cs.s});
             switch (cs.cocg_st) {
+                case 1: launch_cocg_stream<CZ, C, 1>(c, cs, Lc, Z, p, q, st); break;
+                case 2: launch_cocg_stream<CZ, C, 2>(c, cs, Lc, Z, p, q, st); break;
+                case 3: launch_cocg_stream<CZ, C, 3>(c, cs, Lc, Z, p, q, st); break;
+                case 4: launch_cocg_stream<CZ, C, 4>(c, cs, Lc, Z, p, q, st); break;
                 case 8: launch_cocg_spmm<CZ, C, 8>(c, cs, Lc, Z, p, q, st); break;
                 case 16: launch_cocg_spmm<CZ, C, 16>(c, cs, Lc, Z, p, q, st); break;
                 case 32: launch_cocg_spmm<CZ, C, 32>(c, cs, Lc, Z, p, q, st); break;
@@ -3071,7 +3274,7 @@ chaff_status autotune(Cloud* c, chaff_prec prec, const void* Z, void* X, void* Y
     CHAFF_HIP(hipEventCreate(&a));
     CHAFF_HIP(hipEventCreate(&b));
     double bms = 1e300;
-    int bv = default_variant(s);
+    int bv = default_variant(s, c->n, c->nnzb, prec == CHAFF_C64);
     for (int v = 0; v <= 7; ++v) {
         for (int rep = 0; rep < 7; ++rep) {
             if (rep == 2) CHAFF_HIP(hipEventRecord(a, st));
