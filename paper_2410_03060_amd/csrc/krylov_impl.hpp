@@ -15,6 +15,7 @@
 // product reads Z once for every right-hand side, while dot products are
 // reduced per cloud over fixed row chunks in a fixed order (deterministic).
 #include "common.hpp"
+#include "lone.hpp"
 #include "precond.hpp"
 #include "prof.hpp"
 #include "tune.hpp"
@@ -32,6 +33,13 @@
 
 namespace chaff {
 namespace CHAFF_KNS {
+
+// solves of few, small systems in one launch (krylov_small.hpp)
+bool small_solve(const Cloud* c, const chaff_solve_opts* o, int64_t s);
+size_t small_workspace_bytes(const Cloud* c, const chaff_solve_opts* o, int64_t s);
+chaff_status solve_small(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv, const double* k_hat,
+                         const double* e_hat, int64_t s, void* X, void* ws, size_t ws_bytes, chaff_solve_stats* stats,
+                         double* rel_res, hipStream_t st);
 
 constexpr int NB = CHAFF_KNB;         // rooftop unknowns per wire
 constexpr int NSEG = NB + 1;          // segments per wire
@@ -1861,8 +1869,10 @@ static SolveLayout carve_solve(void* ws, size_t ws_bytes, const SolveShape& sh) 
 constexpr double LONE_SHARE = 0.75;
 constexpr int64_t LONE_ROWS = 40000;
 static bool lone_wires(const Cloud* c, const chaff_solve_opts* o) {
-    // a caller's own guess (use_x0 = 1) is left as it is given
-    return o->precond == CHAFF_PRECOND_BLOCK && o->use_x0 != 1 && c->n * NB >= LONE_ROWS &&
+    // a caller's own guess (use_x0 = 1) is left as it is given; complex128 solves
+    // keep one recurrence over every wire, whose iterate at the tolerance is
+    // theirs to 1e-12 and not only to the tolerance
+    return o->prec == CHAFF_C64 && o->precond == CHAFF_PRECOND_BLOCK && o->use_x0 != 1 && c->n * NB >= LONE_ROWS &&
            2.0 * (double)c->n_pairs <= LONE_SHARE * (double)c->n;
 }
 
@@ -1934,6 +1944,7 @@ size_t solve_workspace_bytes(const Cloud* c, const chaff_solve_opts* o, int64_t 
     const int m = o->restart;
     SolveShape sh = solve_shape(c, m, s, (chaff_prec)o->prec, o->method);
     size_t bytes = carve_solve(nullptr, 0, sh).bytes;
+    if (small_solve(c, o, s)) bytes = std::max(bytes, small_workspace_bytes(c, o, s));
     if (lone_wires(c, o)) {
         const int64_t nc = std::min<int64_t>(c->n, 2 * c->n_pairs);
         bytes = std::max(bytes, carve_lone(nullptr, 0, c, s, sh.csize).bytes + compact_solve_bytes(c, o, s, nc));
@@ -3022,35 +3033,14 @@ __global__ __launch_bounds__(256) void k_lone_blocks(int64_t nc, const int64_t* 
     for (int t = lane; t < NB2; t += 64) Pc[ci * NB2 + t] = Pinv[i * NB2 + t];
 }
 
-// a^T v over one row of a stored block, FP64, four independent chains
-template <typename CZ>
-__device__ __forceinline__ c128 row_times(const CZ* __restrict__ row, const c128 (&v)[NB]) {
-    double r0 = 0.0, r1 = 0.0, i0 = 0.0, i1 = 0.0;
-#pragma unroll
-    for (int m = 0; m < NB; ++m) {
-        const c128 a = ccast<c128>(row[m]);
-        r0 = fma(a.re, v[m].re, r0);
-        r1 = fma(a.im, v[m].im, r1);
-        i0 = fma(a.re, v[m].im, i0);
-        i1 = fma(a.im, v[m].re, i1);
-    }
-    return c128{r0 - r1, i0 + i1};
-}
-
-// The wires without neighbours, start to end: u (eq. 4), x = P u, then sweeps
-// of r = u - Z_ii x, x += P r in FP64 over the stored blocks until ||r|| of the
-// wire is below thr ||u|| (at most four), x to the caller's rows, and the
-// chunk's sums of |u|^2 and |r|^2 (r the residual of the x that is written).
-// A thread owns one (wire, right-hand side); with 64 columns the wire is
-// uniform over the wave and its blocks come through the scalar cache.
+// The wires without neighbours, start to end (lone_wire), x to the caller's
+// rows, and the chunk's sums of |u|^2 and |r|^2.  A thread owns one (wire,
+// right-hand side); with 64 columns the wire is uniform over the wave and its
+// blocks come through the scalar cache.
 //   Bound: FP64 arithmetic, four NB x NB complex products with the usual one
-// sweep.  One vector at a time is held in registers and the product's rows are
-// walked by a rolled loop through the lane's own column of LDS: with every
-// product unrolled (NB^2 terms each) the 19-unknown form ran out of registers
-// and instruction cache: 75.7 ms for 95,000 wires x 64 columns, rolled 3.2 ms
-// (16 TFLOP/s, 1.9 GB written); 7 unknowns, 46,000 wires x 360: 3.1 -> 1.9 ms.
-// u is formed again where it is needed, each rooftop's phase from the last by
-// one complex product.
+// sweep.  95,000 wires of 19 unknowns x 64 columns: 75.7 ms with the products
+// unrolled, 3.2 ms (16 TFLOP/s, 1.9 GB written); 46,000 wires of 7 x 360:
+// 3.1 -> 1.9 ms.
 template <typename CZ, int ST>
 __global__ __launch_bounds__(256) void k_lone_solve(LoneLayout l, const Wire* __restrict__ wires,
                                                     const int32_t* __restrict__ perm,
@@ -3066,60 +3056,16 @@ __global__ __launch_bounds__(256) void k_lone_solve(LoneLayout l, const Wire* __
     const int lane = threadIdx.x & 63;
     double u2 = 0.0, r2 = 0.0;
     if (r < s) {
-        const double kx = k_hat[3 * r], ky = k_hat[3 * r + 1], kz = k_hat[3 * r + 2];
-        const double ex = e_hat[3 * r], ey = e_hat[3 * r + 1], ez = e_hat[3 * r + 2];
+        const double kv[3] = {k_hat[3 * r], k_hat[3 * r + 1], k_hat[3 * r + 2]};
+        const double ev[3] = {e_hat[3 * r], e_hat[3 * r + 1], e_hat[3 * r + 2]};
         for (int64_t t = ch.w0 + rsub; t < ch.w1; t += 256 / ST) {
             const int64_t i = l.lone[t];
             const Wire w = wires[i];
             const CZ* zb = Z + row_ptr[i] * NB2;
             const CZ* pb = Pinv + i * NB2;
-            const double tp = w.tx * ex + w.ty * ey + w.tz * ez;
-            const double beta = k * (kx * w.tx + ky * w.ty + kz * w.tz);
-            const double ph0 = k * (kx * w.cx + ky * w.cy + kz * w.cz);
-            const double D = w.len / NSEG;
-            const double sc = sinc(0.5 * beta * D);
-            const double env = tp * D * sc * sc;
-            c128 first, step;   // u_0 and the phase step of one rooftop
-            {
-                double sn, cs;
-                sincos(ph0 - (double)(NB / 2) * beta * D, &sn, &cs);
-                first = c128{env * cs, -env * sn};
-                sincos(beta * D, &sn, &cs);
-                step = c128{cs, -sn};
-            }
             c128 x[NB];
-            double w2 = 0.0;
-            x[0] = first;
-#pragma unroll
-            for (int q = 1; q < NB; ++q) x[q] = cmul(x[q - 1], step);
-#pragma unroll
-            for (int q = 0; q < NB; ++q) w2 += x[q].re * x[q].re + x[q].im * x[q].im;
-#pragma unroll 1
-            for (int q = 0; q < NB; ++q) lv[q][lane] = row_times(pb + q * NB, x);
-            double e2 = w2;
-#pragma unroll 1
-            for (int sweep = 0;; ++sweep) {
-#pragma unroll
-                for (int q = 0; q < NB; ++q) x[q] = lv[q][lane];
-                e2 = 0.0;
-                c128 uq = first;
-#pragma unroll 1
-                for (int q = 0; q < NB; ++q) {   // r = u - Z x, over x in LDS
-                    const c128 rq = csub(uq, row_times(zb + q * NB, x));
-                    e2 += rq.re * rq.re + rq.im * rq.im;
-                    lv[q][lane] = rq;
-                    uq = cmul(uq, step);
-                }
-                if (!(e2 > thr * thr * w2) || sweep == 4) break;
-                c128 rv[NB];
-#pragma unroll
-                for (int q = 0; q < NB; ++q) {
-                    rv[q] = lv[q][lane];
-                    lv[q][lane] = x[q];
-                }
-#pragma unroll 1
-                for (int q = 0; q < NB; ++q) lv[q][lane] = cadd(lv[q][lane], row_times(pb + q * NB, rv));
-            }
+            double w2, e2;
+            lone_wire<NB>(w, zb, pb, kv, ev, k, thr, lv, lane, x, w2, e2);
             const int64_t o = (int64_t)perm[i] * NB * s + r;
 #pragma unroll
             for (int q = 0; q < NB; ++q) X[o + q * s] = x[q];
@@ -3256,6 +3202,8 @@ static chaff_status solve_any(Cloud* c, const chaff_solve_opts* o, const void* Z
 chaff_status solve(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv, const double* k_hat,
                    const double* e_hat, int64_t s, void* X, void* ws, size_t ws_bytes, chaff_solve_stats* st_out,
                    double* rel_res, hipStream_t st) {
+    if (small_solve(c, o, s))
+        return solve_small(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, st_out, rel_res, st);
     if (o->prec == CHAFF_C64)
         return solve_any<c64>(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, st_out, rel_res, st);
     return solve_any<c128>(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, st_out, rel_res, st);

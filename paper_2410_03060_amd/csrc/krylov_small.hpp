@@ -1,0 +1,680 @@
+// Small solves: one workgroup takes one system (cloud, incidence) from its
+// excitation to its currents in a single launch.
+//
+// The lockstep solver (krylov_impl.hpp) spends 12 to 14 launches and a host
+// synchronisation on every Krylov step, about 75 us whatever the system's size;
+// a cloud of a few thousand sparsely coupled wires needs less than 20 us of
+// arithmetic and L2 latency per step on one CU.  Here the vectors of a system
+// sit in L2, its threads take one row each, and barriers of one workgroup stand
+// in for the launches: nothing returns to the host until the residual of every
+// system is below the tolerance.
+//
+// The recurrences, targets and restarts are those of the lockstep solver
+// (GMRES with classical Gram-Schmidt applied twice; COCG restarted at each FP64
+// residual); sums run in another fixed order.  In complex64 the wires without
+// neighbours are solved beforehand (k_lone) and leave the iteration, as there;
+// where the block inverses do not solve them, they stay in it.
+//
+// Included by small7.hip and small19.hip (CHAFF_KNB unknowns per wire, namespace
+// CHAFF_KNS).
+#include "common.hpp"
+#include "lone.hpp"
+#include "prof.hpp"
+
+#include <algorithm>
+#include <chrono>
+
+namespace chaff {
+namespace CHAFF_KNS {
+
+namespace small {
+
+constexpr int NB = CHAFF_KNB, NSEG = NB + 1, NB2 = NB * NB;
+constexpr int TH = NB <= 8 ? 1024 : 512;    // threads of a workgroup (128 and 256 registers)
+constexpr int NW = TH / 64;                 // its waves
+constexpr int MAX_WIRES = 4096;             // wires of one cloud (16-bit indices in LDS)
+constexpr int MAX_CLOUDS = 32;              // cloud offsets travel with the launch
+constexpr int MAX_M = 200;                  // restart lengths chaff_solve accepts
+constexpr double PI_S = 3.14159265358979323846;
+constexpr int64_t MAX_SYSTEMS = 256;         // one workgroup per CU
+constexpr int64_t MAX_BYTES = 5 << 18;        // of the blocks that a product reads (1.25 MiB)
+
+struct Out {             // what a system tells the host
+    double rel;          // FP64 relative residual, +inf after a breakdown
+    int32_t cycles, ok;  // refinement cycles run; 1 converged, 0 not, -1 broken down
+};
+
+template <typename C>
+struct Args {
+    const Wire* wires;
+    const int32_t* perm;
+    const int64_t* row_ptr;
+    const int32_t* col_idx;
+    const C *Z, *P;
+    const double *k_hat, *e_hat;
+    double k, tol, inner_tol;
+    int64_t s;
+    int n_clouds, m, max_cycles, use_x0, method, nvec;
+    int32_t off[MAX_CLOUDS + 1];   // wires before each cloud
+    c128* X;                       // caller's rows
+    c128 *b, *x, *r;               // per system [wires * NB]
+    C* V;                          // per system [nvec][wires * NB]
+    c128* H;                       // per system [m][m + 1], column by column
+    double* lone_e2;               // [wires][s] squared residual of a wire solved by k_lone
+    int take_lone;                 // k_lone ran
+    Out* out;
+    int32_t* steps;                // per system [max_cycles]
+};
+
+struct Shared {
+    uint16_t list[MAX_WIRES];      // coupled wires of the cloud
+    uint16_t where[MAX_WIRES];     // their place in the list
+    c128 h[MAX_M + 1], h2[MAX_M + 1], g[MAX_M + 1], sn[MAX_M];
+    double cs[MAX_M];
+    c128 red[NW][2];
+    c128 dots[NW];
+    int32_t cnt[NW];
+    double val[4];
+    int32_t flag;
+};
+
+__device__ __forceinline__ double wave_add(double v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+// sums over the workgroup, the same value in every thread, fixed order
+__device__ __forceinline__ void block_add(Shared& S, c128& a, c128& b) {
+    a.re = wave_add(a.re);
+    a.im = wave_add(a.im);
+    b.re = wave_add(b.re);
+    b.im = wave_add(b.im);
+    const int w = threadIdx.x >> 6;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        S.red[w][0] = a;
+        S.red[w][1] = b;
+    }
+    __syncthreads();
+    a = b = c128{0, 0};
+    for (int k = 0; k < NW; ++k) {
+        a = cadd(a, S.red[k][0]);
+        b = cadd(b, S.red[k][1]);
+    }
+}
+__device__ __forceinline__ double block_add(Shared& S, double v) {
+    c128 a = {v, 0}, b = {0, 0};
+    block_add(S, a, b);
+    return a.re;
+}
+
+// A[q][.] v over one row of a stored block
+template <typename R, typename C, typename V>
+__device__ __forceinline__ void row_dot(cplx<R>& acc, const C* __restrict__ a, const V* v) {
+    C av[NB];
+    V vv[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        av[k] = a[k];
+        vv[k] = v[k];
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) cfma(acc, ccast<cplx<R>>(av[k]), ccast<cplx<R>>(vv[k]));
+}
+
+// One system: its cloud's wires, its vectors and the rows that are iterated on.
+template <typename C>
+struct System {
+    using R = typename real_of<C>::type;
+    const Args<C>& A;
+    Shared& S;
+    int w0, n, nc, rows;   // first wire, wires, coupled wires, their rows
+    int64_t row0;          // of the whole cloud set
+    c128 *b, *x, *r;
+    C* V;
+    int64_t vs;            // stride of the Krylov vectors
+    int64_t rhs;
+
+    __device__ __forceinline__ int wire(int ci) const { return S.list[ci]; }
+    __device__ __forceinline__ C* vec(int i) const { return V + (int64_t)i * vs; }
+
+    // y = P v over the coupled rows
+    __device__ void precond(const C* v, C* y) const {
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB, q = t - ci * NB;
+            cplx<R> a = {0, 0};
+            row_dot<R>(a, A.P + ((int64_t)(w0 + wire(ci)) * NB + q) * NB, v + ci * NB);
+            y[t] = a;
+        }
+        __syncthreads();
+    }
+    // sum over the row's blocks of Z v, v on the coupled rows (STRIDE: by compact or by cloud wire)
+    template <typename T, typename VT>
+    __device__ __forceinline__ cplx<T> z_row(int i, int q, const VT* v, bool compact) const {
+        cplx<T> a = {0, 0};
+        const int64_t e1 = A.row_ptr[w0 + i + 1];
+        for (int64_t e = A.row_ptr[w0 + i]; e < e1; ++e) {
+            const int j = A.col_idx[e] - w0;
+            row_dot<T>(a, A.Z + e * NB2 + q * NB, v + (int64_t)(compact ? S.where[j] : j) * NB);
+        }
+        return a;
+    }
+    __device__ void product(const C* v, C* y) const {
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB;
+            y[t] = z_row<R>(wire(ci), t - ci * NB, v, true);
+        }
+        __syncthreads();
+    }
+    // r = b - Z x (FP64) on the coupled rows; its squared norm
+    __device__ double residual(bool zero_x) const {
+        double s2 = 0.0;
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB, q = t - ci * NB, i = wire(ci);
+            c128 v = b[i * NB + q];
+            if (!zero_x) v = csub(v, z_row<double>(i, q, x, false));
+            r[i * NB + q] = v;
+            s2 += v.re * v.re + v.im * v.im;
+        }
+        return block_add(S, s2);
+    }
+
+    // the coupled wires in order; nc of them
+    __device__ void list_coupled(bool all) {
+        int base = 0;
+        for (int i0 = 0; i0 < n; i0 += TH) {
+            const int i = i0 + threadIdx.x;
+            const bool on = i < n && (all || A.row_ptr[w0 + i + 1] - A.row_ptr[w0 + i] > 1);
+            const uint64_t m = __ballot(on);
+            const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+            __syncthreads();
+            if (lane == 0) S.cnt[w] = __popcll(m);
+            __syncthreads();
+            int ci = base + __popcll(m & ((1ull << lane) - 1)), tot = 0;
+            for (int k = 0; k < NW; ++k) {
+                if (k < w) ci += S.cnt[k];
+                tot += S.cnt[k];
+            }
+            if (i < n) S.where[i] = on ? (uint16_t)ci : (uint16_t)0xffff;
+            if (on) S.list[ci] = (uint16_t)i;
+            base += tot;
+        }
+        nc = base;
+        rows = nc * NB;
+        __syncthreads();
+    }
+
+    // the incidence's drive of a wire: amplitude (the rooftops differ by their phase
+    // alone), phase step of half the wire's rooftops
+    __device__ __forceinline__ double drive(const Wire& w, double& beta, double& ph0) const {
+        const double* kh = A.k_hat + 3 * rhs;
+        const double* eh = A.e_hat + 3 * rhs;
+        const double tp = w.tx * eh[0] + w.ty * eh[1] + w.tz * eh[2];
+        beta = A.k * (kh[0] * w.tx + kh[1] * w.ty + kh[2] * w.tz);
+        ph0 = A.k * (kh[0] * w.cx + kh[1] * w.cy + kh[2] * w.cz);
+        const double D = w.len / NSEG;
+        const double sc = lone_sinc(0.5 * beta * D);
+        return tp * D * sc * sc;
+    }
+    // u (eq. 4) on the coupled rows
+    __device__ void excite() const {
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB, q = t - ci * NB, i = wire(ci);
+            const Wire w = A.wires[w0 + i];
+            double beta, ph0, sn, cs;
+            const double env = drive(w, beta, ph0);
+            sincos(ph0 + beta * (-0.5 * w.len + (q + 1) * (w.len / NSEG)), &sn, &cs);
+            b[i * NB + q] = c128{env * cs, -env * sn};
+        }
+        __syncthreads();
+    }
+    // ||u||^2 over the whole cloud, and the squared residual that k_lone left
+    __device__ void norms(double& u2, double& lone2) const {
+        c128 a = {0, 0}, none = {0, 0};
+        for (int i = threadIdx.x; i < n; i += TH) {
+            double beta, ph0;
+            const double env = drive(A.wires[w0 + i], beta, ph0);
+            a.re += NB * (env * env);
+            if (S.where[i] == 0xffff) a.im += A.lone_e2[(int64_t)(w0 + i) * A.s + rhs];
+        }
+        block_add(S, a, none);
+        u2 = a.re;
+        lone2 = a.im;
+    }
+};
+
+// One restarted GMRES(m) cycle from r (squared norm rn2); returns its steps.
+template <typename C>
+__device__ int gmres_cycle(System<C>& Y, double rn, double target, c128* H) {
+    using R = typename real_of<C>::type;
+    Shared& S = Y.S;
+    const int m = Y.A.m, rows = Y.rows, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    C* W = Y.vec(m + 1);
+    C* T = Y.vec(m + 2);
+    for (int t = threadIdx.x; t < rows; t += TH) {
+        const int ci = t / NB, q = t - ci * NB;
+        Y.vec(0)[t] = ccast<C>(cscale(Y.r[Y.wire(ci) * NB + q], 1.0 / rn));
+    }
+    if (threadIdx.x == 0) S.g[0] = c128{1, 0};
+    __syncthreads();
+    int j = 0, used = 0;
+    for (; j < m; ++j) {
+        Y.precond(Y.vec(j), T);
+        Y.product(T, W);
+        const int nv = j + 1;
+        double n2 = 0.0;
+        for (int pass = 0; pass < 2; ++pass) {   // classical Gram-Schmidt, twice
+            c128* h = pass ? S.h2 : S.h;
+            const int G = nv >= NW ? 1 : NW / nv;   // waves per vector
+            for (int i0 = 0; i0 < nv; i0 += NW) {
+                const int i = i0 + (G == 1 ? w : w / G), part = G == 1 ? 0 : w % G;
+                c128 a = {0, 0};
+                if (i < nv) {
+                    const C* v = Y.vec(i);
+#pragma unroll 4
+                    for (int t = part * 64 + lane; t < rows; t += 64 * G) cfma_conj(a, ccast<c128>(v[t]), ccast<c128>(W[t]));
+                }
+                a.re = wave_add(a.re);
+                a.im = wave_add(a.im);
+                if (lane == 0) S.dots[w] = a;
+                __syncthreads();
+                if ((int)threadIdx.x < NW && i0 + (int)threadIdx.x < nv && (int)threadIdx.x * G < NW) {
+                    c128 t = {0, 0};
+                    for (int k = 0; k < G; ++k) t = cadd(t, S.dots[threadIdx.x * G + k]);
+                    h[i0 + threadIdx.x] = t;
+                }
+                __syncthreads();
+            }
+            n2 = 0.0;
+            for (int t = threadIdx.x; t < rows; t += TH) {
+                cplx<R> v = W[t];
+#pragma unroll 4
+                for (int i = 0; i < nv; ++i) {
+                    const cplx<R> a = Y.vec(i)[t];
+                    cfma(v, cmk<R>(-a.re, -a.im), ccast<cplx<R>>(h[i]));
+                }
+                W[t] = v;
+                n2 += (double)v.re * v.re + (double)v.im * v.im;
+            }
+            if (pass == 0) __syncthreads();
+        }
+        const double beta = sqrt(fmax(block_add(S, n2), 0.0));
+        if (threadIdx.x == 0) {   // column j of H, the earlier rotations, the new one
+            c128* Hj = H + (int64_t)j * (m + 1);
+            c128 prev = cadd(S.h[0], S.h2[0]);
+            for (int i = 0; i < j; ++i) {
+                const c128 next = cadd(S.h[i + 1], S.h2[i + 1]);
+                Hj[i] = cadd(cscale(prev, S.cs[i]), cmul(S.sn[i], next));
+                prev = csub(cscale(next, S.cs[i]), cmul(c128{S.sn[i].re, -S.sn[i].im}, prev));
+            }
+            const double aa = sqrt(prev.re * prev.re + prev.im * prev.im);
+            double cj;
+            c128 sj, rr;
+            if (beta == 0.0) {
+                cj = 1.0; sj = c128{0, 0}; rr = prev;
+            } else if (aa == 0.0) {
+                cj = 0.0; sj = c128{1, 0}; rr = c128{beta, 0};
+            } else {
+                const double tn = sqrt(aa * aa + beta * beta);
+                const c128 ph = {prev.re / aa, prev.im / aa};
+                cj = aa / tn;
+                sj = cscale(ph, beta / tn);
+                rr = cscale(ph, tn);
+            }
+            S.cs[j] = cj;
+            S.sn[j] = sj;
+            Hj[j] = rr;
+            const c128 gj = S.g[j];
+            S.g[j] = cscale(gj, cj);
+            S.g[j + 1] = cmul(c128{-sj.re, sj.im}, gj);
+            const double est = sqrt(S.g[j + 1].re * S.g[j + 1].re + S.g[j + 1].im * S.g[j + 1].im);
+            const double hscale = sqrt(aa * aa + beta * beta);
+            const bool breakdown = !(beta > 1e-14 * hscale) || !isfinite(beta);
+            S.val[0] = breakdown ? 0.0 : 1.0 / beta;
+            S.flag = est <= target || breakdown || j + 1 >= m;
+        }
+        __syncthreads();
+        used = j + 1;
+        if (S.flag) break;
+        const R f = (R)S.val[0];
+        C* vn = Y.vec(j + 1);
+        for (int t = threadIdx.x; t < rows; t += TH) vn[t] = cscale(W[t], f);
+        __syncthreads();
+    }
+    // y = R^-1 g, scaled by the cycle's residual norm: one wave, column by column
+    if (w == 0) {
+        for (int i = used - 1; i >= 0; --i) {
+            const c128* Hi = H + (int64_t)i * (m + 1);
+            const c128 d = Hi[i];
+            const double dd = d.re * d.re + d.im * d.im;
+            const c128 y = dd > 0 ? cmul(S.g[i], c128{d.re / dd, -d.im / dd}) : c128{0, 0};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int l = lane; l < i; l += 64) S.g[l] = csub(S.g[l], cmul(Hi[l], y));
+            if (lane == 0) S.h[i] = cscale(y, rn);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < rows; t += TH) {   // T = V y
+        cplx<R> a = {0, 0};
+#pragma unroll 4
+        for (int i = 0; i < used; ++i) cfma(a, Y.vec(i)[t], ccast<cplx<R>>(S.h[i]));
+        T[t] = a;
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < rows; t += TH) {   // x += P T
+        const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
+        c128 a = {0, 0};
+        row_dot<double>(a, Y.A.P + ((int64_t)(Y.w0 + i) * NB + q) * NB, T + ci * NB);
+        Y.x[i * NB + q] = cadd(Y.x[i * NB + q], a);
+    }
+    __syncthreads();
+    return used;
+}
+
+// One COCG cycle: r in units of scale, ended below the checkpoint or after m
+// steps; x += scale * (its correction).  Returns its steps.
+template <typename C>
+__device__ int cocg_cycle(System<C>& Y, double scale, double target, double ckpt) {
+    using R = typename real_of<C>::type;
+    Shared& S = Y.S;
+    const int rows = Y.rows;
+    C *rv = Y.vec(0), *p = Y.vec(1), *q = Y.vec(2), *xc = Y.vec(3);
+    for (int t = threadIdx.x; t < rows; t += TH) {
+        const int ci = t / NB;
+        rv[t] = ccast<C>(cscale(Y.r[Y.wire(ci) * NB + t - ci * NB], 1.0 / scale));
+    }
+    __syncthreads();
+    c128 rho = {0, 0}, alpha = {0, 0};
+    int steps = 0;
+    for (int k = 0;; ++k) {
+        // r -= alpha q was applied; z = P r, rho' = r^T z, ||r||^2.  z is formed again below instead of stored
+        c128 rz = {0, 0}, rr = {0, 0};
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB;
+            cplx<R> z = {0, 0};
+            row_dot<R>(z, Y.A.P + ((int64_t)(Y.w0 + Y.wire(ci)) * NB + t - ci * NB) * NB, rv + ci * NB);
+            q[t] = z;
+            const C v = rv[t];
+            cfma(rz, ccast<c128>(v), ccast<c128>(z));
+            rr.re += (double)v.re * v.re + (double)v.im * v.im;
+        }
+        block_add(S, rz, rr);
+        const double rn = sqrt(fmax(rr.re, 0.0));
+        const double dd = rho.re * rho.re + rho.im * rho.im;
+        if (!(rn > target) || !isfinite(rn) || !(rn > ckpt) || k == Y.A.m) break;
+        const c128 beta = k > 0 && dd > 0.0 ? cmul(rz, c128{rho.re / dd, -rho.im / dd}) : c128{0, 0};
+        rho = rz;
+        const cplx<R> bt = ccast<cplx<R>>(beta);
+        for (int t = threadIdx.x; t < rows; t += TH) {   // p = z + beta p
+            cplx<R> z = q[t];
+            if (k > 0) cfma(z, bt, p[t]);
+            p[t] = z;
+        }
+        __syncthreads();
+        ++steps;
+        c128 sg = {0, 0}, none = {0, 0};
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB;
+            const cplx<R> v = Y.template z_row<R>(Y.wire(ci), t - ci * NB, p, true);
+            q[t] = v;
+            cfma(sg, ccast<c128>(p[t]), ccast<c128>(v));
+        }
+        block_add(S, sg, none);
+        const double sd = sg.re * sg.re + sg.im * sg.im;
+        if (!(sd > 0.0) || !isfinite(sd)) break;   // the recurrence broke down: restart from the FP64 residual
+        alpha = cmul(rho, c128{sg.re / sd, -sg.im / sd});
+        const cplx<R> al = ccast<cplx<R>>(alpha), na = {-al.re, -al.im};
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            cplx<R> v = rv[t], xv = k > 0 ? xc[t] : cplx<R>{0, 0};
+            cfma(v, na, q[t]);
+            rv[t] = v;
+            cfma(xv, al, p[t]);
+            xc[t] = xv;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) S.flag = steps;   // xc holds something
+    }
+    __syncthreads();
+    return steps;
+}
+
+// The wires without neighbours of every cloud and incidence, one lane each.
+template <typename C>
+__global__ __launch_bounds__(64) void k_lone(Args<C> A, int64_t n) {
+    __shared__ c128 lv[NB][64];
+    const int lane = threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t i = t / A.s, r = t - i * A.s;
+    if (i >= n || A.row_ptr[i + 1] - A.row_ptr[i] > 1) return;   // no barrier below
+    const double kv[3] = {A.k_hat[3 * r], A.k_hat[3 * r + 1], A.k_hat[3 * r + 2]};
+    const double ev[3] = {A.e_hat[3 * r], A.e_hat[3 * r + 1], A.e_hat[3 * r + 2]};
+    c128 x[NB];
+    double w2, e2;
+    lone_wire<NB>(A.wires[i], A.Z + A.row_ptr[i] * NB2, A.P + i * NB2, kv, ev, A.k, 0.01 * A.tol, lv, lane, x, w2, e2);
+    const int64_t o = (int64_t)A.perm[i] * NB * A.s + r;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) A.X[o + q * A.s] = x[q];
+    A.lone_e2[i * A.s + r] = e2;
+}
+
+template <typename C>
+__global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
+    __shared__ Shared S;
+    const int cl = (int)(blockIdx.x % A.n_clouds);
+    const int64_t rhs = blockIdx.x / A.n_clouds;
+    const int64_t sys = (int64_t)cl * A.s + rhs;
+    const int w0 = A.off[cl], n = A.off[cl + 1] - w0;
+    const int64_t at = ((int64_t)w0 * A.s + rhs * n) * NB;   // this system's part of the vectors
+    System<C> Y{A, S, w0, n, 0, 0, 0, A.b + at, A.x + at, A.r + at, A.V + at * A.nvec, (int64_t)n * NB, rhs};
+    c128* H = A.H + sys * (int64_t)A.m * (A.m + 1);
+    if (n == 0) {
+        if (threadIdx.x == 0) A.out[sys] = Out{0.0, 0, 1};
+        return;
+    }
+    Y.list_coupled(!A.take_lone);
+    double b2, lone2;
+    Y.norms(b2, lone2);
+    if (Y.nc < n && !(lone2 <= 0.01 * A.tol * A.tol * b2)) {   // the block inverses do not solve them
+        Y.list_coupled(true);
+        lone2 = 0.0;
+    }
+    const double bn = sqrt(b2);
+    Y.excite();
+    // initial guess on the rows that are iterated on
+    for (int t = threadIdx.x; t < Y.rows; t += TH) {
+        const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
+        c128 v = {0, 0};
+        if (A.use_x0 == 1) v = A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs];
+        if (A.use_x0 == 2) row_dot<double>(v, A.P + ((int64_t)(w0 + i) * NB + q) * NB, Y.b + i * NB);
+        Y.x[i * NB + q] = v;
+    }
+    __syncthreads();
+    double scale = 0.0, rel = 0.0;
+    int cycles = 0, ok = 0;
+    for (;;) {
+        const double r2 = Y.residual(cycles == 0 && A.use_x0 == 0);
+        const double rn = sqrt(fmax(r2, 0.0));
+        rel = bn > 0 ? sqrt(r2 + lone2) / bn : 0.0;
+        if (!isfinite(r2)) {
+            rel = INFINITY;
+            ok = -1;
+            break;
+        }
+        if (!(rel > A.tol)) {
+            ok = 1;
+            break;
+        }
+        if (cycles >= A.max_cycles) break;
+        int steps;
+        if (A.method == CHAFF_GMRES) {
+            const double need = A.tol * bn / rn;
+            const double target = sizeof(C) == sizeof(c64) ? fmax(A.inner_tol, fmin(need, 1.0) * 0.5) : fmin(need * 0.5, 1.0);
+            steps = gmres_cycle<C>(Y, rn, target, H);
+        } else {
+            if (scale <= 0.0) scale = rn > 0 ? rn : 1.0;
+            const double target = 0.5 * A.tol * bn / scale;
+            if (threadIdx.x == 0) S.flag = 0;
+            steps = cocg_cycle<C>(Y, scale, target, fmax(target, A.inner_tol * rn / scale));
+            if (S.flag) {   // a correction was formed
+                const C* xc = Y.vec(3);
+                for (int t = threadIdx.x; t < Y.rows; t += TH) {
+                    const int ci = t / NB, a = Y.wire(ci) * NB + t - ci * NB;
+                    const c128 v = ccast<c128>(xc[t]);
+                    Y.x[a] = c128{Y.x[a].re + scale * v.re, Y.x[a].im + scale * v.im};
+                }
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) A.steps[sys * A.max_cycles + cycles] = steps;
+        ++cycles;
+    }
+    for (int t = threadIdx.x; t < Y.rows; t += TH) {
+        const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
+        A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs] = Y.x[i * NB + q];
+    }
+    if (threadIdx.x == 0) A.out[sys] = Out{rel, cycles, ok};
+}
+
+// complex128 keeps one recurrence over every wire (its iterate at the tolerance is
+// then the lockstep solver's to rounding); a caller's guess is left as it is given
+inline bool takes_lone(const Cloud* c, const chaff_solve_opts* o) {
+    return o->prec == CHAFF_C64 && o->use_x0 != 1 && 2 * c->n_pairs < c->n;
+}
+
+// vectors of a system beside b, x and r: GMRES m + 1 basis vectors, W and T; COCG r, p, q, x_c
+inline int vectors(const chaff_solve_opts* o) { return o->method == CHAFF_GMRES ? o->restart + 3 : 4; }
+
+template <typename C>
+static size_t carve(void* ws, size_t cap, const Cloud* c, const chaff_solve_opts* o, int64_t s, Args<C>& a) {
+    Carve cv(ws, cap);
+    const int64_t rows = c->n * NB, nsys = (int64_t)c->n_clouds * s;
+    const int m = o->method == CHAFF_GMRES ? o->restart : 0;
+    a.nvec = vectors(o);
+    a.b = cv.take<c128>(rows * s);
+    a.x = cv.take<c128>(rows * s);
+    a.r = cv.take<c128>(rows * s);
+    a.V = cv.take<C>((size_t)a.nvec * rows * s);
+    a.H = cv.take<c128>((size_t)nsys * m * (m + 1));
+    a.lone_e2 = cv.take<double>((size_t)c->n * s);
+    a.out = cv.take<Out>(nsys);
+    a.steps = cv.take<int32_t>((size_t)nsys * o->max_cycles);
+    return cv.off + 256;
+}
+
+}  // namespace small
+
+// Whether a call goes through one launch.  The line, whole steps on one MI355X
+// (single launch / lockstep): blocks of 0.1 MB (64 wires, complex128 GMRES) 0.40 /
+// 1.21 ms; 0.4 MB (2,000 sparse wires, complex64) 0.57 / 1.33 ms; 0.6 MB (256 wires,
+// complex128) 0.67 / 1.5 ms; 0.9 MB (4,000 sparse wires) 0.77 / 1.6 ms; 1.2 MB (4,000
+// wires of 19 unknowns) 0.94 / 1.5 ms; 2.4 MB (1,000 wires, complex128) 3.1 / 2.3 ms;
+// 3 MB (2,500 wires, complex64 COCG) 3.7 / 2.4 ms: one CU streams too slowly from
+// there on.  A system takes a CU; 200 of them take 0.82 ms where one takes 0.59.
+bool small_solve(const Cloud* c, const chaff_solve_opts* o, int64_t s) {
+    if (o->precond != CHAFF_PRECOND_BLOCK || (o->method != CHAFF_GMRES && o->method != CHAFF_COCG)) return false;
+    if (o->spmm_variant >= 0) return false;   // the caller asks for a product kernel
+    if (c->n_clouds > small::MAX_CLOUDS || o->max_cycles > 1000) return false;
+    const int64_t nsys = (int64_t)c->n_clouds * s;
+    if (nsys > small::MAX_SYSTEMS) return false;
+    for (int k = 0; k < c->n_clouds; ++k)
+        if (c->cloud_off[k + 1] - c->cloud_off[k] > small::MAX_WIRES) return false;
+    // blocks that a product reads: of the coupled wires (at most) or of all
+    const int64_t blocks = 2 * c->n_pairs + (small::takes_lone(c, o) ? std::min<int64_t>(c->n, 2 * c->n_pairs) : c->n);
+    return blocks * small::NB2 * (o->prec == CHAFF_C64 ? 8 : 16) <= small::MAX_BYTES;
+}
+
+size_t small_workspace_bytes(const Cloud* c, const chaff_solve_opts* o, int64_t s) {
+    if (o->prec == CHAFF_C64) {
+        small::Args<c64> a{};
+        return small::carve<c64>(nullptr, 0, c, o, s, a);
+    }
+    small::Args<c128> a{};
+    return small::carve<c128>(nullptr, 0, c, o, s, a);
+}
+
+template <typename C>
+static chaff_status solve_small_impl(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv,
+                                     const double* k_hat, const double* e_hat, int64_t s, void* X, void* ws,
+                                     size_t ws_bytes, chaff_solve_stats* stats, double* rel_res, hipStream_t st) {
+    const auto t0 = std::chrono::steady_clock::now();
+    small::Args<C> a{};
+    if (small::carve<C>(ws, ws_bytes, c, o, s, a) > ws_bytes) return fail(CHAFF_EWORKSPACE, "solve workspace too small");
+    a.wires = c->wires;
+    a.perm = c->perm;
+    a.row_ptr = c->row_ptr;
+    a.col_idx = c->col_idx;
+    a.Z = static_cast<const C*>(Z);
+    a.P = static_cast<const C*>(Pinv);
+    a.k_hat = k_hat;
+    a.e_hat = e_hat;
+    a.k = 2.0 * small::PI_S / c->wavelength;
+    a.tol = o->tol;
+    a.inner_tol = o->inner_tol;
+    a.s = s;
+    a.n_clouds = c->n_clouds;
+    a.m = o->restart;
+    a.max_cycles = o->max_cycles;
+    a.use_x0 = o->use_x0;
+    a.method = o->method;
+    for (int k = 0; k <= c->n_clouds; ++k) a.off[k] = (int32_t)c->cloud_off[k];
+    a.X = static_cast<c128*>(X);
+    const int64_t nsys = (int64_t)c->n_clouds * s;
+    a.take_lone = small::takes_lone(c, o) ? 1 : 0;
+    {
+        ProfScope ps("solve_small", st);
+        if (a.take_lone)
+            hipLaunchKernelGGL(small::k_lone<C>, dim3((unsigned)((c->n * s + 63) / 64)), dim3(64), 0, st, a, c->n);
+        hipLaunchKernelGGL(small::k_solve_small<C>, dim3((unsigned)nsys), dim3(small::TH), 0, st, a);
+    }
+    CHAFF_LAUNCH_CHECK();
+    // the systems' answers and steps lie one after the other: one copy
+    const size_t head = (const char*)a.steps - (const char*)a.out;
+    std::vector<char> back(head + (size_t)nsys * o->max_cycles * sizeof(int32_t));
+    CHAFF_HIP(hipMemcpyAsync(back.data(), a.out, back.size(), hipMemcpyDeviceToHost, st));
+    CHAFF_HIP(hipStreamSynchronize(st));
+    const small::Out* out = reinterpret_cast<const small::Out*>(back.data());
+    const int32_t* steps = reinterpret_cast<const int32_t*>(back.data() + head);
+    int cycles = 0, iters = 0;
+    double worst = 0.0;
+    bool all = true, broken = false;
+    for (int64_t i = 0; i < nsys; ++i) {
+        cycles = std::max(cycles, out[i].cycles);
+        worst = std::max(worst, out[i].rel);
+        all = all && out[i].ok == 1;
+        broken = broken || out[i].ok < 0;
+        if (rel_res) rel_res[i] = out[i].rel;
+    }
+    for (int k = 0; k < cycles; ++k) {   // as in lockstep: a cycle lasts as long as its longest system
+        int most = 0;
+        for (int64_t i = 0; i < nsys; ++i)
+            if (k < out[i].cycles) most = std::max(most, steps[i * o->max_cycles + k]);
+        iters += most;
+    }
+    if (stats) {
+        stats->cycles = cycles;
+        stats->iterations = iters;
+        stats->max_rel_residual = worst;
+        stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    }
+    if (!all)
+        return fail(CHAFF_ENOCONV, (broken ? "breakdown (non-finite solution) after " : "no convergence after ") +
+                                       std::to_string(cycles) + " cycles; max relative residual " +
+                                       std::to_string(worst));
+    return CHAFF_OK;
+}
+
+chaff_status solve_small(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv, const double* k_hat,
+                         const double* e_hat, int64_t s, void* X, void* ws, size_t ws_bytes, chaff_solve_stats* stats,
+                         double* rel_res, hipStream_t st) {
+    if (o->prec == CHAFF_C64)
+        return solve_small_impl<c64>(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, stats, rel_res, st);
+    return solve_small_impl<c128>(c, o, Z, Pinv, k_hat, e_hat, s, X, ws, ws_bytes, stats, rel_res, st);
+}
+
+}  // namespace CHAFF_KNS
+}  // namespace chaff
