@@ -13,6 +13,7 @@
 //    folded about each wire's centre, staged in LDS, partial sums per chunk,
 //    same second pass.
 #include "common.hpp"
+#include "phase.hpp"
 #include "prof.hpp"
 
 #include <algorithm>
@@ -27,51 +28,6 @@ constexpr int ff_chunk(int nb) { return nb <= 7 ? 256 : 64; }
 
 __device__ __forceinline__ double sinc_ff(double x) {
     return fabs(x) < 1e-4 ? 1.0 - x * x / 6.0 : sin(x) / x;
-}
-
-// ---- phases.  All arguments are kept in half turns (units of pi), so that the
-// range reduction is one exact subtraction of a whole number instead of the
-// library's reduction by multiples of pi/2, and the quadrant is a sign.
-// Taylor series of sin(pi x) / (pi x) and cos(pi x) in x^2: for |x| <= 1/4 the
-// first omitted terms are 6e-17 and 2e-18.
-// a t + c with the coefficient in a scalar register pair: left to itself the
-// compiler moves every coefficient into vector registers first, one move per
-// step of the series.
-__device__ __forceinline__ double horner(double a, double t, double c) {
-    double d;
-    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(t), "s"(c));
-    return d;
-}
-// sr = sin(pi x) / (pi x), c = cos(pi x)
-__device__ __forceinline__ void sinccospi_small(double x, double& sr, double& c) {
-    const double t = (PI_F * x) * (PI_F * x);
-    double p = horner(t, -1.0 / 1307674368000.0, 1.0 / 6227020800.0);
-    p = horner(p, t, -1.0 / 39916800.0);
-    p = horner(p, t, 1.0 / 362880.0);
-    p = horner(p, t, -1.0 / 5040.0);
-    p = horner(p, t, 1.0 / 120.0);
-    p = horner(p, t, -1.0 / 6.0);
-    sr = fma(p, t, 1.0);
-    double q = horner(t, 1.0 / 20922789888000.0, -1.0 / 87178291200.0);
-    q = horner(q, t, 1.0 / 479001600.0);
-    q = horner(q, t, -1.0 / 3628800.0);
-    q = horner(q, t, 1.0 / 40320.0);
-    q = horner(q, t, -1.0 / 720.0);
-    q = horner(q, t, 1.0 / 24.0);
-    q = fma(q, t, -0.5);
-    c = fma(q, t, 1.0);
-}
-// sin(pi x), cos(pi x) for any finite x (exact quadrant: 2 x - rint(2 x) is exact)
-__device__ __forceinline__ void sincospi_any(double x, double& s, double& c) {
-    const double n = rint(2.0 * x);
-    const double y = fma(-0.5, n, x);
-    double sn, cs;
-    sinccospi_small(y, sn, cs);
-    sn *= PI_F * y;
-    const int k = (int)(n - 4.0 * floor(0.25 * n));   // quadrant, exact below 2^53
-    const double a = (k & 1) ? cs : sn, b = (k & 1) ? sn : cs;
-    s = (k & 2) ? -a : a;
-    c = ((k + 1) & 2) ? -b : b;
 }
 
 // Far-field terms of one wire per direction, with the phases in half turns:

@@ -14,6 +14,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "phase.hpp"
 #include "precond.hpp"
 #include "prof.hpp"
 
@@ -44,7 +45,14 @@ __device__ __forceinline__ uint16_t f2bf(float f) {  // nearest even on the FP32
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 // the same rounding (nearest even) by the hardware conversion, for activations
 __device__ __forceinline__ uint16_t f2bf_hw(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ uint16_t d2bf(double x) { return f2bf((float)x); }
+// FP64 -> FP32 -> BF16, each to nearest even.  The empty statement keeps the FP32
+// value: left to itself the compiler joins the two roundings into one, which
+// resolves the ties of the second otherwise.
+__device__ __forceinline__ uint16_t d2bf(double x) {
+    float f = (float)x;
+    asm("" : "+v"(f));
+    return f2bf_hw(f);
+}
 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
@@ -95,11 +103,18 @@ __global__ void k_pack(const float* __restrict__ th, Packed pk) {
 // All four layers in one persistent kernel: each workgroup copies the BF16
 // weights into LDS once (rows padded by 8 elements so that the 16 rows a
 // ds_read_b128 touches fall in distinct banks), then every wave walks its own
-// 32-row tiles: layer 1 reads the features from HBM, the hidden activations
+// 16-row tiles: layer 1 reads the features from HBM, the hidden activations
 // stay in the wave's LDS tile, and only the 14 outputs are written.  Weight
-// traffic is 116 KB per workgroup instead of per 32-row tile.
+// traffic is 116 KB per workgroup instead of per tile.
+//   Bound: the SiLU of the hidden layers (one exponential and one reciprocal at
+// quarter rate each: 384 per row, 94 us of vector issue for 800,000 rows against
+// 38 us of MFMAs), so two waves per SIMD are wanted, whose products and SiLUs
+// overlap: eight waves of 16 rows are what the LDS holds beside the weights.
+// 305 us for 800,000 rows, 216 so
+constexpr int FWD_WAVES = 8;
 constexpr int FLD1 = NF + 8, FLDH = NH + 8;   // padded LDS row strides (BF16)
-constexpr int FUSED_LDS = (NH * FLD1 + 2 * NH * FLDH + NOP * FLDH + 4 * 32 * FLDH) * 2;
+constexpr int FUSED_LDS = (NH * FLD1 + 2 * NH * FLDH + NOP * FLDH + FWD_WAVES * 16 * FLDH) * 2;
+static_assert(FUSED_LDS <= 160 * 1024, "the weights and the activation tiles share one CU's LDS");
 
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -107,25 +122,25 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(256) void k_fwd_fused(const uint16_t* __restrict__ feat, int64_t M,
+__global__ __launch_bounds__(64 * FWD_WAVES) void k_fwd_fused(const uint16_t* __restrict__ feat, int64_t M,
                                                    const float* __restrict__ th, Packed pk, float* __restrict__ Y) {
     extern __shared__ uint16_t lds[];
     uint16_t* w1 = lds;                      // [128][FLD1]
     uint16_t* w2 = w1 + NH * FLD1;           // [128][FLDH]
     uint16_t* w3 = w2 + NH * FLDH;           // [128][FLDH]
     uint16_t* w4 = w3 + NH * FLDH;           // [16][FLDH]
-    uint16_t* act = w4 + NOP * FLDH;         // [4 waves][32][FLDH]
+    uint16_t* act = w4 + NOP * FLDH;         // [waves][16][FLDH]
     // weights -> LDS (16-byte chunks)
-    for (int t = threadIdx.x; t < NH * (NF / 8); t += 256) {
+    for (int t = threadIdx.x; t < NH * (NF / 8); t += 64 * FWD_WAVES) {
         const int r = t / (NF / 8), c = (t % (NF / 8)) * 8;
         *reinterpret_cast<uint4*>(w1 + r * FLD1 + c) = *reinterpret_cast<const uint4*>(pk.wt1 + r * NF + c);
     }
-    for (int t = threadIdx.x; t < NH * (NH / 8); t += 256) {
+    for (int t = threadIdx.x; t < NH * (NH / 8); t += 64 * FWD_WAVES) {
         const int r = t / (NH / 8), c = (t % (NH / 8)) * 8;
         *reinterpret_cast<uint4*>(w2 + r * FLDH + c) = *reinterpret_cast<const uint4*>(pk.wt2 + r * NH + c);
         *reinterpret_cast<uint4*>(w3 + r * FLDH + c) = *reinterpret_cast<const uint4*>(pk.wt3 + r * NH + c);
     }
-    for (int t = threadIdx.x; t < NOP * (NH / 8); t += 256) {
+    for (int t = threadIdx.x; t < NOP * (NH / 8); t += 64 * FWD_WAVES) {
         const int r = t / (NH / 8), c = (t % (NH / 8)) * 8;
         *reinterpret_cast<uint4*>(w4 + r * FLDH + c) = *reinterpret_cast<const uint4*>(pk.wt4 + r * NH + c);
     }
@@ -134,108 +149,81 @@ __global__ __launch_bounds__(256) void k_fwd_fused(const uint16_t* __restrict__ 
     // the B operand (columns = sample rows): a lane then holds 4 consecutive
     // output features of one sample, written to the LDS tile as one 8-byte store.
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint16_t* my = act + w * 32 * FLDH;
+    uint16_t* my = act + w * 16 * FLDH;
     const int l16 = lane & 15, g4 = (lane >> 4) * 4, kb = (lane >> 4) * 8;
-    const int64_t n_tiles = (M + 31) / 32;
+    const int64_t n_tiles = (M + 15) / 16;
     constexpr int KS1 = NF / 32, MT = NH / 16;
-    auto load_tile = [&](int64_t tile, bf16x8 (&fa)[KS1][2]) {
+    auto load_tile = [&](int64_t tile, bf16x8 (&fa)[KS1]) {
+        const int64_t m = tile * 16 + l16;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t m = tile * 32 + 16 * j + l16;
-#pragma unroll
-            for (int ks = 0; ks < KS1; ++ks) fa[ks][j] = m < M ? ld8(feat + m * NF + ks * 32 + kb) : zero8();
-        }
+        for (int ks = 0; ks < KS1; ++ks) fa[ks] = m < M ? ld8(feat + m * NF + ks * 32 + kb) : zero8();
     };
     // bias + SiLU of acc -> BF16 activation tile
-    auto to_tile = [&](const f32x4 (&acc)[MT][2], const float* bias) {
+    auto to_tile = [&](const f32x4 (&acc)[MT], const float* bias) {
         wave_lds_sync();
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
             const int f0 = 16 * i + g4;
             const float4 b = *reinterpret_cast<const float4*>(bias + f0);
             const float bb[4] = {b.x, b.y, b.z, b.w};
+            uint16_t h[4];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                uint16_t h[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float z = acc[i][j][r] + bb[r];
-                    h[r] = f2bf_hw(z * sigmoidf(z));
-                }
-                *reinterpret_cast<uint2*>(my + (16 * j + l16) * FLDH + f0) =
-                    make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+            for (int r = 0; r < 4; ++r) {
+                const float z = acc[i][r] + bb[r];
+                h[r] = f2bf_hw(z * sigmoidf(z));
             }
+            *reinterpret_cast<uint2*>(my + l16 * FLDH + f0) =
+                make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
         }
         wave_lds_sync();
     };
-    const int64_t t_step = (int64_t)gridDim.x * 4;
-    int64_t tile = (int64_t)blockIdx.x * 4 + w;
-    bf16x8 fa[KS1][2];
+    const int64_t t_step = (int64_t)gridDim.x * FWD_WAVES;
+    int64_t tile = (int64_t)blockIdx.x * FWD_WAVES + w;
+    bf16x8 fa[KS1];
     if (tile < n_tiles) load_tile(tile, fa);
     for (; tile < n_tiles; tile += t_step) {
-        const int64_t m0 = tile * 32;
-        bf16x8 fnext[KS1][2];
+        bf16x8 fnext[KS1];
         if (tile + t_step < n_tiles) load_tile(tile + t_step, fnext);
-        f32x4 acc[MT][2];
+        f32x4 acc[MT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ks = 0; ks < KS1; ++ks)   // layer 1
 #pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {   // layer 1
-#pragma unroll
-            for (int i = 0; i < MT; ++i) {
-                const bf16x8 a = ld8(w1 + (16 * i + l16) * FLD1 + ks * 32 + kb);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, fa[ks][j], acc[i][j], 0, 0, 0);
-            }
-        }
+            for (int i = 0; i < MT; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(w1 + (16 * i + l16) * FLD1 + ks * 32 + kb), fa[ks],
+                                                                 acc[i], 0, 0, 0);
 #pragma unroll
         for (int layer = 0; layer < 2; ++layer) {   // layers 2 and 3
             to_tile(acc, th + (layer == 0 ? OB1 : OB2));
             const uint16_t* wl = layer == 0 ? w2 : w3;
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
+            for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
             for (int k = 0; k < NH; k += 32) {
-                bf16x8 b[2];
+                const bf16x8 b = ld8(my + l16 * FLDH + k + kb);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) b[j] = ld8(my + (16 * j + l16) * FLDH + k + kb);
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    const bf16x8 a = ld8(wl + (16 * i + l16) * FLDH + k + kb);
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[j], acc[i][j], 0, 0, 0);
-                }
+                for (int i = 0; i < MT; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(wl + (16 * i + l16) * FLDH + k + kb), b, acc[i],
+                                                                     0, 0, 0);
             }
         }
         to_tile(acc, th + OB3);
-        f32x4 out[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        f32x4 out = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < NH; k += 32) {   // output layer (14 of 16 rows of W4^T used)
-            const bf16x8 a = ld8(w4 + l16 * FLDH + k + kb);
+        for (int k = 0; k < NH; k += 32)   // output layer (14 of 16 rows of W4^T used)
+            out = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(w4 + l16 * FLDH + k + kb), ld8(my + l16 * FLDH + k + kb),
+                                                          out, 0, 0, 0);
+        const int64_t m = tile * 16 + l16;
+        if (m < M) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                out[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ld8(my + (16 * j + l16) * FLDH + k + kb), out[j], 0, 0, 0);
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t m = m0 + 16 * j + l16;
-            if (m < M) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int f = g4 + r;
-                    if (f < NO) Y[m * NO + f] = out[j][r] + th[OB4 + f];
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int f = g4 + r;
+                if (f < NO) Y[m * NO + f] = out[r] + th[OB4 + f];
             }
         }
 #pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) {
-            fa[ks][0] = fnext[ks][0];
-            fa[ks][1] = fnext[ks][1];
-        }
+        for (int ks = 0; ks < KS1; ++ks) fa[ks] = fnext[ks];
     }
 }
 
@@ -542,6 +530,7 @@ __device__ __forceinline__ double sinc_d(double x) {
 }
 
 constexpr int FW_CAND = 256;   // near-set rows up to this length are ranked in parallel
+constexpr int FW_ROWS = 8;     // rows formed at a time
 
 // One wave per wire p (caller order) and the rows p*R + r of it that fall in
 // the requested range.  The 16 nearest neighbours are chosen once per wire:
@@ -549,18 +538,28 @@ constexpr int FW_CAND = 256;   // near-set rows up to this length are ranked in 
 // (squared distance, caller index) key (rows longer than FW_CAND fall back to
 // repeated minimum search), and the neighbours' geometry is staged in LDS.
 // The features that do not depend on the incidence are formed once per wire.
+// The rows are formed FW_ROWS at a time in LDS, one lane per (row, neighbour) and
+// then per (row, own rooftop), and stored with 16-byte writes.
+//   Bound: FP64 arithmetic and the store of 384 bytes a row.  Two rows per pass
+// (24 of 32 lanes each), the library's sincos and 2-byte stores straight to HBM
+// took 373 us for 800,000 rows, 219 so.
 __global__ __launch_bounds__(64) void k_features(const Wire* __restrict__ wires, const int32_t* __restrict__ perm,
                                                  const int32_t* __restrict__ iperm,
                                                  const int64_t* __restrict__ row_ptr,
                                                  const int32_t* __restrict__ col_idx, int64_t R, int64_t row0,
                                                  int64_t n_rows, const double* __restrict__ k_hat,
-                                                 const double* __restrict__ e_hat, double k, double lam, double d_c,
+                                                 const double* __restrict__ e_hat, double kp, double lam, double d_c,
                                                  uint16_t* __restrict__ feat) {
 #pragma clang fp contract(off)
-    __shared__ double cd2[FW_CAND];
-    __shared__ int32_t cid[FW_CAND], cint[FW_CAND];
+    // the candidates while the neighbours are chosen, then the staged rows
+    __shared__ __align__(16) unsigned char buf[FW_CAND * 16];
+    static_assert(FW_ROWS * NF * 2 <= FW_CAND * 16, "the rows fit the candidates' space");
+    double* cd2 = reinterpret_cast<double*>(buf);
+    int32_t* cid = reinterpret_cast<int32_t*>(buf + FW_CAND * 8);
+    int32_t* cint = cid + FW_CAND;
+    uint16_t* st = reinterpret_cast<uint16_t*>(buf);   // [FW_ROWS][192]
     __shared__ int32_t slot[KNB];
-    __shared__ double sg[KNB][8];   // d.x, d.y, d.z, d2, t'.x, t'.y, t'.z, L'
+    __shared__ double sg[KNB][6];   // d.x, d.y, d.z, t'.x, t'.y, t'.z
     __shared__ uint16_t fixed[KNB][4];   // |d|/d_c, length feature, Re, Im exp(-j k |d|)
     const int lane = threadIdx.x;
     const int64_t p = row0 / R + blockIdx.x;
@@ -573,154 +572,178 @@ __global__ __launch_bounds__(64) void k_features(const Wire* __restrict__ wires,
     const int64_t ne = e1 - e0;   // includes the diagonal
     const int64_t cnt = ne - 1;
     if (lane < KNB) slot[lane] = -1;
-    if (ne <= FW_CAND) {
-        for (int64_t t = lane; t < ne; t += 64) {
-            const int32_t c = col_idx[e0 + t];
-            cint[t] = c;
-            cid[t] = perm[c];
-            cd2[t] = c == ip ? 0.0 : dist2(w, wires[c]);
+    // geometry of the neighbour in slot j and its incidence-independent features
+    auto set_slot = [&](int j, const Wire& v, double d2) {
+        sg[j][0] = v.cx - w.cx;
+        sg[j][1] = v.cy - w.cy;
+        sg[j][2] = v.cz - w.cz;
+        sg[j][3] = v.tx;
+        sg[j][4] = v.ty;
+        sg[j][5] = v.tz;
+        double sn, cs;
+        sincospi_any(kp * sqrt(d2), sn, cs);
+        fixed[j][0] = d2bf(sqrt(d2) / d_c);
+        fixed[j][1] = d2bf(10.0 * (v.len / lam - 0.5));
+        fixed[j][2] = d2bf(cs);
+        fixed[j][3] = d2bf(-sn);
+    };
+    if (ne <= 64) {   // one candidate per lane, kept in its registers until its rank is known
+        Wire v = w;
+        double d2 = 0.0;
+        int32_t id = 0, c = ip;
+        if (lane < ne) {
+            c = col_idx[e0 + lane];
+            id = perm[c];
+            v = wires[c];
+            if (c != ip) d2 = dist2(w, v);
+            cd2[lane] = c == ip ? INFINITY : d2;   // the wire itself comes before nobody
+            cid[lane] = id;
         }
         __syncthreads();
-        for (int64_t t = lane; t < ne; t += 64) {
-            if (cint[t] == ip) continue;
-            const double d2 = cd2[t];
-            const int32_t id = cid[t];
-            int rank = 0;
-            for (int64_t u = 0; u < ne; ++u) {
-                if (cint[u] == ip) continue;
-                const double du = cd2[u];
-                rank += (du < d2 || (du == d2 && cid[u] < id)) ? 1 : 0;
-            }
-            if (rank < KNB) slot[rank] = cint[t];
+        int rank = 0;
+        for (int u = 0; u < (int)ne; ++u) {
+            const double du = cd2[u];
+            rank += (du < d2 || (du == d2 && cid[u] < id)) ? 1 : 0;
         }
-    } else {   // long row: repeated minimum search (the same on every lane)
-        double pd2 = -1.0;
-        int32_t pid = -1;
-        for (int j = 0; j < KNB; ++j) {
-            double bd2 = INFINITY;
-            int32_t bid = INT32_MAX, bint = -1;
-            for (int64_t e = e0; e < e1; ++e) {
-                const int32_t c = col_idx[e];
-                if (c == ip) continue;
-                const double d2 = dist2(w, wires[c]);
-                const int32_t id = perm[c];
-                const bool after = d2 > pd2 || (d2 == pd2 && id > pid);
-                const bool before = d2 < bd2 || (d2 == bd2 && id < bid);
-                if (after && before) { bd2 = d2; bid = id; bint = c; }
+        if (lane < ne && c != ip && rank < KNB) {
+            slot[rank] = c;
+            set_slot(rank, v, d2);
+        }
+    } else {
+        if (ne <= FW_CAND) {
+            for (int64_t t = lane; t < ne; t += 64) {
+                const int32_t c = col_idx[e0 + t];
+                cint[t] = c;
+                cid[t] = perm[c];
+                cd2[t] = c == ip ? 0.0 : dist2(w, wires[c]);
             }
-            if (bint < 0) break;
-            if (lane == 0) slot[j] = bint;
-            pd2 = bd2;
-            pid = bid;
+            __syncthreads();
+            for (int64_t t = lane; t < ne; t += 64) {
+                if (cint[t] == ip) continue;
+                const double d2 = cd2[t];
+                const int32_t id = cid[t];
+                int rank = 0;
+                for (int64_t u = 0; u < ne; ++u) {
+                    if (cint[u] == ip) continue;
+                    const double du = cd2[u];
+                    rank += (du < d2 || (du == d2 && cid[u] < id)) ? 1 : 0;
+                }
+                if (rank < KNB) slot[rank] = cint[t];
+            }
+        } else {   // long row: repeated minimum search (the same on every lane)
+            double pd2 = -1.0;
+            int32_t pid = -1;
+            for (int j = 0; j < KNB; ++j) {
+                double bd2 = INFINITY;
+                int32_t bid = INT32_MAX, bint = -1;
+                for (int64_t e = e0; e < e1; ++e) {
+                    const int32_t c = col_idx[e];
+                    if (c == ip) continue;
+                    const double d2 = dist2(w, wires[c]);
+                    const int32_t id = perm[c];
+                    const bool after = d2 > pd2 || (d2 == pd2 && id > pid);
+                    const bool before = d2 < bd2 || (d2 == bd2 && id < bid);
+                    if (after && before) { bd2 = d2; bid = id; bint = c; }
+                }
+                if (bint < 0) break;
+                if (lane == 0) slot[j] = bint;
+                pd2 = bd2;
+                pid = bid;
+            }
+        }
+        __syncthreads();
+        if (lane < KNB && slot[lane] >= 0) {
+            const Wire v = wires[slot[lane]];
+            set_slot(lane, v, dist2(w, v));
         }
     }
     __syncthreads();
-    // per-slot geometry and the incidence-independent features
-    if (lane < KNB && slot[lane] >= 0) {
-        const Wire v = wires[slot[lane]];
-        const double d2 = dist2(w, v);
-        sg[lane][0] = v.cx - w.cx;
-        sg[lane][1] = v.cy - w.cy;
-        sg[lane][2] = v.cz - w.cz;
-        sg[lane][3] = d2;
-        sg[lane][4] = v.tx;
-        sg[lane][5] = v.ty;
-        sg[lane][6] = v.tz;
-        sg[lane][7] = v.len;
-        double sn, cs;
-        sincos(k * sqrt(d2), &sn, &cs);
-        fixed[lane][0] = d2bf(sqrt(d2) / d_c);
-        fixed[lane][1] = d2bf(10.0 * (v.len / lam - 0.5));
-        fixed[lane][2] = d2bf(cs);
-        fixed[lane][3] = d2bf(-sn);
-    }
-    __syncthreads();
-    // two rows per pass: lanes 0-31 the first, 32-63 the second; within a half,
-    // lane m < 16 writes neighbour slot m, 16 <= m < 23 own rooftop m - 16,
-    // m = 23 the two scalar own features.  Every active lane evaluates exactly
-    // one sine/cosine per row.
     const double D = w.len / 8.0;
-    const int half = lane >> 5, m = lane & 31;
-    for (int64_t row2 = rb; row2 < re; row2 += 2) {
-        const int64_t row = row2 + half;
-        const bool live = row < re;
-        const int64_t r = (live ? row : row2) - p * R;
-        const double kx = k_hat[3 * r], ky = k_hat[3 * r + 1], kz = k_hat[3 * r + 2];
-        const double ex = e_hat[3 * r], ey = e_hat[3 * r + 1], ez = e_hat[3 * r + 2];
-        const double sp = (w.tx * ex + w.ty * ey + w.tz * ez) >= 0.0 ? 1.0 : -1.0;
-        const double tx = sp * w.tx, ty = sp * w.ty, tz = sp * w.tz;
-        const bool is_slot = m < KNB && slot[m < KNB ? m : 0] >= 0;
-        const bool is_own = m >= 16 && m < 23;
-        const int jj = m < KNB ? m : 0;
-        double dx = 0.0, dy = 0.0, dz = 0.0;
-        if (is_slot) {
-            dx = sg[jj][0];
-            dy = sg[jj][1];
-            dz = sg[jj][2];
-        }
-        double beta = 0.0, arg = 0.0;
-        if (is_own) {
-            beta = k * (kx * tx + ky * ty + kz * tz);
-            arg = beta * (-0.5 * w.len + (m - 16 + 1) * D);
-        } else if (is_slot) {
-            arg = k * (kx * dx + ky * dy + kz * dz);
-        }
-        double sn, cs;
-        sincos(arg, &sn, &cs);
-        if (!live) continue;
-        uint16_t* out = feat + (row - row0) * NF;
-        if (is_slot) {
-            const double vtx = sg[jj][4], vty = sg[jj][5], vtz = sg[jj][6];
+    for (int64_t row0s = rb; row0s < re; row0s += FW_ROWS) {
+        const int nr = (int)(re - row0s < FW_ROWS ? re - row0s : FW_ROWS);
+        for (int t = lane; t < KNB * nr; t += 64) {   // neighbour slots
+            const int m = t % KNB, rl = t / KNB;
+            uint16_t* f = st + rl * NF + FOWN + FNB * m;
+            if (slot[m] < 0) {
+#pragma unroll
+                for (int g = 0; g < FNB; ++g) f[g] = 0;
+                continue;
+            }
+            const int64_t r = row0s + rl - p * R;
+            const double kx = k_hat[3 * r], ky = k_hat[3 * r + 1], kz = k_hat[3 * r + 2];
+            const double ex = e_hat[3 * r], ey = e_hat[3 * r + 1], ez = e_hat[3 * r + 2];
+            const double sp = (w.tx * ex + w.ty * ey + w.tz * ez) >= 0.0 ? 1.0 : -1.0;
+            const double tx = sp * w.tx, ty = sp * w.ty, tz = sp * w.tz;
+            const double dx = sg[m][0], dy = sg[m][1], dz = sg[m][2];
+            double sn, cs;
+            sincospi_any(kp * (kx * dx + ky * dy + kz * dz), sn, cs);
+            const double vtx = sg[m][3], vty = sg[m][4], vtz = sg[m][5];
             const double sv = (vtx * ex + vty * ey + vtz * ez) >= 0.0 ? 1.0 : -1.0;
             const double ux = sv * vtx, uy = sv * vty, uz = sv * vtz;
             const double ue = ux * ex + uy * ey + uz * ez;
-            uint16_t* f = out + FOWN + FNB * jj;
-            f[0] = fixed[jj][0];
+            f[0] = fixed[m][0];
             f[1] = d2bf((tx * dx + ty * dy + tz * dz) / d_c);
             f[2] = d2bf((ux * dx + uy * dy + uz * dz) / d_c);
             f[3] = d2bf(tx * ux + ty * uy + tz * uz);
             f[4] = d2bf(ue * cs);
             f[5] = d2bf(-ue * sn);
-            f[6] = fixed[jj][1];
+            f[6] = fixed[m][1];
             f[7] = d2bf(kx * ux + ky * uy + kz * uz);
-            f[8] = fixed[jj][2];
-            f[9] = fixed[jj][3];
+            f[8] = fixed[m][2];
+            f[9] = fixed[m][3];
             f[10] = d2bf(1.0);
-        } else if (m < KNB) {   // empty slot
-            uint16_t* f = out + FOWN + FNB * m;
-#pragma unroll
-            for (int g = 0; g < FNB; ++g) f[g] = 0;
-        } else if (is_own) {
-            const double te = tx * ex + ty * ey + tz * ez;
-            const double env = sinc_d(beta * D / 2.0);
+        }
+        for (int t = lane; t < 8 * nr; t += 64) {   // own rooftops (7 a row) and the two scalars
+            const int q = t % 8, rl = t / 8;
+            uint16_t* out = st + rl * NF;
+            if (q == 7) {
+                out[0] = d2bf(10.0 * (w.len / lam - 0.5));
+                out[1] = d2bf((double)cnt / 16.0);
+                continue;
+            }
+            const int64_t r = row0s + rl - p * R;
+            const double kx = k_hat[3 * r], ky = k_hat[3 * r + 1], kz = k_hat[3 * r + 2];
+            const double te0 = w.tx * e_hat[3 * r] + w.ty * e_hat[3 * r + 1] + w.tz * e_hat[3 * r + 2];
+            const double sp = te0 >= 0.0 ? 1.0 : -1.0;
+            const double te = sp * te0;
+            const double beta = kp * (sp * (kx * w.tx + ky * w.ty + kz * w.tz));   // half turns per metre
+            double sn, cs;
+            sincospi_any(beta * (-0.5 * w.len + (q + 1) * D), sn, cs);
+            const double env = sinc_d(PI_H * beta * D / 2.0);
             const double a = te * (env * env);
-            const int q = m - 16;
             out[2 + 2 * q] = d2bf(a * cs);
             out[3 + 2 * q] = d2bf(-a * sn);
-        } else if (m == 23) {
-            out[0] = d2bf(10.0 * (w.len / lam - 0.5));
-            out[1] = d2bf((double)cnt / 16.0);
         }
+        __syncthreads();
+        uint4* dst = reinterpret_cast<uint4*>(feat + (row0s - row0) * NF);   // the rows are consecutive, 384 bytes each
+        for (int t = lane; t < nr * (NF / 8); t += 64) dst[t] = reinterpret_cast<const uint4*>(st)[t];
+        __syncthreads();
     }
 }
 
 // ------------------------------------------------------------------ currents <-> outputs
 // Isolated response of wire w: b = Pinv_p u_p exp(+j k k_hat.c_p), raw rooftop
-// order, FP64 accumulation over the stored inverse self block.
+// order, FP64 accumulation over the stored inverse self block; kp = 2/lambda.
+// The rooftops' phases are walked outwards from the wire's centre by one complex
+// product each, the segment's phase and its sinc come from one half angle.
 template <typename CZ>
 __device__ __forceinline__ void isolated_response(const Wire& w, const CZ* __restrict__ P, const double* kh,
-                                                  const double* eh, double k, c128 (&b)[7]) {
+                                                  const double* eh, double kp, c128 (&b)[7]) {
     const double te = w.tx * eh[0] + w.ty * eh[1] + w.tz * eh[2];
-    const double beta = k * (kh[0] * w.tx + kh[1] * w.ty + kh[2] * w.tz);
     const double D = w.len / 8.0;
-    const double sc = sinc_d(0.5 * beta * D);
+    const double bd = kp * (kh[0] * w.tx + kh[1] * w.ty + kh[2] * w.tz) * D;   // phase of a segment, half turns
+    double sh, ch;
+    sincospi_any(0.5 * bd, sh, ch);
+    const double h = PI_H * 0.5 * bd;
+    const double sc = fabs(h) < 1e-4 ? 1.0 - h * h / 6.0 : sh / h;
     const double env = te * D * (sc * sc);
+    const c128 fwd = {fma(-2.0 * sh, sh, 1.0), -2.0 * sh * ch}, bwd = {fwd.re, -fwd.im};
     c128 u[7];
+    u[3] = c128{env, 0.0};
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        double sn, cs;
-        sincos(beta * (-0.5 * w.len + (q + 1) * D), &sn, &cs);
-        u[q] = c128{env * cs, -env * sn};
+    for (int m = 1; m <= 3; ++m) {
+        u[3 + m] = cmul(u[2 + m], fwd);
+        u[3 - m] = cmul(u[4 - m], bwd);
     }
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
@@ -734,7 +757,7 @@ __device__ __forceinline__ void isolated_response(const Wire& w, const CZ* __res
 template <typename CZ>
 __global__ void k_targets(const Wire* __restrict__ wires, const int32_t* __restrict__ iperm, const CZ* __restrict__ Pinv,
                           int64_t n, int64_t R, const double* __restrict__ k_hat, const double* __restrict__ e_hat,
-                          double k, const c128* __restrict__ X, float* __restrict__ Y) {
+                          double kp, const c128* __restrict__ X, float* __restrict__ Y) {
     const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (row >= n * R) return;
     const int64_t p = row / R, r = row - p * R;
@@ -744,9 +767,9 @@ __global__ void k_targets(const Wire* __restrict__ wires, const int32_t* __restr
     const double* eh = e_hat + 3 * r;
     const bool flip = (w.tx * eh[0] + w.ty * eh[1] + w.tz * eh[2]) < 0.0;
     c128 b[7];
-    isolated_response(w, Pinv + (int64_t)ip * 49, kh, eh, k, b);
+    isolated_response(w, Pinv + (int64_t)ip * 49, kh, eh, kp, b);
     double sn, cs;
-    sincos(k * (kh[0] * w.cx + kh[1] * w.cy + kh[2] * w.cz), &sn, &cs);
+    sincospi_any(kp * (kh[0] * w.cx + kh[1] * w.cy + kh[2] * w.cz), sn, cs);
     const double sc = (flip ? -1.0 : 1.0) / X_SCALE;
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
@@ -762,7 +785,7 @@ __global__ void k_targets(const Wire* __restrict__ wires, const int32_t* __restr
 template <typename CZ>
 __global__ void k_assemble(const Wire* __restrict__ wires, const int32_t* __restrict__ iperm,
                            const CZ* __restrict__ Pinv, int64_t R, int64_t row0, int64_t n_rows,
-                           const double* __restrict__ k_hat, const double* __restrict__ e_hat, double k,
+                           const double* __restrict__ k_hat, const double* __restrict__ e_hat, double kp,
                            const float* __restrict__ Y, c128* __restrict__ X) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n_rows) return;
@@ -774,9 +797,9 @@ __global__ void k_assemble(const Wire* __restrict__ wires, const int32_t* __rest
     const double* eh = e_hat + 3 * r;
     const bool flip = (w.tx * eh[0] + w.ty * eh[1] + w.tz * eh[2]) < 0.0;
     c128 b[7];
-    isolated_response(w, Pinv + (int64_t)ip * 49, kh, eh, k, b);
+    isolated_response(w, Pinv + (int64_t)ip * 49, kh, eh, kp, b);
     double sn, cs;
-    sincos(k * (kh[0] * w.cx + kh[1] * w.cy + kh[2] * w.cz), &sn, &cs);
+    sincospi_any(kp * (kh[0] * w.cx + kh[1] * w.cy + kh[2] * w.cz), sn, cs);
     const double sc = (flip ? -1.0 : 1.0) * X_SCALE;
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
@@ -1047,10 +1070,10 @@ chaff_status forward_fused(const float* theta, const Packed& pk, const uint16_t*
                                    FUSED_LDS) == hipSuccess;
     }();
     if (!attr) return fail(CHAFF_EHIP, "cannot reserve LDS for the fused forward kernel");
-    const int64_t tiles = (M + 31) / 32;
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (tiles + 3) / 4));
+    const int64_t tiles = (M + 15) / 16;
+    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (tiles + FWD_WAVES - 1) / FWD_WAVES));
     ProfScope ps("mlp_forward", st, layer_flops(M, NF, NH) + 2 * layer_flops(M, NH, NH) + layer_flops(M, NH, NO), true);
-    hipLaunchKernelGGL(k_fwd_fused, dim3(grid), dim3(256), FUSED_LDS, st, feat, M, theta, pk, Y);
+    hipLaunchKernelGGL(k_fwd_fused, dim3(grid), dim3(64 * FWD_WAVES), FUSED_LDS, st, feat, M, theta, pk, Y);
     CHAFF_LAUNCH_CHECK();
     return CHAFF_OK;
 }
@@ -1144,26 +1167,26 @@ chaff_status mlp_train_step(float* theta, float* m, float* v, int32_t t, float l
 chaff_status mlp_features(Cloud* c, const double* k_hat, const double* e_hat, int64_t R, int64_t row0, int64_t n_rows,
                           uint16_t* feat, hipStream_t st) {
     if (n_rows == 0) return CHAFF_OK;
-    const double k = 2.0 * 3.14159265358979323846 / c->wavelength;
     ProfScope ps("mlp_features", st, (double)n_rows * NF * 2.0);
     const int64_t n_wires = (row0 + n_rows - 1) / R - row0 / R + 1;
     hipLaunchKernelGGL(k_features, dim3((unsigned)n_wires), dim3(64), 0, st, (const Wire*)c->wires,
                        (const int32_t*)c->perm, (const int32_t*)c->iperm, (const int64_t*)c->row_ptr,
-                       (const int32_t*)c->col_idx, R, row0, n_rows, k_hat, e_hat, k, c->wavelength, c->d_c, feat);
+                       (const int32_t*)c->col_idx, R, row0, n_rows, k_hat, e_hat, 2.0 / c->wavelength, c->wavelength,
+                       c->d_c, feat);
     CHAFF_LAUNCH_CHECK();
     return CHAFF_OK;
 }
 
 chaff_status mlp_targets(Cloud* c, chaff_prec prec, const void* Pinv, const double* k_hat, const double* e_hat,
                          int64_t R, const void* X, float* Y, hipStream_t st) {
-    const double k = 2.0 * 3.14159265358979323846 / c->wavelength;
+    const double kp = 2.0 / c->wavelength;
     ProfScope ps("mlp_targets", st, (double)c->n * R * (7 * 16 + NO * 4));
     if (prec == CHAFF_C64)
         hipLaunchKernelGGL(k_targets<c64>, dim3(nblk(c->n * R, 256)), dim3(256), 0, st, (const Wire*)c->wires,
-                           (const int32_t*)c->iperm, (const c64*)Pinv, c->n, R, k_hat, e_hat, k, (const c128*)X, Y);
+                           (const int32_t*)c->iperm, (const c64*)Pinv, c->n, R, k_hat, e_hat, kp, (const c128*)X, Y);
     else
         hipLaunchKernelGGL(k_targets<c128>, dim3(nblk(c->n * R, 256)), dim3(256), 0, st, (const Wire*)c->wires,
-                           (const int32_t*)c->iperm, (const c128*)Pinv, c->n, R, k_hat, e_hat, k, (const c128*)X, Y);
+                           (const int32_t*)c->iperm, (const c128*)Pinv, c->n, R, k_hat, e_hat, kp, (const c128*)X, Y);
     CHAFF_LAUNCH_CHECK();
     return CHAFF_OK;
 }
@@ -1188,7 +1211,7 @@ chaff_status mlp_guess(Cloud* c, chaff_prec prec, const void* Pinv, const float*
     if (!cv.ok()) return fail(CHAFF_EWORKSPACE, "mlp guess workspace too small");
     chaff_status s = launch_pack(theta, b.pk, st);
     if (s != CHAFF_OK) return s;
-    const double k = 2.0 * 3.14159265358979323846 / c->wavelength;
+    const double kp = 2.0 / c->wavelength;
     for (int64_t r0 = 0; r0 < total; r0 += chunk) {
         const int64_t nr = std::min(chunk, total - r0);
         s = mlp_features(c, k_hat, e_hat, R, r0, nr, feat, st);
@@ -1198,11 +1221,11 @@ chaff_status mlp_guess(Cloud* c, chaff_prec prec, const void* Pinv, const float*
         ProfScope ps("mlp_assemble", st, (double)nr * (NO * 4 + 7 * 16) + (double)nr / R * 49 * (prec == CHAFF_C64 ? 8 : 16));
         if (prec == CHAFF_C64)
             hipLaunchKernelGGL(k_assemble<c64>, dim3(nblk(nr, 256)), dim3(256), 0, st, (const Wire*)c->wires,
-                               (const int32_t*)c->iperm, (const c64*)Pinv, R, r0, nr, k_hat, e_hat, k,
+                               (const int32_t*)c->iperm, (const c64*)Pinv, R, r0, nr, k_hat, e_hat, kp,
                                (const float*)b.Y, (c128*)X);
         else
             hipLaunchKernelGGL(k_assemble<c128>, dim3(nblk(nr, 256)), dim3(256), 0, st, (const Wire*)c->wires,
-                               (const int32_t*)c->iperm, (const c128*)Pinv, R, r0, nr, k_hat, e_hat, k,
+                               (const int32_t*)c->iperm, (const c128*)Pinv, R, r0, nr, k_hat, e_hat, kp,
                                (const float*)b.Y, (c128*)X);
         CHAFF_LAUNCH_CHECK();
     }
