@@ -794,38 +794,73 @@ __global__ __launch_bounds__(RB) void k_norm2(const Chunk* __restrict__ chunks, 
     if (threadIdx.x < st && m.r < s) part[((int64_t)blockIdx.x * nslot + slot) * s + m.r] = v;
 }
 
-// out[rel][g][r] = sum over k in [off[g], off[g+1]) of in[k*ch_stride + (slot0+rel)*slot_stride + r].
-// One 1024-thread block per (rel, g, 64-column tile): wave w sums k = off[g]+w,
-// +16, ... (coalesced over the columns), then the 16 wave sums are added in
-// wave order.  Fixed order throughout, so the result is reproducible.
-constexpr int CS_WAVES = 16;
-__global__ __launch_bounds__(64 * CS_WAVES) void k_group_sum(const c128* __restrict__ in, int64_t ch_stride,
-                                                             int64_t slot_stride, int slot0,
-                                                             const int32_t* __restrict__ off, int n_groups,
-                                                             int64_t s, c128* __restrict__ out) {
-    __shared__ c128 red[CS_WAVES][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// Sums over many partial results.  A block of SUM_THREADS threads sums in[k stride + r] over
+// k in [k0, k1) for CW columns: SUM_THREADS / CW strands walk k, coalesced over the columns, four
+// loads in flight each, and are added pairwise in LDS.  Fixed order throughout, so
+// the result is reproducible.  Thread r < CW returns the sum of column r.
+//   Bound: the latency of a strand's loads.  One 64-column tile per block left
+// 7 of 8 lanes idle at 8 columns and gave each of the 16 waves n/16 loads one
+// after the other: 2048 partials of 64 columns took 38 us, of 8 columns 21 us.
+constexpr int SUM_THREADS = 1024;
+template <int CW>
+__device__ __forceinline__ c128 block_sum(const c128* __restrict__ in, int64_t stride, int64_t k0, int64_t k1,
+                                          int64_t r, bool live, c128* red) {
+    constexpr int STRANDS = SUM_THREADS / CW;
+    c128 acc = {0, 0};
+    if (live) {
+        int64_t k = k0 + (int)threadIdx.x / CW;
+        for (; k + 3 * STRANDS < k1; k += 4 * STRANDS) {
+            const c128* q = in + k * stride + r;
+            const c128 a0 = q[0], a1 = q[STRANDS * stride], a2 = q[2 * STRANDS * stride], a3 = q[3 * STRANDS * stride];
+            acc = cadd(cadd(cadd(cadd(acc, a0), a1), a2), a3);
+        }
+        for (; k < k1; k += STRANDS) acc = cadd(acc, in[k * stride + r]);
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int h = SUM_THREADS / 2; h >= CW; h >>= 1) {
+        if ((int)threadIdx.x < h) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + h]);
+        __syncthreads();
+    }
+    const c128 out = red[threadIdx.x % CW];
+    __syncthreads();
+    return out;
+}
+
+// out[rel][g][r] = sum over k in [off[g], off[g+1]) of in[k*ch_stride + (slot0+rel)*slot_stride + r]
+template <int CW>
+__global__ __launch_bounds__(SUM_THREADS) void k_group_sum(const c128* __restrict__ in, int64_t ch_stride,
+                                                           int64_t slot_stride, int slot0,
+                                                           const int32_t* __restrict__ off, int n_groups, int64_t s,
+                                                           c128* __restrict__ out) {
+    __shared__ c128 red[SUM_THREADS];
     const int g = blockIdx.x % n_groups;
     const int rel = blockIdx.x / n_groups;
-    const int64_t r = (int64_t)blockIdx.y * 64 + lane;
-    c128 acc = {0, 0};
-    if (r < s)
-        for (int64_t k = off[g] + w; k < off[g + 1]; k += CS_WAVES)
-            acc = cadd(acc, in[k * ch_stride + (int64_t)(slot0 + rel) * slot_stride + r]);
-    red[w][lane] = acc;
-    __syncthreads();
-    if (w == 0 && r < s) {
-        c128 t = red[0][lane];
-        for (int k = 1; k < CS_WAVES; ++k) t = cadd(t, red[k][lane]);
-        out[((int64_t)rel * n_groups + g) * s + r] = t;
-    }
+    const int64_t r = (int64_t)blockIdx.y * CW + threadIdx.x % CW;
+    const c128 t = block_sum<CW>(in + (int64_t)(slot0 + rel) * slot_stride, ch_stride, off[g], off[g + 1], r, r < s, red);
+    if ((int)threadIdx.x < CW && r < s) out[((int64_t)rel * n_groups + g) * s + r] = t;
 }
+
+// columns per block of the sums: 8 (one 128-byte line of a row), fewer where there are fewer
+static inline int sum_width(int64_t s) { return s >= 8 ? 8 : s >= 4 ? 4 : s >= 2 ? 2 : 1; }
 
 static inline void group_sum(const c128* in, int64_t ch_stride, int64_t slot_stride, int slot0, int ns,
                              const int32_t* off, int n_groups, int64_t s, c128* out, hipStream_t st) {
-    dim3 grid((unsigned)(ns * n_groups), (unsigned)((s + 63) / 64));
-    hipLaunchKernelGGL(k_group_sum, grid, dim3(64 * CS_WAVES), 0, st, in, ch_stride, slot_stride, slot0, off,
-                       n_groups, s, out);
+    // 64 columns per block where the groups alone fill the chip: the loads of a wave
+    // are then whole rows (tile sums of 10^6 wires x 64 columns: 49 us, all of it HBM)
+    const int cw = s > 32 && (int64_t)ns * n_groups >= 128 ? 64 : sum_width(s);
+    const dim3 grid((unsigned)(ns * n_groups), (unsigned)((s + cw - 1) / cw));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(SUM_THREADS), 0, st, in, ch_stride, slot_stride, slot0, off, n_groups, s,
+                           out);
+    };
+    switch (cw) {
+        case 1: go(k_group_sum<1>); break;
+        case 2: go(k_group_sum<2>); break;
+        case 4: go(k_group_sum<4>); break;
+        case 8: go(k_group_sum<8>); break;
+        default: go(k_group_sum<64>); break;
+    }
 }
 
 // out[slot - slot0][cloud][r] = sum over the cloud's chunks of part[chunk][slot][r]
@@ -1012,12 +1047,22 @@ struct CgState {
     int32_t pad;
 };
 
-// alpha = rho / (p^T q)
-__global__ void k_cg_alpha(int64_t nsys, const c128* __restrict__ pq, CgState* __restrict__ cg) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nsys) return;
+// alpha = rho / (p^T q), with p^T q summed here over the groups of each cloud.
+// Also clears the count of systems above their checkpoint for the step that follows.
+//   The sum and the scalar update of the system it belongs to are one launch (as
+// are those of k_cg_step): one system's sums are all a system's update needs.
+template <int CW>
+__global__ __launch_bounds__(SUM_THREADS) void k_cg_alpha(const c128* __restrict__ gpart,
+                                                          const int32_t* __restrict__ cloud_group_off, int64_t s,
+                                                          CgState* __restrict__ cg, int32_t* __restrict__ n_active) {
+    __shared__ c128 red[SUM_THREADS];
+    const int cl = blockIdx.x;
+    const int64_t r = (int64_t)blockIdx.y * CW + threadIdx.x % CW;
+    const c128 d = block_sum<CW>(gpart, s, cloud_group_off[cl], cloud_group_off[cl + 1], r, r < s, red);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *n_active = 0;
+    if ((int)threadIdx.x >= CW || r >= s) return;
+    const int64_t t = (int64_t)cl * s + r;
     CgState S = cg[t];
-    const c128 d = pq[t];
     const double dd = d.re * d.re + d.im * d.im;
     if (S.done || !(dd > 0.0) || !isfinite(dd)) {
         S.alpha_re = S.alpha_im = 0.0;
@@ -1651,13 +1696,24 @@ __global__ __launch_bounds__(RB) void k_cg_pdir_z(const Chunk* __restrict__ chun
 // flags; beta for p = z + beta p.  mode 0: first step of a run (beta = 0);
 // mode 1: ordinary step; mode 2: step right after a residual replacement
 // (rho_prev is kept as the denominator).
-__global__ void k_cg_step(int64_t nsys, const c128* __restrict__ rz, const c128* __restrict__ rr, int mode,
-                          CgState* __restrict__ cg, int32_t* __restrict__ n_active, int32_t* __restrict__ flags) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nsys) return;
+// r^T z and ||r||^2 are summed here over each cloud's partial results: rz over the
+// product's groups or the update's chunks, rr over the chunks.
+template <int CW>
+__global__ __launch_bounds__(SUM_THREADS) void k_cg_step(const c128* __restrict__ rz, int64_t rz_stride,
+                                                         const int32_t* __restrict__ rz_off,
+                                                         const c128* __restrict__ rr, int64_t rr_stride,
+                                                         const int32_t* __restrict__ rr_off, int64_t s, int mode,
+                                                         CgState* __restrict__ cg, int32_t* __restrict__ n_active,
+                                                         int32_t* __restrict__ flags) {
+    __shared__ c128 red[SUM_THREADS];
+    const int cl = blockIdx.x;
+    const int64_t r = (int64_t)blockIdx.y * CW + threadIdx.x % CW;
+    const c128 rho_new = block_sum<CW>(rz, rz_stride, rz_off[cl], rz_off[cl + 1], r, r < s, red);
+    const c128 rr_new = block_sum<CW>(rr, rr_stride, rr_off[cl], rr_off[cl + 1], r, r < s, red);
+    if ((int)threadIdx.x >= CW || r >= s) return;
+    const int64_t t = (int64_t)cl * s + r;
     CgState S = cg[t];
-    const double rn = sqrt(fmax(rr[t].re, 0.0));
-    const c128 rho_new = rz[t];
+    const double rn = sqrt(fmax(rr_new.re, 0.0));
     if (!S.done) S.rnorm = rn;
     if (!S.done && (rn <= S.target || !isfinite(rn))) S.done = 1;
     const c128 den = (mode == 1) ? c128{S.rho, S.rho_im} : c128{S.rho_prev, S.rho_prev_im};
@@ -1685,8 +1741,10 @@ __global__ void k_cg_step(int64_t nsys, const c128* __restrict__ rz, const c128*
 
 // start of a cycle: targets, checkpoint, alpha = 0 (the update kernel then only forms z)
 __global__ void k_cg_cycle_start(int64_t nsys, const double* __restrict__ target, const double* __restrict__ ckpt,
-                                 const int32_t* __restrict__ active, int first, CgState* __restrict__ cg) {
+                                 const int32_t* __restrict__ active, int first, CgState* __restrict__ cg,
+                                 int32_t* __restrict__ n_active) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0) *n_active = 0;
     if (t >= nsys) return;
     CgState S = first ? CgState{} : cg[t];
     S.target = target[t];
@@ -2148,6 +2206,40 @@ static chaff_status cocg_narrow_shape(const Cloud* c, SolveShape& cs, SolveLayou
     return CHAFF_OK;
 }
 
+static void launch_cg_alpha(const SolveShape& sh, SolveLayout& L, hipStream_t st) {
+    const int cw = sum_width(sh.s);
+    const dim3 grid((unsigned)sh.n_clouds, (unsigned)((sh.s + cw - 1) / cw));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(SUM_THREADS), 0, st, (const c128*)L.gpart,
+                           (const int32_t*)L.cloud_group_off, sh.s, L.cg, L.counter);
+    };
+    switch (cw) {
+        case 1: go(k_cg_alpha<1>); break;
+        case 2: go(k_cg_alpha<2>); break;
+        case 4: go(k_cg_alpha<4>); break;
+        default: go(k_cg_alpha<8>); break;
+    }
+}
+// grouped: r^T z lies in the product's groups (neighbourhood inverse), otherwise in slot 0 of the chunks
+static void launch_cg_step(const SolveShape& sh, SolveLayout& L, bool grouped, int mode, hipStream_t st) {
+    const int cw = sum_width(sh.s);
+    const dim3 grid((unsigned)sh.n_clouds, (unsigned)((sh.s + cw - 1) / cw));
+    const int64_t ch = (int64_t)sh.nslot * sh.s;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(SUM_THREADS), 0, st, grouped ? (const c128*)L.gpart : (const c128*)L.part,
+                           grouped ? sh.s : ch,
+                           grouped ? (const int32_t*)L.cloud_group_off : (const int32_t*)L.cloud_chunk_off,
+                           (const c128*)(L.part + sh.s), ch, (const int32_t*)L.cloud_chunk_off, sh.s, mode, L.cg,
+                           L.counter, L.active);
+    };
+    switch (cw) {
+        case 1: go(k_cg_step<1>); break;
+        case 2: go(k_cg_step<2>); break;
+        case 4: go(k_cg_step<4>); break;
+        default: go(k_cg_step<8>); break;
+    }
+}
+
 // One COCG refinement cycle.  L.r holds the FP64 true residual; it replaces the
 // recursive residual (in units of the run's fixed per-system scale).  With
 // CHAFF_COCG the recurrence restarts from it; with CHAFF_COCG_RR the search
@@ -2186,7 +2278,7 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
     CHAFF_HIP(hipMemcpyAsync(L.h2, ckpt.data(), nsys * sizeof(double), hipMemcpyHostToDevice, st));
     CHAFF_HIP(hipMemcpyAsync(L.active, act.data(), nsys * sizeof(int32_t), hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_cg_cycle_start, dim3(blocks_for(nsys, 64)), dim3(64), 0, st, nsys, (const double*)L.target,
-                       (const double*)L.h2, (const int32_t*)L.active, first ? 1 : 0, L.cg);
+                       (const double*)L.h2, (const int32_t*)L.active, first ? 1 : 0, L.cg, L.counter);
     CHAFF_LAUNCH_CHECK();
     // With the neighbourhood inverse a fresh recurrence skips the passes that
     // only carry zeros: x_c, p and q are not cleared, the first step forms
@@ -2278,10 +2370,6 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
             CHAFF_LAUNCH_CHECK();
             group_sum(L.tpart, cs.s, 0, 0, 1, Lc.group_tile_off, cs.n_groups, cs.s, L.gpart, st);
             CHAFF_LAUNCH_CHECK();
-            group_sum(L.gpart, cs.s, 0, 0, 1, Lc.cloud_group_off, cs.n_clouds, cs.s, L.h1, st);   // r^T z
-            CHAFF_LAUNCH_CHECK();
-            chunk_sum((const c128*)L.part, (const int32_t*)L.cloud_chunk_off, cs.n_clouds, cs.nslot, 1, 1, cs.s,
-                      L.h1 + cs.nsys, st);   // ||r||^2
         } else if (clus) {   // r -= alpha q, z = M r (over q), r^T z, ||r||^2
             ProfScope pu(wst == 64 ? "k_cg_update" : "k_cg_update_narrow", st,
                          ProfWork{(4.0 * rows * cs.s) * sizeof(C) + (double)cluster_count(c) * CLR2 * sizeof(CZ),
@@ -2310,14 +2398,7 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
             }
         }
         CHAFF_LAUNCH_CHECK();
-        if (!nbhd)
-            chunk_sum((const c128*)L.part, (const int32_t*)L.cloud_chunk_off, cs.n_clouds, cs.nslot, 0, 2, cs.s,
-                      L.h1, st);
-        CHAFF_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_zero_bytes, dim3(1), dim3(64), 0, st, (uint32_t*)L.counter, (int64_t)1);
-        CHAFF_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_cg_step, dim3(blocks_for(cs.nsys, 64)), dim3(64), 0, st, cs.nsys, (const c128*)L.h1,
-                           (const c128*)(L.h1 + cs.nsys), mode, L.cg, L.counter, L.active);
+        launch_cg_step(cs, Lc, nbhd, mode, st);
         CHAFF_LAUNCH_CHECK();
         int32_t n_act = 0;
         CHAFF_HIP(hipMemcpyAsync(&n_act, L.counter, sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -2412,10 +2493,7 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
         // sigma: tiles -> groups -> clouds, fixed order
         group_sum(L.tpart, cs.s, 0, 0, 1, Lc.group_tile_off, cs.n_groups, cs.s, L.gpart, st);
         CHAFF_LAUNCH_CHECK();
-        group_sum(L.gpart, cs.s, 0, 0, 1, Lc.cloud_group_off, cs.n_clouds, cs.s, L.nrm, st);
-        CHAFF_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_cg_alpha, dim3(blocks_for(cs.nsys, 64)), dim3(64), 0, st, cs.nsys, (const c128*)L.nrm,
-                           L.cg);
+        launch_cg_alpha(cs, Lc, st);
         CHAFF_LAUNCH_CHECK();
     }
     // the deferred x update of the last step, then x64 += scale * xc (one pass)
