@@ -1140,7 +1140,7 @@ __global__ void k_gather_sys(const T* __restrict__ src, int n_clouds, int64_t s_
 // COCG product q = Z p.  A tile is four block rows of one cloud, one row per
 // wave; tiles are walked in XCD-aware order (XCD x takes tiles
 // [x T/8, (x+1) T/8) in Morton order, so the neighbour slabs a row gathers
-// stay in that XCD's L2).  Each wave stages the 7x7 blocks of its row in its
+// stay in that XCD's L2).  Each wave stages the blocks of its row in its
 // own LDS slot with one coalesced load, prefetched one block ahead so the
 // HBM latency of the Z stream overlaps the arithmetic; lane (group g, column
 // c) applies block columns k = g, g + G, ... (G = 64/S) to RHS column c, and
@@ -1149,18 +1149,14 @@ __global__ void k_gather_sys(const T* __restrict__ src, int n_clouds, int64_t s_
 // LDS when its diagonal block's slab is gathered (no second read of p, no
 // registers held across the loop).  Blocks are applied in ascending column
 // order: the rows in flight on an XCD then gather their neighbours' slabs in
-// step, and L2 serves them (10.2 GB fetched per C5 launch; starting each row
-// after its diagonal, so that the own slab came last, fetched 12.9 GB).  Two
-// fixed-order passes then sum tiles per group and groups per cloud.  The
-// gathers of p bound the kernel: complex64 tiles ask the compiler for at
-// least seven waves per SIMD (the 64-column three-product MFMA tile fits 66
-// registers; eight waves spill); complex128 tiles would spill under that
-// bound.  Gathering the next block's slab during the current block's MFMAs
-// measured no faster at C5 (it costs one wave per SIMD).
+// step, and L2 serves them (starting each row after its diagonal, so that the
+// own slab came last, fetched a quarter more).  Two fixed-order passes then sum
+// tiles per group and groups per cloud.  Complex64 blocks of 7 unknowns take
+// k_cocg_mfma instead.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int COCG_TILE_ROWS = RB / 64;
 template <typename CZ, typename C, int S>
-__global__ __launch_bounds__(RB) __attribute__((amdgpu_waves_per_eu(sizeof(C) == sizeof(c64) && NB == 7 ? 7 : 1)))
+__global__ __launch_bounds__(RB)
 void k_cocg_spmm(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles, int xcd_order,
                  const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const CZ* __restrict__ Z,
                  const C* __restrict__ P, C* __restrict__ Q, int64_t s, c128* __restrict__ tpart) {
@@ -1192,26 +1188,10 @@ void k_cocg_spmm(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles
     const int64_t r = ctile_l * S + c;
     const int64_t rc = r < s ? r : 0;
     c128 dot = {0, 0};
-    // complex64: the 7x7 block times the slab on the FP32 matrix cores
-    // (v_mfma_f32_4x4x1_16b_f32: 16 blocks of 4 lanes, lane l = RHS column
-    // l % S of depth group l / S; the 4 lanes of an MFMA block share their
-    // group, so each block forms its group's partial sums for 4 columns, and
-    // the groups are added by the cross-lane sums below.  Rows 0-3 and 4-7 of
-    // the block are two 4-row tiles, row 7 zero.  Three real products per
-    // complex one (Gauss's form): the sums a.re x.re, a.im x.im and
-    // (a.re + a.im)(x.re + x.im) are accumulated apart and combined at the
-    // end, so a depth step takes three MFMAs per tile instead of four; its
-    // rounding differs from the four-product form by a few units of the
-    // largest partial sum, within the FP32 accuracy the refinement corrects)
-    constexpr bool PMFMA = sizeof(C) == sizeof(c64) && sizeof(CZ) == sizeof(c64) && NB == 7;
-    static_assert(!PMFMA || S % 4 == 0, "an MFMA block of 4 lanes stays inside one depth group");
     if (i < tl.w1) {   // wave-uniform
         cplx<R> acc[NB];
 #pragma unroll
         for (int q = 0; q < NB; ++q) acc[q] = {0, 0};
-        f32x4_t mr[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        f32x4_t mi[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        f32x4_t ms[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         // blocks in ascending column order; the row's own p slab is stashed in
         // LDS when its diagonal block is gathered (each lane reads back only
         // what it wrote, so no barrier) for p^T q after the loop
@@ -1249,38 +1229,13 @@ void k_cocg_spmm(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if constexpr (PMFMA) {
 #pragma unroll
-                for (int kk = 0; kk < KK; ++kk) {
-                    const int k = g + kk * G;
-                    const float xs = (float)x[kk].re + (float)x[kk].im;
+            for (int kk = 0; kk < KK; ++kk) {
+                const int k = g + kk * G;
+                if (k < NB) {
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const int row = 4 * t + (lane & 3);
-                        const c64 a = (row < NB && k < NB) ? ccast<c64>(zs[w][buf][row * NB + k]) : c64{0.f, 0.f};
-                        // three real products per complex one: re = a.re x.re - a.im x.im,
-                        // im = (a.re + a.im)(x.re + x.im) - a.re x.re - a.im x.im
-                        mr[t] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.re, (float)x[kk].re, mr[t], 0, 0, 0);
-                        mi[t] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.im, (float)x[kk].im, mi[t], 0, 0, 0);
-                        ms[t] = __builtin_amdgcn_mfma_f32_4x4x1f32(a.re + a.im, xs, ms[t], 0, 0, 0);
-                    }
+                    for (int q = 0; q < NB; ++q) cfma(acc[q], ccast<cplx<R>>(zs[w][buf][q * NB + k]), x[kk]);
                 }
-            } else {
-#pragma unroll
-                for (int kk = 0; kk < KK; ++kk) {
-                    const int k = g + kk * G;
-                    if (k < NB) {
-#pragma unroll
-                        for (int q = 0; q < NB; ++q) cfma(acc[q], ccast<cplx<R>>(zs[w][buf][q * NB + k]), x[kk]);
-                    }
-                }
-            }
-        }
-        if constexpr (PMFMA) {
-#pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const float pr = mr[q >> 2][q & 3], pi = mi[q >> 2][q & 3], ps = ms[q >> 2][q & 3];
-                acc[q] = cplx<R>{(R)(pr - pi), (R)(ps - pr - pi)};
             }
         }
 #pragma unroll
@@ -1302,6 +1257,207 @@ void k_cocg_spmm(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles
     }
     // columns: lanes with equal c across waves and groups
     c128 v = block_col_reduce(dot, S, red);
+    if (threadIdx.x < S && r < s) tpart[t * s + r] = v;
+}
+
+// One complex64 7x7 block times the slab of a wave on the FP32 matrix cores
+// (v_mfma_f32_4x4x1_16b_f32: 16 blocks of 4 lanes).  Lane l holds RHS column
+// l % S of depth group l / S; the 4 lanes of an MFMA block share their group,
+// so each MFMA block forms its group's partial sums for 4 columns.  Rows 0-3
+// and 4-7 of the 7x7 block are two 4-row tiles, row 7 unused.  The block itself
+// lies in one register pair: the S lanes of a group hold S / 4 operands of four
+// rows, operand t S/8 + kk being rows 4 t.. of block column kk G + group
+// (G = 64 / S), and the matrix instruction's own block broadcast (2^CB MFMA
+// blocks take operand ABID of their group) hands each step its operand.
+// Three real products per complex one (Gauss's form): the sums a.re x.re,
+// a.im x.im and (a.re + a.im)(x.re + x.im) are accumulated apart and combined
+// at the end, so a depth step takes three MFMAs per tile instead of four; its
+// rounding differs from the four-product form by a few units of the largest
+// partial sum, within the FP32 accuracy the refinement corrects.
+template <int S, int KK, int kk>
+__device__ __forceinline__ void block_times_slab(float zr, float zi, float zs, const c64 (&x)[KK], f32x4_t (&mr)[2],
+                                                 f32x4_t (&mi)[2], f32x4_t (&ms)[2]) {
+    if constexpr (kk < KK) {
+        constexpr int CB = S == 64 ? 4 : S == 32 ? 3 : S == 16 ? 2 : 1, KB = S / 8;
+        const float xs = x[kk].re + x[kk].im;
+        mr[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(zr, x[kk].re, mr[0], CB, kk, 0);
+        mr[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(zr, x[kk].re, mr[1], CB, KB + kk, 0);
+        mi[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(zi, x[kk].im, mi[0], CB, kk, 0);
+        mi[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(zi, x[kk].im, mi[1], CB, KB + kk, 0);
+        ms[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(zs, xs, ms[0], CB, kk, 0);
+        ms[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(zs, xs, ms[1], CB, KB + kk, 0);
+        block_times_slab<S, KK, kk + 1>(zr, zi, zs, x, mr, mi, ms);
+    }
+}
+
+// entry at a 32-bit byte offset of a wave-uniform address: the base stays in scalar registers
+__device__ __forceinline__ c64 at_byte(const c64* base, uint32_t off) {
+    return *reinterpret_cast<const c64*>(reinterpret_cast<const char*>(base) + off);
+}
+
+// the same of memory that the launch reads only once: not kept in L2 before what is read again
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ c64 load_once(const c64* base, uint32_t off) {
+    const f32x2_t v = __builtin_nontemporal_load(
+        reinterpret_cast<const f32x2_t*>(reinterpret_cast<const char*>(base) + off));
+    return c64{v.x, v.y};
+}
+__device__ __forceinline__ void store_once(c64* p, c64 v) {
+    __builtin_nontemporal_store(f32x2_t{v.re, v.im}, reinterpret_cast<f32x2_t*>(p));
+}
+
+// Lanes with bit OFF clear return the sum of a over the two lanes that differ in
+// that bit, the others that of b.
+template <int OFF>
+__device__ __forceinline__ float swap_add(float a, float b) {
+    static_assert(OFF == 8 || OFF == 16 || OFF == 32, "row rotation or half-row exchange");
+    if constexpr (OFF == 8) {
+        const bool hi = (threadIdx.x & 8) != 0;
+        const float keep = hi ? b : a, send = hi ? a : b;
+        const int got = __builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xF, 0xF, false);   // row_ror:8
+        return keep + __int_as_float(got);
+    } else {
+        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+        u32x2_t v;
+        if constexpr (OFF == 16)
+            v = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        else
+            v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(v.x) + __uint_as_float(v.y);
+    }
+}
+
+// k_cocg_spmm for complex64 blocks of 7 unknowns, on the matrix cores.
+//   Bound: at 64 columns the gathers of p (the slabs of the rows in flight on an
+// XCD do not fit its L2: two launches of 32 columns each, on different XCDs,
+// halve them but read Z twice, 17% slower), so Z and q, which nothing of the
+// launch reads again, pass L2 by; at 8 the latency of the two loads per block.
+// With the blocks staged in LDS and read back entry by entry, a block cost 69
+// other vector, 53 scalar and 17 LDS instructions beside its 42 MFMAs.  10^6
+// rows of 8.9 blocks: 64 columns 3.81 -> 3.60 ms, 32 columns 2.55 -> 2.22; 10^5
+// rows of 6.3 blocks, 8 columns: 132 -> 110 us.  A next block's slab in flight
+// during the MFMAs costs a wave per SIMD and gained nothing at 64 columns.
+template <int S>
+__global__ __launch_bounds__(RB) __attribute__((amdgpu_waves_per_eu(6)))
+void k_cocg_mfma(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles, int xcd_order,
+                 const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const c64* __restrict__ Z,
+                 const c64* __restrict__ P, c64* __restrict__ Q, int64_t s, c128* __restrict__ tpart) {
+    static_assert(NB == 7 && S >= 8, "7 block columns over at most 8 depth groups");
+    constexpr int G = 64 / S;
+    constexpr int KK = (NB + G - 1) / G;
+    __shared__ c64 pown[COCG_TILE_ROWS][KK][64];
+    __shared__ c128 red[RB];
+    const int64_t id = blockIdx.x;
+    int64_t t, ctile_l;
+    if (xcd_order) {
+        const int xcd = (int)(id % NXCD);
+        const int64_t local = id / NXCD;
+        const int64_t per_xcd = (n_tiles + NXCD - 1) / NXCD;
+        t = (int64_t)xcd * per_xcd + local / col_tiles;
+        ctile_l = local % col_tiles;
+    } else {
+        t = id / col_tiles;
+        ctile_l = id % col_tiles;
+    }
+    if (t >= n_tiles) return;   // uniform over the block
+    const Chunk tl = tiles[t];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    const int g = lane / S, c = lane % S;
+    const int64_t i = tl.w0 + w;
+    const int64_t r = ctile_l * S + c;
+    c128 dot = {0, 0};
+    if (i < tl.w1) {   // wave-uniform
+        f32x4_t mr[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        f32x4_t mi[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        f32x4_t ms[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        // the lane's entry of a block: row 4 at + l % 4, column ak (row 7 and column 7: not in the block)
+        const int op = (lane % S) / 4, at = op / (S / 8), ak = g + (op % (S / 8)) * G, ar = 4 * at + (lane & 3);
+        const bool in = ar < NB && ak < NB;
+        const uint32_t zo = (uint32_t)((in ? ar * NB + ak : 0) * (int)sizeof(c64));
+        // the lane's entry of block row kk G + g of a slab
+        const uint32_t xo = (uint32_t)(((uint32_t)g * (uint32_t)s + (r < s ? c : 0)) * sizeof(c64));
+        const c64* Pt = P + ctile_l * S;
+        const int64_t e0 = row_ptr[i], e1 = row_ptr[i + 1];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) pown[w][kk][lane] = c64{0.f, 0.f};
+        for (int64_t eb = e0; eb < e1; eb += 64) {
+            const int m = (int)(e1 - eb < 64 ? e1 - eb : 64);
+            const int32_t cv = lane < m ? col_idx[eb + lane] : 0;   // the columns of the next 64 blocks
+            for (int j = 0; j < m; ++j) {
+                const int32_t ce = __builtin_amdgcn_readlane(cv, j);
+                const c64 z = load_once(Z + (eb + j) * NB2, zo);
+                c64 x[KK];
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    const c64* xb = Pt + ((int64_t)ce * NB + kk * G) * s;
+                    if ((kk + 1) * G <= NB)
+                        x[kk] = at_byte(xb, xo);
+                    else   // the last group's row 7 is no row of the slab
+                        x[kk] = g + kk * G < NB ? at_byte(xb, xo) : c64{0.f, 0.f};
+                }
+                if (ce == i) {   // wave-uniform: the diagonal block
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk) pown[w][kk][lane] = x[kk];
+                }
+                const float zr = in ? z.re : 0.f, zi = in ? z.im : 0.f;
+                block_times_slab<S, KK, 0>(zr, zi, zr + zi, x, mr, mi, ms);
+            }
+        }
+        float re[8], im[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float pr = mr[q >> 2][q & 3], pi = mi[q >> 2][q & 3], ps = ms[q >> 2][q & 3];
+            re[q] = pr - pi;
+            im[q] = ps - pr - pi;
+        }
+        // sum over the groups: each exchange leaves a lane with half of its rows, added over
+        // two groups (neighbouring groups first), so a lane ends with 8 / G complete rows from row0 on
+        int row0 = 0;
+        if constexpr (G >= 8) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                re[q] = swap_add<8>(re[q], re[q + 4]);
+                im[q] = swap_add<8>(im[q], im[q + 4]);
+            }
+        }
+        if constexpr (G >= 4) {
+            constexpr int H = G == 8 ? 2 : 4;
+#pragma unroll
+            for (int q = 0; q < H; ++q) {
+                re[q] = swap_add<16>(re[q], re[q + H]);
+                im[q] = swap_add<16>(im[q], im[q + H]);
+            }
+        }
+        if constexpr (G >= 2) {
+            constexpr int H = 8 / G;
+#pragma unroll
+            for (int q = 0; q < H; ++q) {
+                re[q] = swap_add<32>(re[q], re[q + H]);
+                im[q] = swap_add<32>(im[q], im[q + H]);
+            }
+        }
+        // bit b of the group number (lowest first) chose the upper half at the exchange over it
+        if constexpr (G == 8) row0 = 4 * (g & 1) + (g & 2) + (g >> 2);
+        if constexpr (G == 4) row0 = 4 * (g & 1) + (g & 2);
+        if constexpr (G == 2) row0 = 4 * g;
+        // the stash of the row's own slab is read by other lanes of the wave than wrote it
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (r < s) {
+#pragma unroll
+            for (int u = 0; u < 8 / G; ++u) {
+                const int q = row0 + u;
+                if (q >= NB) continue;
+                const c64 v = {re[u], im[u]};
+                store_once(Q + (i * NB + q) * s + r, v);
+                cfma(dot, ccast<c128>(pown[w][q / G][(q % G) * S + c]), ccast<c128>(v));
+            }
+        }
+    }
+    // columns: lanes with equal c across waves and groups
+    const c128 v = block_col_reduce(dot, S, red);
     if (threadIdx.x < S && r < s) tpart[t * s + r] = v;
 }
 
@@ -2103,9 +2259,14 @@ static void launch_cocg_spmm(const Cloud* c, const SolveShape& sh, SolveLayout& 
     const int ct = (int)((sh.s + ST - 1) / ST);
     const int64_t per_xcd = (sh.n_tiles + NXCD - 1) / NXCD;
     const int64_t nblk = sh.cocg_xcd ? per_xcd * NXCD * ct : sh.n_tiles * ct;
-    hipLaunchKernelGGL((k_cocg_spmm<CZ, C, ST>), dim3((unsigned)nblk), dim3(RB), 0, st,
-                       (const Chunk*)L.tiles, sh.n_tiles, ct, sh.cocg_xcd, (const int64_t*)c->row_ptr,
-                       (const int32_t*)c->col_idx, Z, p, q, sh.s, L.tpart);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(RB), 0, st, (const Chunk*)L.tiles, sh.n_tiles, ct,
+                           sh.cocg_xcd, (const int64_t*)c->row_ptr, (const int32_t*)c->col_idx, Z, p, q, sh.s, L.tpart);
+    };
+    if constexpr (sizeof(C) == sizeof(c64) && sizeof(CZ) == sizeof(c64) && NB == 7)
+        go(k_cocg_mfma<ST>);
+    else
+        go(k_cocg_spmm<CZ, C, ST>);
 }
 
 static chaff_status cocg_narrow_shape(const Cloud* c, SolveShape& cs, SolveLayout& Lc, const SolveLayout& L,
