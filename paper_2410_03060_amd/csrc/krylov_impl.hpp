@@ -1017,10 +1017,6 @@ __global__ void k_permute_rows(const c128* __restrict__ src, const int32_t* __re
     else dst[t] = src[(p * NB + q) * s + r];
 }
 
-__global__ void k_copy_c128(const c128* __restrict__ a, int64_t n, c128* __restrict__ b) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) b[t] = a[t];
-}
 __global__ void k_zero_bytes(uint32_t* __restrict__ a, int64_t nwords) {
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nwords;
          t += (int64_t)gridDim.x * blockDim.x)
@@ -1504,12 +1500,14 @@ __global__ __launch_bounds__(RB) void k_cocg_stream(const Chunk* __restrict__ ti
 
 // Search direction and deferred solution update, one pass per step:
 //   x += alpha p_old (the step whose residual update ran last; skipped with
-//   pend = 0 when that update was already applied), z = P_i r, p = z + beta p_old.
+//   pend = 0 when that update was already applied, x = alpha p_old with
+//   pend = 2, where x holds nothing yet), z = P_i r, p = z + beta p_old
+//   (p = z with pfirst, where p holds nothing yet).
 // z is recomputed here from r instead of being stored by the update kernel.
 template <typename CZ, typename C, int ST>
 __global__ __launch_bounds__(RB) void k_cg_pdir(const Chunk* __restrict__ chunks, const CgState* __restrict__ cg,
                                                 const CZ* __restrict__ Pinv, const C* __restrict__ rv,
-                                                C* __restrict__ p, C* __restrict__ x, int64_t s, int pend) {
+                                                C* __restrict__ p, C* __restrict__ x, int64_t s, int pend, int pfirst) {
     using R = typename real_of<C>::type;
     const Chunk ch = chunks[blockIdx.x];
     const int rsub = ST == 64 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x / ST);
@@ -1524,8 +1522,8 @@ __global__ __launch_bounds__(RB) void k_cg_pdir(const Chunk* __restrict__ chunks
         for (int k = 0; k < NB; ++k) {
             const int64_t o = (i * NB + k) * s + r;
             res[k] = rv[o];
-            pv[k] = p[o];
-            if (pend) xv[k] = x[o];
+            pv[k] = pfirst ? cplx<R>{0, 0} : p[o];
+            xv[k] = pend == 1 ? x[o] : cplx<R>{0, 0};
         }
         const CZ* pb = Pinv + i * NB2;
 #pragma unroll
@@ -1546,11 +1544,12 @@ __global__ __launch_bounds__(RB) void k_cg_pdir(const Chunk* __restrict__ chunks
 
 
 // r -= alpha q ; z = P_i r (not stored) ; partial r^T z and ||r||^2
+// first: the first step of a cycle (alpha = 0), where q holds nothing yet and r stays.
 template <typename CZ, typename C, int ST>
 __global__ __launch_bounds__(RB) void k_cg_update(const Chunk* __restrict__ chunks, const CgState* __restrict__ cg,
                                                   const CZ* __restrict__ Pinv, const C* __restrict__ q,
                                                   C* __restrict__ rv, int64_t s, c128* __restrict__ part, int nslot,
-                                                  int slot0) {
+                                                  int slot0, int first) {
     using R = typename real_of<C>::type;
     __shared__ c128 red[RB];
     const Chunk ch = chunks[blockIdx.x];
@@ -1566,12 +1565,14 @@ __global__ __launch_bounds__(RB) void k_cg_update(const Chunk* __restrict__ chun
             for (int k = 0; k < NB; ++k) {   // issue all loads before any arithmetic
                 const int64_t o = (i * NB + k) * s + r;
                 res[k] = rv[o];
-                qv[k] = q[o];
+                if (!first) qv[k] = q[o];
             }
+            if (!first) {
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                cfma(res[k], na, qv[k]);
-                rv[(i * NB + k) * s + r] = res[k];
+                for (int k = 0; k < NB; ++k) {
+                    cfma(res[k], na, qv[k]);
+                    rv[(i * NB + k) * s + r] = res[k];
+                }
             }
             const CZ* pb = Pinv + i * NB2;
 #pragma unroll
@@ -2203,18 +2204,18 @@ static chaff_status norms_to(const SolveShape& sh, SolveLayout& L, const C* v, c
 
 
 template <typename CZ, typename C, int ST>
-static void launch_cg_update(const SolveShape& sh, SolveLayout& L, const CZ* Pinv, const C* q, C* r,
+static void launch_cg_update(const SolveShape& sh, SolveLayout& L, const CZ* Pinv, const C* q, C* r, bool first,
                              hipStream_t st) {
     const dim3 grid(sh.n_chunks, (unsigned)((sh.s + ST - 1) / ST));
     hipLaunchKernelGGL((k_cg_update<CZ, C, ST>), grid, dim3(RB), 0, st, (const Chunk*)L.chunks, (const CgState*)L.cg,
-                       Pinv, q, r, sh.s, L.part, sh.nslot, 0);
+                       Pinv, q, r, sh.s, L.part, sh.nslot, 0, first ? 1 : 0);
 }
 template <typename CZ, typename C, int ST>
 static void launch_cg_pdir(const SolveShape& sh, SolveLayout& L, const CZ* Pinv, const C* r, C* p, C* x, int pend,
-                           hipStream_t st) {
+                           bool pfirst, hipStream_t st) {
     const dim3 grid(sh.n_chunks, (unsigned)((sh.s + ST - 1) / ST));
     hipLaunchKernelGGL((k_cg_pdir<CZ, C, ST>), grid, dim3(RB), 0, st, (const Chunk*)L.chunks, (const CgState*)L.cg,
-                       Pinv, r, p, x, sh.s, pend);
+                       Pinv, r, p, x, sh.s, pend, pfirst ? 1 : 0);
 }
 template <typename C, int ST>
 static void launch_cg_rupd(const SolveShape& sh, SolveLayout& L, const C* q, C* r, bool first, hipStream_t st) {
@@ -2441,11 +2442,15 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
     hipLaunchKernelGGL(k_cg_cycle_start, dim3(blocks_for(nsys, 64)), dim3(64), 0, st, nsys, (const double*)L.target,
                        (const double*)L.h2, (const int32_t*)L.active, first ? 1 : 0, L.cg, L.counter);
     CHAFF_LAUNCH_CHECK();
-    // With the neighbourhood inverse a fresh recurrence skips the passes that
-    // only carry zeros: x_c, p and q are not cleared, the first step forms
-    // ||r||^2 without the update r -= 0 q, sets p = z without reading p, and
-    // the first correction is written as alpha p rather than added to x_c.
-    const bool lazy = nbhd && !use_rr;   // (COCG_RR carries p and q into the next cycle)
+    // A fresh recurrence skips the passes that only carry zeros: x_c, p and q are
+    // not cleared, the first step forms its sums without the update r -= 0 q, sets
+    // p = z without reading p, and the first correction is written as alpha p
+    // rather than added to x_c.  13,278 coupled wires x 360 columns, block-diagonal,
+    // two cycles of 11 steps: an evaluation of 17.4 ms takes 16.0 (with the first
+    // residual of a zero start, which is the excitation, no longer copied and summed).
+    // (COCG_RR carries p and q into the next cycle; the cluster form of the update
+    // stores z over q and reads both, so it keeps the cleared vectors.)
+    const bool lazy = !clus && !use_rr;
     bool xc_valid = !lazy, p_valid = !lazy;
     // columns that hold a live system: with at most half a tile of them the
     // cycle starts compacted (the rule of the compaction inside the cycle)
@@ -2546,16 +2551,16 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
             }
         } else {   // r -= alpha q, r^T (P r), ||r||^2 (alpha = 0 on entry)
             ProfScope pu(wst == 64 ? "k_cg_update" : "k_cg_update_narrow", st,
-                         (3.0 * rows * cs.s) * sizeof(C) + (double)sh.n * NB2 * sizeof(CZ));
+                         ((first_step ? 1.0 : 3.0) * rows * cs.s) * sizeof(C) + (double)sh.n * NB2 * sizeof(CZ));
             const C* qc = q;
             switch (wst) {
-                case 1: launch_cg_update<CZ, C, 1>(cs, Lc, Pinv, qc, r, st); break;
-                case 2: launch_cg_update<CZ, C, 2>(cs, Lc, Pinv, qc, r, st); break;
-                case 4: launch_cg_update<CZ, C, 4>(cs, Lc, Pinv, qc, r, st); break;
-                case 8: launch_cg_update<CZ, C, 8>(cs, Lc, Pinv, qc, r, st); break;
-                case 16: launch_cg_update<CZ, C, 16>(cs, Lc, Pinv, qc, r, st); break;
-                case 32: launch_cg_update<CZ, C, 32>(cs, Lc, Pinv, qc, r, st); break;
-                default: launch_cg_update<CZ, C, 64>(cs, Lc, Pinv, qc, r, st); break;
+                case 1: launch_cg_update<CZ, C, 1>(cs, Lc, Pinv, qc, r, first_step, st); break;
+                case 2: launch_cg_update<CZ, C, 2>(cs, Lc, Pinv, qc, r, first_step, st); break;
+                case 4: launch_cg_update<CZ, C, 4>(cs, Lc, Pinv, qc, r, first_step, st); break;
+                case 8: launch_cg_update<CZ, C, 8>(cs, Lc, Pinv, qc, r, first_step, st); break;
+                case 16: launch_cg_update<CZ, C, 16>(cs, Lc, Pinv, qc, r, first_step, st); break;
+                case 32: launch_cg_update<CZ, C, 32>(cs, Lc, Pinv, qc, r, first_step, st); break;
+                default: launch_cg_update<CZ, C, 64>(cs, Lc, Pinv, qc, r, first_step, st); break;
             }
         }
         CHAFF_LAUNCH_CHECK();
@@ -2595,12 +2600,12 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
         }
         mode = 1;
         ++iters;
+        const bool pfirst = !p_valid;   // the first direction: p = z, nothing to add to x
+        const int pend = (pending_applied || pfirst) ? 0 : (xc_valid ? 1 : 2);
+        pending_applied = false;
+        p_valid = true;
+        if (pend == 2) xc_valid = true;
         if (zq) {   // x += alpha p_old (deferred), p = z + beta p_old
-            const bool pfirst = !p_valid;   // the first direction: p = z, nothing to add to x
-            const int pend = (pending_applied || pfirst) ? 0 : (xc_valid ? 1 : 2);
-            pending_applied = false;
-            p_valid = true;
-            if (pend == 2) xc_valid = true;
             ProfScope pp(spmm_tile_width(cs.s) == 64 ? "k_cg_p" : "k_cg_p_narrow", st,
                          (pfirst ? 2.0 : 3.0 + (pend == 2 ? 1.0 : 2.0 * pend)) * rows * cs.s * sizeof(C));
             const C* zc = q;
@@ -2614,20 +2619,19 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
                 default: launch_cg_pdir_z<C, 64>(cs, Lc, zc, p, xc, pend, pfirst, st); break;
             }
         } else {   // x += alpha p_old (deferred), p = P r + beta p_old
-            const int pend = pending_applied ? 0 : 1;
-            pending_applied = false;
             ProfScope pp(spmm_tile_width(cs.s) == 64 ? "k_cg_p" : "k_cg_p_narrow", st,
-                         (3.0 + 2.0 * pend) * rows * cs.s * sizeof(C) + (double)sh.n * NB2 * sizeof(CZ));
+                         (pfirst ? 2.0 : 3.0 + (pend == 2 ? 1.0 : 2.0 * pend)) * rows * cs.s * sizeof(C) +
+                             (double)sh.n * NB2 * sizeof(CZ));
             const int ws2 = spmm_tile_width(cs.s);
             const C* rc_ = r;
             switch (ws2) {
-                case 1: launch_cg_pdir<CZ, C, 1>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
-                case 2: launch_cg_pdir<CZ, C, 2>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
-                case 4: launch_cg_pdir<CZ, C, 4>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
-                case 8: launch_cg_pdir<CZ, C, 8>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
-                case 16: launch_cg_pdir<CZ, C, 16>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
-                case 32: launch_cg_pdir<CZ, C, 32>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
-                default: launch_cg_pdir<CZ, C, 64>(cs, Lc, Pinv, rc_, p, xc, pend, st); break;
+                case 1: launch_cg_pdir<CZ, C, 1>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
+                case 2: launch_cg_pdir<CZ, C, 2>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
+                case 4: launch_cg_pdir<CZ, C, 4>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
+                case 8: launch_cg_pdir<CZ, C, 8>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
+                case 16: launch_cg_pdir<CZ, C, 16>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
+                case 32: launch_cg_pdir<CZ, C, 32>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
+                default: launch_cg_pdir<CZ, C, 64>(cs, Lc, Pinv, rc_, p, xc, pend, pfirst, st); break;
             }
         }
         CHAFF_LAUNCH_CHECK();
@@ -2965,11 +2969,13 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
     bool converged = false, broken = false, rr_restart = false;
     std::vector<double> hinv(nsys), hrn(nsys), cocg_scale;
     std::vector<SysState> hsys(nsys);
+    c128* const r_buf = L.r;
     for (;;) {
-        // true residual r = b - Z x (FP64 accumulation over the stored Z)
-        if (cycles == 0 && o->use_x0 == 0) {
-            hipLaunchKernelGGL(k_copy_c128, dim3(blocks_for(vs)), dim3(256), 0, st, (const c128*)L.b, vs, L.r);
-            CHAFF_LAUNCH_CHECK();
+        // true residual r = b - Z x (FP64 accumulation over the stored Z); from zero it is b itself
+        const bool zero_start = cycles == 0 && o->use_x0 == 0;
+        L.r = zero_start ? L.b : r_buf;
+        if (zero_start) {
+            hr = hb;
         } else if (cycles == 0 && guess32) {   // x = x32 exactly: the FP32 slabs give the same residual
             sst = spmm_launch<CZ, c64, c128, 1, false>(c->row_ptr, c->col_idx, Z, (const c64*)x32, L.b, L.r, c->n,
                                                        c->nnzb, s, -1, st, "spmm_residual_fp64");
@@ -2979,10 +2985,12 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
                                                         "spmm_residual_fp64");
             if (sst != CHAFF_OK) return sst;
         }
-        sst = norms_to<c128>(sh, L, L.r, L.red, st);
-        if (sst != CHAFF_OK) return sst;
-        CHAFF_HIP(hipMemcpyAsync(hr.data(), L.red, nsys * sizeof(c128), hipMemcpyDeviceToHost, st));
-        CHAFF_HIP(hipStreamSynchronize(st));
+        if (!zero_start) {
+            sst = norms_to<c128>(sh, L, L.r, L.red, st);
+            if (sst != CHAFF_OK) return sst;
+            CHAFF_HIP(hipMemcpyAsync(hr.data(), L.red, nsys * sizeof(c128), hipMemcpyDeviceToHost, st));
+            CHAFF_HIP(hipStreamSynchronize(st));
+        }
         double worst = 0.0;
         int64_t active = 0;
         broken = false;
