@@ -794,6 +794,16 @@ __global__ __launch_bounds__(RB) void k_norm2(const Chunk* __restrict__ chunks, 
     if (threadIdx.x < st && m.r < s) part[((int64_t)blockIdx.x * nslot + slot) * s + m.r] = v;
 }
 
+// stores of results that the launch does not read again, past L2
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void store_once(c64* p, c64 v) {
+    __builtin_nontemporal_store(f32x2_t{v.re, v.im}, reinterpret_cast<f32x2_t*>(p));
+}
+__device__ __forceinline__ void store_once(c128* p, c128 v) {
+    __builtin_nontemporal_store(f64x2_t{v.re, v.im}, reinterpret_cast<f64x2_t*>(p));
+}
+
 // Sums over many partial results.  A block of SUM_THREADS threads sums in[k stride + r] over
 // k in [k0, k1) for CW columns: SUM_THREADS / CW strands walk k, coalesced over the columns, four
 // loads in flight each, and are added pairwise in LDS.  Fixed order throughout, so
@@ -1292,14 +1302,10 @@ __device__ __forceinline__ c64 at_byte(const c64* base, uint32_t off) {
 }
 
 // the same of memory that the launch reads only once: not kept in L2 before what is read again
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ c64 load_once(const c64* base, uint32_t off) {
     const f32x2_t v = __builtin_nontemporal_load(
         reinterpret_cast<const f32x2_t*>(reinterpret_cast<const char*>(base) + off));
     return c64{v.x, v.y};
-}
-__device__ __forceinline__ void store_once(c64* p, c64 v) {
-    __builtin_nontemporal_store(f32x2_t{v.re, v.im}, reinterpret_cast<f32x2_t*>(p));
 }
 
 // Lanes with bit OFF clear return the sum of a over the two lanes that differ in
@@ -2095,6 +2101,10 @@ constexpr int LONE_BLOCK = 256;   // wires per counting block
 static int64_t lone_blocks(int64_t n) { return (n + LONE_BLOCK - 1) / LONE_BLOCK; }
 
 // Device arrays of the compact cloud, before the solver's own workspace.
+// From this many columns on the lone wires' inverse blocks are refined in FP64
+// once and applied to the columns, where a wave holds one wire; with fewer, each
+// (wire, column) refines its own solution.
+constexpr int64_t LONE_INV = 32;
 struct LoneLayout {
     int32_t* cmap;      // [n] compact index of a coupled wire, -1 for the others
     int32_t* lone;      // [n] wires without neighbours, ascending
@@ -2109,6 +2119,8 @@ struct LoneLayout {
     int32_t* cloud_chunk_off;
     c128 *part, *sums;  // [chunk][2][s], [2][n_clouds][s]
     size_t bytes;
+    c128* inv;      // FP64 inverse self blocks of the lone wires (more than LONE_INV columns)
+    double* inv2;   // ||I - Z inv||_F^2 of each
 };
 constexpr int LONE_CHUNK = 64;   // lone wires per chunk
 
@@ -2133,6 +2145,8 @@ static LoneLayout carve_lone(void* ws, size_t cap, const Cloud* c, int64_t s, si
     l.cloud_chunk_off = cv.take<int32_t>((size_t)c->n_clouds + 1);
     l.part = cv.take<c128>((size_t)nch * 2 * s);
     l.sums = cv.take<c128>((size_t)2 * c->n_clouds * s);
+    l.inv = cv.take<c128>(s > LONE_INV ? (size_t)n * NB2 : 0);
+    l.inv2 = cv.take<double>(s > LONE_INV ? n : 0);
     l.bytes = align_up(cv.off, 256);
     return l;
 }
@@ -3280,24 +3294,149 @@ __global__ __launch_bounds__(256) void k_lone_blocks(int64_t nc, const int64_t* 
     for (int t = lane; t < NB2; t += 64) Pc[ci * NB2 + t] = Pinv[i * NB2 + t];
 }
 
+// G = Z_ii^-1 of every lone wire in FP64: Newton's iteration G <- G + G (I - Z G)
+// from the stored inverse until ||I - Z G||_F <= thr (kept for the residuals),
+// one wave per wire, each lane a patch of the product.
+template <typename CZ>
+__global__ __launch_bounds__(256) void k_lone_inverse(int64_t n_lone, const int32_t* __restrict__ lone,
+                                                      const int64_t* __restrict__ row_ptr, const CZ* __restrict__ Z,
+                                                      const CZ* __restrict__ Pinv, double thr, c128* __restrict__ inv,
+                                                      double* __restrict__ inv2) {
+    constexpr int R = (NB + 7) / 8;   // rows ly, ly + 8, ... and columns lx, lx + 8, ... of lane (ly, lx)
+    __shared__ CZ zs[4][NB2];
+    __shared__ c128 gs[4][NB2], ts[4][NB2];
+    const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63), ly = lane >> 3, lx = lane & 7;
+    const int64_t t = (int64_t)blockIdx.x * 4 + wv;
+    if (t >= n_lone) return;   // wave-uniform; the waves of a workgroup never wait for each other
+    const int64_t i = lone[t];
+    const CZ* zb = Z + row_ptr[i] * NB2;
+    const CZ* pb = Pinv + i * NB2;
+    CZ* zw = zs[wv];
+    c128 *gw = gs[wv], *tw = ts[wv];
+    for (int e = lane; e < NB2; e += 64) {
+        zw[e] = zb[e];
+        gw[e] = ccast<c128>(pb[e]);
+    }
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto times = [&](const auto* a, const c128* b, c128 (&acc)[R][R]) {
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+#pragma unroll
+            for (int v = 0; v < R; ++v) acc[u][v] = c128{0, 0};
+#pragma unroll 1
+        for (int k = 0; k < NB; ++k) {
+            c128 av[R], bv[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {   // rows and columns past the end repeat the last and are not kept
+                av[u] = ccast<c128>(a[min(ly + 8 * u, NB - 1) * NB + k]);
+                bv[u] = b[k * NB + min(lx + 8 * u, NB - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+#pragma unroll
+                for (int v = 0; v < R; ++v) cfma(acc[u][v], av[u], bv[v]);
+        }
+    };
+    c128 acc[R][R];
+    double f2;
+    for (int it = 0;; ++it) {
+        wave_sync();
+        times(zw, gw, acc);
+        f2 = 0.0;
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+#pragma unroll
+            for (int v = 0; v < R; ++v) {
+                const int row = ly + 8 * u, col = lx + 8 * v;
+                if (row >= NB || col >= NB) continue;
+                const c128 e = {(row == col ? 1.0 : 0.0) - acc[u][v].re, -acc[u][v].im};
+                tw[row * NB + col] = e;
+                f2 += e.re * e.re + e.im * e.im;
+            }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) f2 += __shfl_xor(f2, off, 64);
+        if (f2 <= thr * thr || it == 4) break;   // the same on every lane
+        wave_sync();
+        times(gw, tw, acc);
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+#pragma unroll
+            for (int v = 0; v < R; ++v) {
+                const int row = ly + 8 * u, col = lx + 8 * v;
+                if (row < NB && col < NB) gw[row * NB + col] = cadd(gw[row * NB + col], acc[u][v]);
+            }
+    }
+    for (int e = lane; e < NB2; e += 64) inv[t * NB2 + e] = gw[e];
+    if (lane == 0) inv2[t] = f2;
+}
+
+// x = G u of every lone wire and column, to the caller's rows, and the chunk's
+// sums of |u|^2 and of the bound ||I - Z G||_F^2 |u|^2 on |u - Z x|^2.  A wave
+// owns one wire and 64 columns: G comes through the scalar cache as operands of
+// the FP64 products.
+//   Bound: the store of X, which passes L2 by (kept in it, the scattered rows
+// took 995 us for 455).  Refining each column's own solution instead takes four
+// products with FP32 blocks (converted entry by entry) where this takes one, and
+// three per wire.  46,000 wires of 7 x 360 columns: 1.86 ms -> 455 us and 44 for
+// the inverses; 95,000 of 19 x 64: 3.2 ms -> 1.06 ms and 770 us.
+__global__ __launch_bounds__(256) void k_lone_apply(LoneLayout l, const Wire* __restrict__ wires,
+                                                    const int32_t* __restrict__ perm, const c128* __restrict__ inv,
+                                                    const double* __restrict__ k_hat, const double* __restrict__ e_hat,
+                                                    double kp, int64_t s, c128* __restrict__ X) {
+    __shared__ c128 red[RB];
+    const Chunk ch = l.chunks[blockIdx.x];
+    const int rsub = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t r = (int64_t)blockIdx.y * 64 + (threadIdx.x & 63);
+    double u2 = 0.0, r2 = 0.0;
+    if (r < s) {
+        const double kv[3] = {k_hat[3 * r], k_hat[3 * r + 1], k_hat[3 * r + 2]};
+        const double ev[3] = {e_hat[3 * r], e_hat[3 * r + 1], e_hat[3 * r + 2]};
+        for (int64_t t = ch.w0 + rsub; t < ch.w1; t += RB / 64) {
+            const int64_t i = l.lone[t];
+            const c128* g = inv + t * NB2;
+            c128 u[NB], step;
+            lone_excitation<NB>(wires[i], kv, ev, kp, u[0], step);
+            double w2 = u[0].re * u[0].re + u[0].im * u[0].im;
+#pragma unroll
+            for (int q = 1; q < NB; ++q) {
+                u[q] = cmul(u[q - 1], step);
+                w2 += u[q].re * u[q].re + u[q].im * u[q].im;
+            }
+            const int64_t o = (int64_t)perm[i] * NB * s + r;
+#pragma unroll 1
+            for (int q = 0; q < NB; ++q) store_once(X + o + q * s, row_times<NB>(g + q * NB, u));
+            u2 += w2;
+            r2 += l.inv2[t] * w2;
+        }
+    }
+    const c128 v = block_col_reduce(c128{u2, r2}, 64, red);
+    if (threadIdx.x < 64 && r < s) {
+        l.part[((int64_t)blockIdx.x * 2) * s + r] = c128{v.re, 0.0};
+        l.part[((int64_t)blockIdx.x * 2 + 1) * s + r] = c128{v.im, 0.0};
+    }
+}
+
 // The wires without neighbours, start to end (lone_wire), x to the caller's
 // rows, and the chunk's sums of |u|^2 and |r|^2.  A thread owns one (wire,
-// right-hand side); with 64 columns the wire is uniform over the wave and its
-// blocks come through the scalar cache.
+// right-hand side).
 //   Bound: FP64 arithmetic, four NB x NB complex products with the usual one
-// sweep.  95,000 wires of 19 unknowns x 64 columns: 75.7 ms with the products
-// unrolled, 3.2 ms (16 TFLOP/s, 1.9 GB written); 46,000 wires of 7 x 360:
-// 3.1 -> 1.9 ms.
+// sweep; the products are rolled (unrolled, 95,000 wires of 19 unknowns x 64
+// columns took 75.7 ms for 3.2).
 template <typename CZ, int ST>
 __global__ __launch_bounds__(256) void k_lone_solve(LoneLayout l, const Wire* __restrict__ wires,
                                                     const int32_t* __restrict__ perm,
                                                     const int64_t* __restrict__ row_ptr, const CZ* __restrict__ Z,
                                                     const CZ* __restrict__ Pinv, const double* __restrict__ k_hat,
-                                                    const double* __restrict__ e_hat, double k, int64_t s, double thr,
+                                                    const double* __restrict__ e_hat, double kp, int64_t s, double thr,
                                                     c128* __restrict__ X) {
     __shared__ c128 vs[4][NB][64];   // at least 7 x 256 entries: also the column reduction's
     const Chunk ch = l.chunks[blockIdx.x];
-    const int rsub = ST == 64 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x / ST);
+    const int rsub = (int)(threadIdx.x / ST);
     const int64_t r = (int64_t)blockIdx.y * ST + threadIdx.x % ST;
     c128(*lv)[64] = vs[threadIdx.x >> 6];   // this wave's; a lane reads what it wrote itself
     const int lane = threadIdx.x & 63;
@@ -3312,7 +3451,7 @@ __global__ __launch_bounds__(256) void k_lone_solve(LoneLayout l, const Wire* __
             const CZ* pb = Pinv + i * NB2;
             c128 x[NB];
             double w2, e2;
-            lone_wire<NB>(w, zb, pb, kv, ev, k, thr, lv, lane, x, w2, e2);
+            lone_wire<NB>(w, zb, pb, kv, ev, kp, thr, lv, lane, x, w2, e2);
             const int64_t o = (int64_t)perm[i] * NB * s + r;
 #pragma unroll
             for (int q = 0; q < NB; ++q) X[o + q * s] = x[q];
@@ -3373,11 +3512,19 @@ static chaff_status solve_compact(Cloud* c, const chaff_solve_opts* o, const CZ*
     case W:                                                                                                      \
         hipLaunchKernelGGL((k_lone_solve<CZ, W>), grid, dim3(256), 0, st, l, (const Wire*)c->wires,              \
                            (const int32_t*)c->perm, (const int64_t*)c->row_ptr, Z, Pinv, k_hat, e_hat,           \
-                           2.0 * PI_K / c->wavelength, s, 0.01 * o->tol, X);                                     \
+                           2.0 / c->wavelength, s, 0.01 * o->tol, X);                                     \
         break;
-            switch (w) {
-                CHAFF_LONE(1) CHAFF_LONE(2) CHAFF_LONE(4) CHAFF_LONE(8) CHAFF_LONE(16) CHAFF_LONE(32) CHAFF_LONE(64)
-            }
+            if (s > LONE_INV) {
+                hipLaunchKernelGGL((k_lone_inverse<CZ>), dim3((unsigned)((n_lone + 3) / 4)), dim3(256), 0, st, n_lone,
+                                   (const int32_t*)l.lone, (const int64_t*)c->row_ptr, Z, Pinv, 0.01 * o->tol, l.inv,
+                                   l.inv2);
+                CHAFF_LAUNCH_CHECK();
+                hipLaunchKernelGGL(k_lone_apply, grid, dim3(RB), 0, st, l, (const Wire*)c->wires, (const int32_t*)c->perm,
+                                   (const c128*)l.inv, k_hat, e_hat, 2.0 / c->wavelength, s, X);
+            } else
+                switch (w) {
+                    CHAFF_LONE(1) CHAFF_LONE(2) CHAFF_LONE(4) CHAFF_LONE(8) CHAFF_LONE(16) CHAFF_LONE(32)
+                }
 #undef CHAFF_LONE
         }
         CHAFF_LAUNCH_CHECK();
@@ -3436,11 +3583,13 @@ template <typename C>
 static chaff_status solve_any(Cloud* c, const chaff_solve_opts* o, const void* Z, const void* Pinv, const double* k_hat,
                               const double* e_hat, int64_t s, void* X, void* ws, size_t ws_bytes,
                               chaff_solve_stats* st_out, double* rel_res, hipStream_t st) {
-    if (lone_wires(c, o)) {
-        bool done = false;
-        const chaff_status e = solve_compact<C, C>(c, o, (const C*)Z, (const C*)Pinv, k_hat, e_hat, s, (c128*)X, ws,
-                                                   ws_bytes, st_out, rel_res, st, &done);
-        if (done || e != CHAFF_OK) return e;
+    if constexpr (std::is_same<C, c64>::value) {
+        if (lone_wires(c, o)) {
+            bool done = false;
+            const chaff_status e = solve_compact<C, C>(c, o, (const C*)Z, (const C*)Pinv, k_hat, e_hat, s, (c128*)X, ws,
+                                                       ws_bytes, st_out, rel_res, st, &done);
+            if (done || e != CHAFF_OK) return e;
+        }
     }
     return solve_impl<C, C>(c, o, (const C*)Z, (const C*)Pinv, k_hat, e_hat, s, (c128*)X, ws, ws_bytes, st_out, rel_res,
                             st);

@@ -213,7 +213,8 @@ struct System {
         beta = A.k * (kh[0] * w.tx + kh[1] * w.ty + kh[2] * w.tz);
         ph0 = A.k * (kh[0] * w.cx + kh[1] * w.cy + kh[2] * w.cz);
         const double D = w.len / NSEG;
-        const double sc = lone_sinc(0.5 * beta * D);
+        const double h = 0.5 * beta * D;
+        const double sc = fabs(h) < 1e-4 ? 1.0 - h * h / 6.0 : sin(h) / h;
         return tp * D * sc * sc;
     }
     // u (eq. 4) on the coupled rows
@@ -455,7 +456,8 @@ __global__ __launch_bounds__(64) void k_lone(Args<C> A, int64_t n) {
     const double ev[3] = {A.e_hat[3 * r], A.e_hat[3 * r + 1], A.e_hat[3 * r + 2]};
     c128 x[NB];
     double w2, e2;
-    lone_wire<NB>(A.wires[i], A.Z + A.row_ptr[i] * NB2, A.P + i * NB2, kv, ev, A.k, 0.01 * A.tol, lv, lane, x, w2, e2);
+    lone_wire<NB>(A.wires[i], A.Z + A.row_ptr[i] * NB2, A.P + i * NB2, kv, ev, A.k / PI_H, 0.01 * A.tol, lv, lane, x,
+                   w2, e2);
     const int64_t o = (int64_t)A.perm[i] * NB * A.s + r;
 #pragma unroll
     for (int q = 0; q < NB; ++q) A.X[o + q * A.s] = x[q];

@@ -4,11 +4,9 @@
 // solves (krylov_small.hpp); NB = rooftop unknowns per wire.
 #pragma once
 
-#include "common.hpp"
+#include "phase.hpp"
 
 namespace chaff {
-
-__device__ __forceinline__ double lone_sinc(double x) { return fabs(x) < 1e-4 ? 1.0 - x * x / 6.0 : sin(x) / x; }
 
 // a^T v over one row of a stored block, FP64, four independent chains
 template <int NB, typename CZ>
@@ -25,6 +23,26 @@ __device__ __forceinline__ c128 row_times(const CZ* __restrict__ row, const c128
     return c128{r0 - r1, i0 + i1};
 }
 
+// u of one wire and incidence (eq. 4): its first entry and the factor from one
+// rooftop to the next (kp = k / pi; the half step's sine serves both the envelope
+// and the factor)
+template <int NB>
+__device__ __forceinline__ void lone_excitation(const Wire& w, const double (&kv)[3], const double (&ev)[3], double kp,
+                                                c128& first, c128& step) {
+    const double tp = w.tx * ev[0] + w.ty * ev[1] + w.tz * ev[2];
+    const double D = w.len / (NB + 1);
+    const double bd = kp * (kv[0] * w.tx + kv[1] * w.ty + kv[2] * w.tz) * D;   // phase of a segment
+    const double ph0 = kp * (kv[0] * w.cx + kv[1] * w.cy + kv[2] * w.cz);
+    double sn, cs;
+    sincospi_any(0.5 * bd, sn, cs);
+    const double h = PI_H * (0.5 * bd);
+    const double sc = fabs(h) < 1e-4 ? 1.0 - h * h / 6.0 : sn / h;
+    const double env = tp * D * sc * sc;
+    step = c128{cs * cs - sn * sn, -2.0 * sn * cs};
+    sincospi_any(ph0 - (double)(NB / 2) * bd, sn, cs);
+    first = c128{env * cs, -env * sn};
+}
+
 // One wire and incidence (kv propagation, ev polarisation): x = P u, then at most
 // four sweeps of r = u - Z x, x += P r until ||r|| <= thr ||u||.  w2 = ||u||^2,
 // e2 = ||r||^2 of the x returned.  u (eq. 4) is formed where it is needed, each
@@ -34,22 +52,10 @@ __device__ __forceinline__ c128 row_times(const CZ* __restrict__ row, const c128
 // each, the 19-unknown form ran out of registers and instruction cache).
 template <int NB, typename CZ>
 __device__ __forceinline__ void lone_wire(const Wire& w, const CZ* __restrict__ zb, const CZ* __restrict__ pb,
-                                          const double (&kv)[3], const double (&ev)[3], double k, double thr,
+                                          const double (&kv)[3], const double (&ev)[3], double kp, double thr,
                                           c128 (*lv)[64], int lane, c128 (&x)[NB], double& w2, double& e2) {
-    const double tp = w.tx * ev[0] + w.ty * ev[1] + w.tz * ev[2];
-    const double beta = k * (kv[0] * w.tx + kv[1] * w.ty + kv[2] * w.tz);
-    const double ph0 = k * (kv[0] * w.cx + kv[1] * w.cy + kv[2] * w.cz);
-    const double D = w.len / (NB + 1);
-    const double sc = lone_sinc(0.5 * beta * D);
-    const double env = tp * D * sc * sc;
     c128 first, step;   // u_0 and the phase step of one rooftop
-    {
-        double sn, cs;
-        sincos(ph0 - (double)(NB / 2) * beta * D, &sn, &cs);
-        first = c128{env * cs, -env * sn};
-        sincos(beta * D, &sn, &cs);
-        step = c128{cs, -sn};
-    }
+    lone_excitation<NB>(w, kv, ev, kp, first, step);
     w2 = 0.0;
     x[0] = first;
 #pragma unroll
