@@ -795,8 +795,8 @@ __global__ __launch_bounds__(RB) void k_norm2(const Chunk* __restrict__ chunks, 
 }
 
 // stores of results that the launch does not read again, past L2
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef double f64x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef double f64x2_t __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ void store_once(c64* p, c64 v) {
     __builtin_nontemporal_store(f32x2_t{v.re, v.im}, reinterpret_cast<f32x2_t*>(p));
 }
@@ -1964,9 +1964,13 @@ struct SolveLayout {
 // Wires per reduction chunk (about 2048 chunks in total): streaming kernels
 // reduce per chunk; COCG's product uses its own small tiles (see k_cocg_spmm).
 // Wires per solver chunk: a multiple of the cluster width, so that chunks
-// starting at a cloud's first wire never split a cluster.
-static int64_t chunk_wires(int64_t n, int /*method*/) {
-    return (int64_t)align_up((size_t)std::max<int64_t>(32, (n + 2047) / 2048), CLW);
+// starting at a cloud's first wire never split a cluster.  COCG's passes take
+// short chunks where there are few wires (its sums have 128 strands per column):
+// 5,000 coupled wires of 19 unknowns x 64 columns are 156 blocks of 32 wires for
+// 256 CUs; of 8, the update takes 46 us for 119 and the direction 44 for 81.
+static int64_t chunk_wires(int64_t n, int method) {
+    const int64_t least = method == CHAFF_COCG ? 8 : 32;
+    return (int64_t)align_up((size_t)std::max<int64_t>(least, (n + 2047) / 2048), CLW);
 }
 constexpr int TILE_GROUP = 256;   // tiles per first-stage group of the sigma reduction
 
@@ -2161,7 +2165,7 @@ static size_t compact_solve_bytes(const Cloud* c, const chaff_solve_opts* o, int
     SolveShape sh = solve_shape(&cc, o->restart, s, (chaff_prec)o->prec, o->method);
     sh.n_clouds = c->n_clouds;
     sh.nsys = (int64_t)c->n_clouds * s;
-    sh.n_chunks = (int)std::min<int64_t>((nc + 31) / 32, 2048) + c->n_clouds;   // chunk_wires: at least 32 wires, 2048 chunks
+    sh.n_chunks = (int)std::min<int64_t>((nc + 7) / 8, 2048) + c->n_clouds;   // chunk_wires: at least 8 wires, 2048 chunks
     if (sh.n_tiles > 0) {
         sh.n_tiles += c->n_clouds;
         sh.n_groups = (int)(sh.n_tiles / TILE_GROUP) + c->n_clouds + 1;
