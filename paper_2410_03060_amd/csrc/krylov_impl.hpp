@@ -16,6 +16,7 @@
 // reduced per cloud over fixed row chunks in a fixed order (deterministic).
 #include "common.hpp"
 #include "lone.hpp"
+#include "step_flag.hpp"
 #include "precond.hpp"
 #include "prof.hpp"
 #include "tune.hpp"
@@ -1054,18 +1055,16 @@ struct CgState {
 };
 
 // alpha = rho / (p^T q), with p^T q summed here over the groups of each cloud.
-// Also clears the count of systems above their checkpoint for the step that follows.
 //   The sum and the scalar update of the system it belongs to are one launch (as
 // are those of k_cg_step): one system's sums are all a system's update needs.
 template <int CW>
 __global__ __launch_bounds__(SUM_THREADS) void k_cg_alpha(const c128* __restrict__ gpart,
                                                           const int32_t* __restrict__ cloud_group_off, int64_t s,
-                                                          CgState* __restrict__ cg, int32_t* __restrict__ n_active) {
+                                                          CgState* __restrict__ cg) {
     __shared__ c128 red[SUM_THREADS];
     const int cl = blockIdx.x;
     const int64_t r = (int64_t)blockIdx.y * CW + threadIdx.x % CW;
     const c128 d = block_sum<CW>(gpart, s, cloud_group_off[cl], cloud_group_off[cl + 1], r, r < s, red);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *n_active = 0;
     if ((int)threadIdx.x >= CW || r >= s) return;
     const int64_t t = (int64_t)cl * s + r;
     CgState S = cg[t];
@@ -1867,39 +1866,51 @@ __global__ __launch_bounds__(SUM_THREADS) void k_cg_step(const c128* __restrict_
                                                          const c128* __restrict__ rr, int64_t rr_stride,
                                                          const int32_t* __restrict__ rr_off, int64_t s, int mode,
                                                          CgState* __restrict__ cg, int32_t* __restrict__ n_active,
-                                                         int32_t* __restrict__ flags) {
+                                                         int32_t* __restrict__ flags, uint64_t* __restrict__ host,
+                                                         uint32_t seq) {
     __shared__ c128 red[SUM_THREADS];
     const int cl = blockIdx.x;
     const int64_t r = (int64_t)blockIdx.y * CW + threadIdx.x % CW;
     const c128 rho_new = block_sum<CW>(rz, rz_stride, rz_off[cl], rz_off[cl + 1], r, r < s, red);
     const c128 rr_new = block_sum<CW>(rr, rr_stride, rr_off[cl], rr_off[cl + 1], r, r < s, red);
-    if ((int)threadIdx.x >= CW || r >= s) return;
-    const int64_t t = (int64_t)cl * s + r;
-    CgState S = cg[t];
-    const double rn = sqrt(fmax(rr_new.re, 0.0));
-    if (!S.done) S.rnorm = rn;
-    if (!S.done && (rn <= S.target || !isfinite(rn))) S.done = 1;
-    const c128 den = (mode == 1) ? c128{S.rho, S.rho_im} : c128{S.rho_prev, S.rho_prev_im};
-    const double dd = den.re * den.re + den.im * den.im;
-    if (S.done) {   // alpha stays: the deferred x update of this step is still to be applied
-        S.beta_re = S.beta_im = 0.0;
-    } else if (mode == 0 || !(dd > 0.0)) {
-        S.beta_re = S.beta_im = 0.0;
-    } else {
-        const c128 b = cmul(rho_new, c128{den.re / dd, -den.im / dd});
-        S.beta_re = b.re;
-        S.beta_im = b.im;
+    int above = 0;
+    if ((int)threadIdx.x < CW && r < s) {
+        const int64_t t = (int64_t)cl * s + r;
+        CgState S = cg[t];
+        const double rn = sqrt(fmax(rr_new.re, 0.0));
+        if (!S.done) S.rnorm = rn;
+        if (!S.done && (rn <= S.target || !isfinite(rn))) S.done = 1;
+        const c128 den = (mode == 1) ? c128{S.rho, S.rho_im} : c128{S.rho_prev, S.rho_prev_im};
+        const double dd = den.re * den.re + den.im * den.im;
+        if (S.done) {   // alpha stays: the deferred x update of this step is still to be applied
+            S.beta_re = S.beta_im = 0.0;
+        } else if (mode == 0 || !(dd > 0.0)) {
+            S.beta_re = S.beta_im = 0.0;
+        } else {
+            const c128 b = cmul(rho_new, c128{den.re / dd, -den.im / dd});
+            S.beta_re = b.re;
+            S.beta_im = b.im;
+        }
+        if (mode == 1) {
+            S.rho_prev = S.rho;
+            S.rho_prev_im = S.rho_im;
+        }
+        S.rho = rho_new.re;
+        S.rho_im = rho_new.im;
+        cg[t] = S;
+        above = (!S.done && rn > S.ckpt) ? 1 : 0;
+        flags[t] = above;
     }
-    if (mode == 1) {
-        S.rho_prev = S.rho;
-        S.rho_prev_im = S.rho_im;
-    }
-    S.rho = rho_new.re;
-    S.rho_im = rho_new.im;
-    cg[t] = S;
-    const int above = (!S.done && rn > S.ckpt) ? 1 : 0;
-    flags[t] = above;
-    if (above) atomicAdd(n_active, 1);
+    // tickets and counts in one word: the last block to add its own holds the total
+    const int here = __syncthreads_count(above);
+    if (threadIdx.x != 0) return;
+    unsigned long long* tally = reinterpret_cast<unsigned long long*>(n_active + 2);
+    const unsigned long long old = atomicAdd(tally, 1ull << 32 | (unsigned)here);
+    if ((uint32_t)(old >> 32) != gridDim.x * gridDim.y - 1) return;
+    const uint32_t n = (uint32_t)old + (uint32_t)here;
+    *tally = 0;
+    *n_active = (int32_t)n;
+    if (host) __hip_atomic_store(host, (uint64_t)seq << 32 | n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // start of a cycle: targets, checkpoint, alpha = 0 (the update kernel then only forms z)
@@ -1907,7 +1918,7 @@ __global__ void k_cg_cycle_start(int64_t nsys, const double* __restrict__ target
                                  const int32_t* __restrict__ active, int first, CgState* __restrict__ cg,
                                  int32_t* __restrict__ n_active) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0) *n_active = 0;
+    if (t < 4) n_active[t] = 0;   // the count and k_cg_step's tally
     if (t >= nsys) return;
     CgState S = first ? CgState{} : cg[t];
     S.target = target[t];
@@ -2391,7 +2402,7 @@ static void launch_cg_alpha(const SolveShape& sh, SolveLayout& L, hipStream_t st
     const dim3 grid((unsigned)sh.n_clouds, (unsigned)((sh.s + cw - 1) / cw));
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(SUM_THREADS), 0, st, (const c128*)L.gpart,
-                           (const int32_t*)L.cloud_group_off, sh.s, L.cg, L.counter);
+                           (const int32_t*)L.cloud_group_off, sh.s, L.cg);
     };
     switch (cw) {
         case 1: go(k_cg_alpha<1>); break;
@@ -2401,7 +2412,8 @@ static void launch_cg_alpha(const SolveShape& sh, SolveLayout& L, hipStream_t st
     }
 }
 // grouped: r^T z lies in the product's groups (neighbourhood inverse), otherwise in slot 0 of the chunks
-static void launch_cg_step(const SolveShape& sh, SolveLayout& L, bool grouped, int mode, hipStream_t st) {
+static void launch_cg_step(const SolveShape& sh, SolveLayout& L, bool grouped, int mode, uint64_t* host, uint32_t seq,
+                           hipStream_t st) {
     const int cw = sum_width(sh.s);
     const dim3 grid((unsigned)sh.n_clouds, (unsigned)((sh.s + cw - 1) / cw));
     const int64_t ch = (int64_t)sh.nslot * sh.s;
@@ -2410,7 +2422,7 @@ static void launch_cg_step(const SolveShape& sh, SolveLayout& L, bool grouped, i
                            grouped ? sh.s : ch,
                            grouped ? (const int32_t*)L.cloud_group_off : (const int32_t*)L.cloud_chunk_off,
                            (const c128*)(L.part + sh.s), ch, (const int32_t*)L.cloud_chunk_off, sh.s, mode, L.cg,
-                           L.counter, L.active);
+                           L.counter, L.active, host, seq);
     };
     switch (cw) {
         case 1: go(k_cg_step<1>); break;
@@ -2431,7 +2443,7 @@ template <typename C, typename CZ>
 static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveShape& sh, SolveLayout& L,
                                const CZ* Z, const CZ* Pinv, const std::vector<double>& target,
                                const std::vector<double>& ckpt, const std::vector<int32_t>& act, bool first,
-                               int& iters, bool& capped, hipStream_t st) {
+                               int& iters, bool& capped, StepFlag& flag, hipStream_t st) {
     capped = false;
     const int64_t rows = sh.rows, s = sh.s, vs = rows * s, nsys = sh.nsys;
     C* V = static_cast<C*>(L.V);   // [x_c | r | p | q], each with room for [rows][s]
@@ -2582,11 +2594,11 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
             }
         }
         CHAFF_LAUNCH_CHECK();
-        launch_cg_step(cs, Lc, nbhd, mode, st);
+        launch_cg_step(cs, Lc, nbhd, mode, flag.p, ++flag.seq, st);
         CHAFF_LAUNCH_CHECK();
         int32_t n_act = 0;
-        CHAFF_HIP(hipMemcpyAsync(&n_act, L.counter, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        CHAFF_HIP(hipStreamSynchronize(st));
+        const chaff_status fst = flag.wait(L.counter, n_act, st);
+        if (fst != CHAFF_OK) return fst;
         if (g_verbose && k % 50 == 0)
             std::fprintf(stderr, "[chaff] cocg step %d: %d of %lld systems above their checkpoint (%lld columns)\n",
                          k, n_act, (long long)cs.nsys, (long long)cs.s);
@@ -2988,6 +3000,7 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
     std::vector<double> hinv(nsys), hrn(nsys), cocg_scale;
     std::vector<SysState> hsys(nsys);
     c128* const r_buf = L.r;
+    StepFlag flag;
     for (;;) {
         // true residual r = b - Z x (FP64 accumulation over the stored Z); from zero it is b itself
         const bool zero_start = cycles == 0 && o->use_x0 == 0;
@@ -3063,7 +3076,8 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
             // stalled at its step cap the recurrence restarts from the true residual
             // instead (a stagnating FP32 recurrence carried on can overflow)
             bool capped = false;
-            sst = cocg_cycle<C, CZ>(c, o, sh, L, Z, Pinv, tg, ck, act, first || rr_restart, iters, capped, st);
+            flag.take();
+            sst = cocg_cycle<C, CZ>(c, o, sh, L, Z, Pinv, tg, ck, act, first || rr_restart, iters, capped, flag, st);
             if (sst != CHAFF_OK) return sst;
             rr_restart = capped;
             continue;
@@ -3182,6 +3196,7 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
                        (const int32_t*)c->perm, c->n, s, Xout, 1);
     CHAFF_LAUNCH_CHECK();
     CHAFF_HIP(hipStreamSynchronize(st));
+    flag.give();
     double worst = 0.0;
     for (int64_t i = 0; i < nsys; ++i) worst = std::max(worst, rel[i]);
     if (rel_res_out)
