@@ -34,14 +34,14 @@ FP32_PEAK_TFLOPS = 157.3       # MI355X FP32 vector (packed) peak, TFLOP/s
 
 # profile name -> (kernel symbol prefix in rocprofv3 output, source file)
 KERNEL_SYMBOLS = {
-    "spmm": ("chaff::kr7::k_cocg_spmm", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
+    "spmm": ("chaff::kr7::k_cocg_mfma", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "k_cg_update": ("chaff::kr7::k_cg_update", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "k_cg_p": ("chaff::kr7::k_cg_p", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "fill_mutual": ("chaff::k_mutual", "paper_2410_03060_amd/csrc/fill.hip"),
     "fill_self": ("chaff::k_self", "paper_2410_03060_amd/csrc/fill.hip"),
     "rcs_mono": ("chaff::k_mono", "paper_2410_03060_amd/csrc/farfield.hip"),
     "cluster_build": ("chaff::k_cluster_build", "paper_2410_03060_amd/csrc/precond.hip"),
-    "nbhd_apply": ("chaff::kr7::k_cocg_spmm", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
+    "nbhd_apply": ("chaff::kr7::k_cocg_mfma", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "k_cg_rupd": ("chaff::kr7::k_cg_rupd", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "nbhd_build": ("chaff::k_nbhd_build", "paper_2410_03060_amd/csrc/precond.hip"),
 }

@@ -210,8 +210,9 @@ size_t chaff_solve_workspace_bytes(chaff_cloud c, const chaff_solve_opts* o, int
  *   ws       device workspace of chaff_solve_workspace_bytes.
  *   rel_res  [host out, optional] [n_clouds*R] final relative residuals (cloud-major).
  *   Host-synchronising: once per Krylov step the host reads back the count
- *   of systems still above their checkpoint (one int32), and once per cycle
- *   the FP64 residual norms. */
+ *   of systems still above their checkpoint (one int32; COCG's comes through a
+ *   slot of pinned memory), and once per cycle the FP64 residual norms; a small
+ *   solve is one launch and one read back at its end. */
 chaff_status chaff_solve(chaff_cloud c, const chaff_solve_opts* o, const void* Z,
                          const void* Pinv, const double* k_hat, const double* e_hat,
                          int64_t n_rhs, void* X, void* ws, size_t ws_bytes,

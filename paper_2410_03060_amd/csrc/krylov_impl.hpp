@@ -2090,7 +2090,7 @@ static SolveLayout carve_solve(void* ws, size_t ws_bytes, const SolveShape& sh) 
 // currents are Z_ii^-1 u_i, which the block-diagonal preconditioner holds.
 // Where at most LONE_SHARE of the wires can have a neighbour (bounded from the
 // pair count: n_coupled <= 2 n_pairs), the solve takes the others out of the
-// iteration: k_lone_solve solves them in one pass, and the Krylov cycles run on
+// iteration: they are solved in one pass (k_lone_solve, k_lone_apply), and the Krylov cycles run on
 // a compact cloud of the coupled wires.
 //   The line: the compaction costs a copy of the coupled blocks and two host
 // synchronisations (about 100 us); the iteration saves every vector pass of the
@@ -2115,11 +2115,13 @@ static bool lone_wires(const Cloud* c, const chaff_solve_opts* o) {
 constexpr int LONE_BLOCK = 256;   // wires per counting block
 static int64_t lone_blocks(int64_t n) { return (n + LONE_BLOCK - 1) / LONE_BLOCK; }
 
-// Device arrays of the compact cloud, before the solver's own workspace.
 // From this many columns on the lone wires' inverse blocks are refined in FP64
 // once and applied to the columns, where a wave holds one wire; with fewer, each
-// (wire, column) refines its own solution.
+// (wire, column) refines its own solution.  The two meet at the line: 10^5 wires of
+// 19 unknowns take 7.38 ms for 32 columns refined one by one and 7.25 for 33 this
+// way, 17 clouds of 7 unknowns 2.77 and 2.82; at 64 and 360 columns see k_lone_apply.
 constexpr int64_t LONE_INV = 32;
+// Device arrays of the compact cloud, before the solver's own workspace.
 struct LoneLayout {
     int32_t* cmap;      // [n] compact index of a coupled wire, -1 for the others
     int32_t* lone;      // [n] wires without neighbours, ascending

@@ -133,3 +133,22 @@ def test_a_preconditioner_that_is_not_the_inverse(B):
     with pytest.raises(B.ChaffError) as err:
         B.solve(cl, Z, P, inc.k_hat, inc.e_hat, B.solve_opts(tol=1e-6, method=B.COCG, restart=50, max_cycles=3))
     assert err.value.status == B.ENOCONV
+
+
+def test_a_preconditioner_that_is_not_the_inverse_many_columns(B):
+    """The same where the inverses are refined once per wire."""
+    cloud = _sparse(5, 5801, 60.0)
+    inc = W.azimuth_incidences(40)
+    cl = B.build_cloud(cloud)
+    Z, P = B.fill_Z(cl, B.C64)
+    X, info = B.solve(cl, Z, P * 0.25, inc.k_hat, inc.e_hat,
+                      B.solve_opts(tol=1e-7, method=B.COCG, restart=2000, inner_tol=1e-3))
+    assert info["max_rel_residual"] <= 1e-7
+    r2, u2 = _residual(B, cl, Z, X, inc)
+    assert (r2.sum(0) / u2.sum(0)).sqrt().max().item() <= 1.1e-7
+    row_ptr, _, _, _ = cl.pattern()
+    i = int(np.nonzero(np.diff(row_ptr) == 1)[0][0])
+    Z[int(row_ptr[i]), 0, 0] = complex(float("nan"), 0.0)
+    with pytest.raises(B.ChaffError) as err:
+        B.solve(cl, Z, P, inc.k_hat, inc.e_hat, B.solve_opts(tol=1e-6, method=B.COCG, restart=50, max_cycles=3))
+    assert err.value.status == B.ENOCONV
