@@ -7,7 +7,8 @@
 // arithmetic and L2 latency per step on one CU.  Here the vectors of a system
 // sit in L2, its threads take one row each, and barriers of one workgroup stand
 // in for the launches: nothing returns to the host until the residual of every
-// system is below the tolerance.
+// system is below the tolerance or the launch has run its share of steps
+// (LAUNCH_STEPS; the next launch then goes on where this one stopped).
 //
 // The recurrences, targets and restarts are those of the lockstep solver
 // (GMRES with classical Gram-Schmidt applied twice; COCG restarted at each FP64
@@ -35,13 +36,27 @@ constexpr int NW = TH / 64;                 // its waves
 constexpr int MAX_WIRES = 4096;             // wires of one cloud (16-bit indices in LDS)
 constexpr int MAX_CLOUDS = 32;              // cloud offsets travel with the launch
 constexpr int MAX_M = 200;                  // restart lengths chaff_solve accepts
+// Krylov steps of a system per launch: a solve that does not converge (restart
+// lengths up to 10^6, 1,000 cycles) is then a row of short launches with the host
+// between them, as the lockstep solver's is.  A step takes 20 us and more, a
+// further launch with its read back about 30 us.
+constexpr int LAUNCH_STEPS = 512;
 constexpr double PI_S = 3.14159265358979323846;
 constexpr int64_t MAX_SYSTEMS = 256;         // one workgroup per CU
 constexpr int64_t MAX_BYTES = 5 << 18;        // of the blocks that a product reads (1.25 MiB)
 
 struct Out {             // what a system tells the host
     double rel;          // FP64 relative residual, +inf after a breakdown
-    int32_t cycles, ok;  // refinement cycles run; 1 converged, 0 not, -1 broken down
+    int32_t cycles, ok;  // refinement cycles run; 1 converged, 0 not, -1 broken down, 2 goes on in another launch
+};
+
+// What a system carries from cycle to cycle, and over the end of a launch's share
+// into the next; its vectors lie in the workspace.
+struct Resume {
+    double bn, lone2, scale, target, ckpt;
+    c128 rho;
+    int32_t k, cycles;       // COCG cycle under way: r^T z of its last step, steps taken; cycles run
+    int32_t all, in_cycle;   // every wire is iterated on; the launch ended inside a cycle
 };
 
 template <typename C>
@@ -62,6 +77,8 @@ struct Args {
     c128* H;                       // per system [m][m + 1], column by column
     double* lone_e2;               // [wires][s] squared residual of a wire solved by k_lone
     int take_lone;                 // k_lone ran
+    int again;                     // a further launch of the same solve
+    Resume* resume;                // per system
     Out* out;
     int32_t* steps;                // per system [max_cycles]
 };
@@ -76,6 +93,7 @@ struct Shared {
     int32_t cnt[NW];
     double val[4];
     int32_t flag;
+    Resume at;                     // written by thread 0
 };
 
 __device__ __forceinline__ double wave_add(double v) {
@@ -377,23 +395,36 @@ __device__ int gmres_cycle(System<C>& Y, double rn, double target, c128* H) {
     return used;
 }
 
-// One COCG cycle: r in units of scale, ended below the checkpoint or after m
-// steps; x += scale * (its correction).  Returns its steps.
+// One COCG cycle: r in units of S.at.scale, ended below the checkpoint or after m
+// steps; S.flag says whether x_c holds a correction.  Returns its steps, or -1
+// where left, the launch's remaining steps, ran out first: called again, it goes
+// on from S.at.
 template <typename C>
-__device__ int cocg_cycle(System<C>& Y, double scale, double target, double ckpt) {
+__device__ int cocg_cycle(System<C>& Y, int left) {
     using R = typename real_of<C>::type;
     Shared& S = Y.S;
-    const int rows = Y.rows;
+    const int rows = Y.rows, k0 = S.at.k;
     C *rv = Y.vec(0), *p = Y.vec(1), *q = Y.vec(2), *xc = Y.vec(3);
-    for (int t = threadIdx.x; t < rows; t += TH) {
-        const int ci = t / NB;
-        rv[t] = ccast<C>(cscale(Y.r[Y.wire(ci) * NB + t - ci * NB], 1.0 / scale));
-    }
+    if (threadIdx.x == 0) S.flag = k0;   // every step so far added to x_c
+    if (k0 == 0)
+        for (int t = threadIdx.x; t < rows; t += TH) {
+            const int ci = t / NB;
+            rv[t] = ccast<C>(cscale(Y.r[Y.wire(ci) * NB + t - ci * NB], 1.0 / S.at.scale));
+        }
     __syncthreads();
-    c128 rho = {0, 0}, alpha = {0, 0};
-    int steps = 0;
-    for (int k = 0;; ++k) {
-        // r -= alpha q was applied; z = P r, rho' = r^T z, ||r||^2.  z is formed again below instead of stored
+    c128 rho = S.at.rho, alpha = {0, 0};
+    int steps;
+    for (int k = k0;; ++k) {
+        steps = k;
+        if (k - k0 >= left) {
+            if (threadIdx.x == 0) {
+                S.at.rho = rho;
+                S.at.k = k;
+            }
+            steps = -1;
+            break;
+        }
+        // r -= alpha q was applied; z = P r (in q until p takes it), rho' = r^T z, ||r||^2
         c128 rz = {0, 0}, rr = {0, 0};
         for (int t = threadIdx.x; t < rows; t += TH) {
             const int ci = t / NB;
@@ -407,7 +438,7 @@ __device__ int cocg_cycle(System<C>& Y, double scale, double target, double ckpt
         block_add(S, rz, rr);
         const double rn = sqrt(fmax(rr.re, 0.0));
         const double dd = rho.re * rho.re + rho.im * rho.im;
-        if (!(rn > target) || !isfinite(rn) || !(rn > ckpt) || k == Y.A.m) break;
+        if (!(rn > S.at.target) || !isfinite(rn) || !(rn > S.at.ckpt) || k == Y.A.m) break;
         const c128 beta = k > 0 && dd > 0.0 ? cmul(rz, c128{rho.re / dd, -rho.im / dd}) : c128{0, 0};
         rho = rz;
         const cplx<R> bt = ccast<cplx<R>>(beta);
@@ -417,7 +448,7 @@ __device__ int cocg_cycle(System<C>& Y, double scale, double target, double ckpt
             p[t] = z;
         }
         __syncthreads();
-        ++steps;
+        steps = k + 1;
         c128 sg = {0, 0}, none = {0, 0};
         for (int t = threadIdx.x; t < rows; t += TH) {
             const int ci = t / NB;
@@ -438,7 +469,7 @@ __device__ int cocg_cycle(System<C>& Y, double scale, double target, double ckpt
             xc[t] = xv;
         }
         __syncthreads();
-        if (threadIdx.x == 0) S.flag = steps;   // xc holds something
+        if (threadIdx.x == 0) S.flag = k + 1;   // xc holds something
     }
     __syncthreads();
     return steps;
@@ -478,68 +509,108 @@ __global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
         if (threadIdx.x == 0) A.out[sys] = Out{0.0, 0, 1};
         return;
     }
-    Y.list_coupled(!A.take_lone);
-    double b2, lone2;
-    Y.norms(b2, lone2);
-    if (Y.nc < n && !(lone2 <= 0.01 * A.tol * A.tol * b2)) {   // the block inverses do not solve them
-        Y.list_coupled(true);
-        lone2 = 0.0;
-    }
-    const double bn = sqrt(b2);
-    Y.excite();
-    // initial guess on the rows that are iterated on
-    for (int t = threadIdx.x; t < Y.rows; t += TH) {
-        const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
-        c128 v = {0, 0};
-        if (A.use_x0 == 1) v = A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs];
-        if (A.use_x0 == 2) row_dot<double>(v, A.P + ((int64_t)(w0 + i) * NB + q) * NB, Y.b + i * NB);
-        Y.x[i * NB + q] = v;
+    Resume& now = S.at;
+    if (A.again && A.out[sys].ok != 2) return;   // this system is done
+    if (threadIdx.x == 0) {
+        now = A.again ? A.resume[sys] : Resume{};
+        if (!A.again) now.all = !A.take_lone;
     }
     __syncthreads();
-    double scale = 0.0, rel = 0.0;
-    int cycles = 0, ok = 0;
+    Y.list_coupled(now.all);
+    if (!A.again) {
+        double b2, lone2;
+        Y.norms(b2, lone2);
+        if (Y.nc < n && !(lone2 <= 0.01 * A.tol * A.tol * b2)) {   // the block inverses do not solve them
+            Y.list_coupled(true);
+            lone2 = 0.0;
+        }
+        if (threadIdx.x == 0) {
+            now.bn = sqrt(b2);
+            now.lone2 = lone2;
+            now.all = Y.nc == n;
+        }
+        Y.excite();
+        // initial guess on the rows that are iterated on
+        for (int t = threadIdx.x; t < Y.rows; t += TH) {
+            const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
+            c128 v = {0, 0};
+            if (A.use_x0 == 1) v = A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs];
+            if (A.use_x0 == 2) row_dot<double>(v, A.P + ((int64_t)(w0 + i) * NB + q) * NB, Y.b + i * NB);
+            Y.x[i * NB + q] = v;
+        }
+        __syncthreads();
+    }
+    double rel = 0.0;
+    int ok = 0, left = LAUNCH_STEPS;   // a cycle counts as one more, for its residual
     for (;;) {
-        const double r2 = Y.residual(cycles == 0 && A.use_x0 == 0);
-        const double rn = sqrt(fmax(r2, 0.0));
-        rel = bn > 0 ? sqrt(r2 + lone2) / bn : 0.0;
-        if (!isfinite(r2)) {
-            rel = INFINITY;
-            ok = -1;
+        if (left <= 0) {
+            ok = 2;
             break;
         }
-        if (!(rel > A.tol)) {
-            ok = 1;
-            break;
-        }
-        if (cycles >= A.max_cycles) break;
         int steps;
-        if (A.method == CHAFF_GMRES) {
-            const double need = A.tol * bn / rn;
-            const double target = sizeof(C) == sizeof(c64) ? fmax(A.inner_tol, fmin(need, 1.0) * 0.5) : fmin(need * 0.5, 1.0);
-            steps = gmres_cycle<C>(Y, rn, target, H);
-        } else {
-            if (scale <= 0.0) scale = rn > 0 ? rn : 1.0;
-            const double target = 0.5 * A.tol * bn / scale;
-            if (threadIdx.x == 0) S.flag = 0;
-            steps = cocg_cycle<C>(Y, scale, target, fmax(target, A.inner_tol * rn / scale));
+        if (!now.in_cycle) {
+            const double bn = now.bn, r2 = Y.residual(now.cycles == 0 && A.use_x0 == 0), rn = sqrt(fmax(r2, 0.0));
+            rel = bn > 0 ? sqrt(r2 + now.lone2) / bn : 0.0;
+            if (!isfinite(r2)) {
+                rel = INFINITY;
+                ok = -1;
+                break;
+            }
+            if (!(rel > A.tol)) {
+                ok = 1;
+                break;
+            }
+            if (now.cycles >= A.max_cycles) break;
+            --left;
+            if (A.method == CHAFF_GMRES) {
+                const double need = A.tol * bn / rn;
+                const double target = sizeof(C) == sizeof(c64) ? fmax(A.inner_tol, fmin(need, 1.0) * 0.5) : fmin(need * 0.5, 1.0);
+                steps = gmres_cycle<C>(Y, rn, target, H);
+            } else if (threadIdx.x == 0) {
+                if (now.scale <= 0.0) now.scale = rn > 0 ? rn : 1.0;
+                now.target = 0.5 * A.tol * bn / now.scale;
+                now.ckpt = fmax(now.target, A.inner_tol * rn / now.scale);
+                now.k = 0;
+                now.rho = c128{0, 0};
+            }
+        }
+        if (A.method != CHAFF_GMRES) {
+            __syncthreads();
+            const int k0 = now.k;
+            steps = cocg_cycle<C>(Y, left);
+            if (threadIdx.x == 0) now.in_cycle = steps < 0;
+            if (steps < 0) {
+                left = 0;
+                __syncthreads();
+                continue;
+            }
+            left += k0;
             if (S.flag) {   // a correction was formed
                 const C* xc = Y.vec(3);
+                const double scale = now.scale;
                 for (int t = threadIdx.x; t < Y.rows; t += TH) {
                     const int ci = t / NB, a = Y.wire(ci) * NB + t - ci * NB;
                     const c128 v = ccast<c128>(xc[t]);
                     Y.x[a] = c128{Y.x[a].re + scale * v.re, Y.x[a].im + scale * v.im};
                 }
             }
-            __syncthreads();
         }
-        if (threadIdx.x == 0) A.steps[sys * A.max_cycles + cycles] = steps;
-        ++cycles;
+        left -= steps;
+        if (threadIdx.x == 0) {
+            A.steps[sys * A.max_cycles + now.cycles] = steps;
+            ++now.cycles;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) A.out[sys] = Out{rel, now.cycles, ok};
+    if (ok == 2) {
+        if (threadIdx.x == 0) A.resume[sys] = now;
+        return;
     }
     for (int t = threadIdx.x; t < Y.rows; t += TH) {
         const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
         A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs] = Y.x[i * NB + q];
     }
-    if (threadIdx.x == 0) A.out[sys] = Out{rel, cycles, ok};
 }
 
 // complex128 keeps one recurrence over every wire (its iterate at the tolerance is
@@ -563,6 +634,7 @@ static size_t carve(void* ws, size_t cap, const Cloud* c, const chaff_solve_opts
     a.V = cv.take<C>((size_t)a.nvec * rows * s);
     a.H = cv.take<c128>((size_t)nsys * m * (m + 1));
     a.lone_e2 = cv.take<double>((size_t)c->n * s);
+    a.resume = cv.take<Resume>(nsys);
     a.out = cv.take<Out>(nsys);
     a.steps = cv.take<int32_t>((size_t)nsys * o->max_cycles);
     return cv.off + 256;
@@ -627,20 +699,25 @@ static chaff_status solve_small_impl(Cloud* c, const chaff_solve_opts* o, const 
     a.X = static_cast<c128*>(X);
     const int64_t nsys = (int64_t)c->n_clouds * s;
     a.take_lone = small::takes_lone(c, o) ? 1 : 0;
-    {
-        ProfScope ps("solve_small", st);
-        if (a.take_lone)
-            hipLaunchKernelGGL(small::k_lone<C>, dim3((unsigned)((c->n * s + 63) / 64)), dim3(64), 0, st, a, c->n);
-        hipLaunchKernelGGL(small::k_solve_small<C>, dim3((unsigned)nsys), dim3(small::TH), 0, st, a);
-    }
-    CHAFF_LAUNCH_CHECK();
     // the systems' answers and steps lie one after the other: one copy
     const size_t head = (const char*)a.steps - (const char*)a.out;
     std::vector<char> back(head + (size_t)nsys * o->max_cycles * sizeof(int32_t));
-    CHAFF_HIP(hipMemcpyAsync(back.data(), a.out, back.size(), hipMemcpyDeviceToHost, st));
-    CHAFF_HIP(hipStreamSynchronize(st));
     const small::Out* out = reinterpret_cast<const small::Out*>(back.data());
     const int32_t* steps = reinterpret_cast<const int32_t*>(back.data() + head);
+    for (bool more = true; more;) {   // a launch per LAUNCH_STEPS steps of the slowest system
+        {
+            ProfScope ps("solve_small", st);
+            if (a.take_lone && !a.again)
+                hipLaunchKernelGGL(small::k_lone<C>, dim3((unsigned)((c->n * s + 63) / 64)), dim3(64), 0, st, a, c->n);
+            hipLaunchKernelGGL(small::k_solve_small<C>, dim3((unsigned)nsys), dim3(small::TH), 0, st, a);
+        }
+        CHAFF_LAUNCH_CHECK();
+        CHAFF_HIP(hipMemcpyAsync(back.data(), a.out, back.size(), hipMemcpyDeviceToHost, st));
+        CHAFF_HIP(hipStreamSynchronize(st));
+        a.again = 1;
+        more = false;
+        for (int64_t i = 0; i < nsys; ++i) more = more || out[i].ok == 2;
+    }
     int cycles = 0, iters = 0;
     double worst = 0.0;
     bool all = true, broken = false;
