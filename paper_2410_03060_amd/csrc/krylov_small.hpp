@@ -1,9 +1,10 @@
 // Small solves: one workgroup takes one system (cloud, incidence) from its
 // excitation to its currents in a single launch.
 //
-// The lockstep solver (krylov_impl.hpp) spends 12 to 14 launches and a host
-// synchronisation on every Krylov step, about 75 us whatever the system's size;
-// a cloud of a few thousand sparsely coupled wires needs less than 20 us of
+// The lockstep solver (krylov_impl.hpp) spends six launches and a look at pinned
+// memory on a COCG step (30 us whatever the system's size), twice that and a host
+// synchronisation on a GMRES step (100 us and more), and 0.3 ms on a solve beside
+// them; a cloud of a few thousand sparsely coupled wires needs 10 to 40 us of
 // arithmetic and L2 latency per step on one CU.  Here the vectors of a system
 // sit in L2, its threads take one row each, and barriers of one workgroup stand
 // in for the launches: nothing returns to the host until the residual of every
@@ -166,7 +167,7 @@ struct System {
         }
         __syncthreads();
     }
-    // sum over the row's blocks of Z v, v on the coupled rows (STRIDE: by compact or by cloud wire)
+    // sum over the row's blocks of Z v, v indexed by coupled wire (compact) or by wire of the cloud
     template <typename T, typename VT>
     __device__ __forceinline__ cplx<T> z_row(int i, int q, const VT* v, bool compact) const {
         cplx<T> a = {0, 0};
@@ -642,24 +643,51 @@ static size_t carve(void* ws, size_t cap, const Cloud* c, const chaff_solve_opts
 
 }  // namespace small
 
-// Whether a call goes through one launch.  The line, whole steps on one MI355X
-// (single launch / lockstep): blocks of 0.1 MB (64 wires, complex128 GMRES) 0.40 /
-// 1.21 ms; 0.4 MB (2,000 sparse wires, complex64) 0.57 / 1.33 ms; 0.6 MB (256 wires,
-// complex128) 0.67 / 1.5 ms; 0.9 MB (4,000 sparse wires) 0.77 / 1.6 ms; 1.2 MB (4,000
-// wires of 19 unknowns) 0.94 / 1.5 ms; 2.4 MB (1,000 wires, complex128) 3.1 / 2.3 ms;
-// 3 MB (2,500 wires, complex64 COCG) 3.7 / 2.4 ms: one CU streams too slowly from
-// there on.  A system takes a CU; 200 of them take 0.82 ms where one takes 0.59.
+// Whether a call goes through one launch: blocks of at most MAX_BYTES (one CU
+// streams too slowly from there on) and an estimate of its step's time on the CU
+// that the largest cloud takes, in us, against the lockstep solver's.
+//   A step here takes 5 us, 21 per MB of blocks, per iterated row 3.2e-3 (complex64,
+// 7 unknowns; in complex128 1.6 times as much, with 19 unknowns another 1.65), and
+// in GMRES 0.5e-3 per row and basis vector that a full cycle holds.  COCG, measured /
+// estimated: complex64 0.11 MB on 1,050 rows 11.0 / 10.7, 0.74 MB on 7,000 rows 46 / 43,
+// 1.27 MB on 399 rows 37 / 33; complex128 0.43 MB on 2,100 rows 25 / 25, 0.86 MB on
+// 4,200 rows 44 / 44; 19 unknowns, 1.06 MB on 6,650 rows 61 / 62.  GMRES(30), complex64,
+// 7,000 rows 121 / 148; GMRES(200), complex128, 2,100 rows 276 / 230, 7,000 rows 941 / 760.
+//   Lockstep COCG: 30 us a step (19 unknowns 40) and 0.3 ms a solve; the line is where a
+// solve of ten steps takes as long either way.  Whole solves, here / lockstep, ms:
+// estimate 38 (complex128, 600 sparse wires, 8 steps) 0.39 / 0.60; 44 (600 in a box,
+// 12 steps) 0.67 / 0.74; 47 (complex64, 1,200, 18 steps) 0.80 / 0.87; 59 (complex128,
+// 1,000 sparse, 9 steps) 0.64 / 0.63; 64 (900 in a box, 17 steps) 1.26 / 0.89.  A
+// solve of hundreds of steps would be faster in lockstep from an estimate of 30 on
+// (at 44: 12.3 / 8.9), but no call says beforehand how many it will take.
+//   Lockstep GMRES: 80 us a step and 1.75 per basis vector.  A full cycle may cost
+// 1.3 times that: the cycles that end early, as most do, then gain.  Ratio of the
+// estimates against whole solves, here / lockstep, ms: 0.55 (GMRES(200), 300 wires,
+// complex128, 1,070 steps) 295 / 466; 0.8 (GMRES(30), 600 wires in a box, 10 steps)
+// 0.68 / 1.04; 1.2 (1,200, complex64, 18 steps) 1.08 / 1.81; 1.2 (900, complex128, 15 steps)
+// 1.55 / 1.62; 1.5 (GMRES(60), 1,000 wires, complex128, 1,380 steps) 399 / 255; 1.8
+// (GMRES(200), the same) 1,130 / 562.
+//   A system takes a CU; 256 of them take 1.3 times as long as 32, lockstep 1.5 to 2.5.
 bool small_solve(const Cloud* c, const chaff_solve_opts* o, int64_t s) {
     if (o->precond != CHAFF_PRECOND_BLOCK || (o->method != CHAFF_GMRES && o->method != CHAFF_COCG)) return false;
     if (o->spmm_variant >= 0) return false;   // the caller asks for a product kernel
     if (c->n_clouds > small::MAX_CLOUDS || o->max_cycles > 1000) return false;
     const int64_t nsys = (int64_t)c->n_clouds * s;
     if (nsys > small::MAX_SYSTEMS) return false;
-    for (int k = 0; k < c->n_clouds; ++k)
-        if (c->cloud_off[k + 1] - c->cloud_off[k] > small::MAX_WIRES) return false;
-    // blocks that a product reads: of the coupled wires (at most) or of all
-    const int64_t blocks = 2 * c->n_pairs + (small::takes_lone(c, o) ? std::min<int64_t>(c->n, 2 * c->n_pairs) : c->n);
-    return blocks * small::NB2 * (o->prec == CHAFF_C64 ? 8 : 16) <= small::MAX_BYTES;
+    int64_t largest = 0;
+    for (int k = 0; k < c->n_clouds; ++k) largest = std::max(largest, c->cloud_off[k + 1] - c->cloud_off[k]);
+    if (largest > small::MAX_WIRES) return false;
+    // wires that are iterated on and blocks that a product reads: of the coupled wires (at most) or of all
+    const bool single = o->prec == CHAFF_C64;
+    const int64_t coupled = small::takes_lone(c, o) ? std::min<int64_t>(c->n, 2 * c->n_pairs) : c->n;
+    const int64_t bytes = (2 * c->n_pairs + coupled) * small::NB2 * (single ? 8 : 16);
+    if (bytes > small::MAX_BYTES) return false;
+    const double share = (double)largest / (double)std::max<int64_t>(c->n, 1);
+    const double rows = (double)(std::min(largest, coupled) * small::NB);
+    const double step = 5.0 + 21e-6 * share * (double)bytes +
+                        3.2e-3 * (single ? 1.0 : 1.6) * (small::NB > 8 ? 1.65 : 1.0) * rows;
+    if (o->method == CHAFF_COCG) return step <= (small::NB > 8 ? 70.0 : 60.0);
+    return step + 0.5e-3 * rows * o->restart <= 1.3 * (80.0 + 1.75 * o->restart);
 }
 
 size_t small_workspace_bytes(const Cloud* c, const chaff_solve_opts* o, int64_t s) {
