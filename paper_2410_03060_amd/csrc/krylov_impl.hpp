@@ -500,6 +500,10 @@ static int cocg_width(int64_t s) {
     return s <= STREAM_COCG ? (int)s : std::max(spmm_tile_width(s), 8);
 }
 
+// block rows per launch of the variants that take up to a wave per row: the
+// threads of a launch are counted in 32 bits, and a cloud may hold 2^28 wires
+constexpr int64_t WAVE_ROWS = int64_t{1} << 25;
+
 // variant: 0 = rowq, 1 = tile (ST from s), 2 = tile with ST halved (more rows per wave),
 // 3 = tile in XCD-aware order, 4 = XCD-aware with ST halved, 5 = rowq with up to 16
 // columns per lane, 6 = one wave per block row with the block staged in LDS, 7 = 6 in
@@ -533,6 +537,16 @@ static chaff_status spmm_launch(const int64_t* row_ptr, const int32_t* col_idx, 
         if (variant == 6 || variant == 7) variant = 3;
     }
     if constexpr (NB2 <= 64) if ((variant == 6 || variant == 7) && !DIAG) {
+        if (n > WAVE_ROWS) {   // row by row as one launch
+            for (int64_t i = 0; i < n; i += WAVE_ROWS) {
+                const int64_t o = i * NB * s;
+                const chaff_status e = spmm_launch<CZ, CX, CY, MODE, DIAG>(row_ptr + i, col_idx, Z, X, B ? B + o : B, Y + o,
+                                                                           std::min(WAVE_ROWS, n - i), nnzb, s, variant, st,
+                                                                           nullptr);
+                if (e != CHAFF_OK) return e;
+            }
+            return CHAFF_OK;
+        }
         if (variant == 7 && s <= STREAM_MAX) {
             const int64_t n_grp = (n + STREAM_WAVES - 1) / STREAM_WAVES;
             const dim3 grid((unsigned)((n_grp + NXCD - 1) / NXCD * NXCD));
@@ -3300,10 +3314,10 @@ __global__ __launch_bounds__(LONE_BLOCK) void k_lone_place(const int64_t* __rest
 
 // Blocks, columns and inverse self blocks of the coupled wires: one wave per wire.
 template <typename CZ>
-__global__ __launch_bounds__(256) void k_lone_blocks(int64_t nc, const int64_t* __restrict__ row_ptr,
+__global__ __launch_bounds__(256) void k_lone_blocks(int64_t c0, int64_t nc, const int64_t* __restrict__ row_ptr,
                                                      const int32_t* __restrict__ col_idx, const CZ* __restrict__ Z,
                                                      const CZ* __restrict__ Pinv, LoneLayout l) {
-    const int64_t ci = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t ci = c0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (ci >= nc) return;
     const int64_t i = l.src[ci], e0 = row_ptr[i], f0 = l.row_ptr[ci];
@@ -3578,9 +3592,11 @@ static chaff_status solve_compact(Cloud* c, const chaff_solve_opts* o, const CZ*
         }
         return CHAFF_OK;
     }
-    hipLaunchKernelGGL((k_lone_blocks<CZ>), dim3((unsigned)((nc + 3) / 4)), dim3(256), 0, st, nc,
-                       (const int64_t*)c->row_ptr, (const int32_t*)c->col_idx, Z, Pinv, l);
-    CHAFF_LAUNCH_CHECK();
+    for (int64_t c0 = 0; c0 < nc; c0 += WAVE_ROWS) {
+        hipLaunchKernelGGL((k_lone_blocks<CZ>), dim3((unsigned)((std::min(WAVE_ROWS, nc - c0) + 3) / 4)), dim3(256), 0, st,
+                           c0, nc, (const int64_t*)c->row_ptr, (const int32_t*)c->col_idx, Z, Pinv, l);
+        CHAFF_LAUNCH_CHECK();
+    }
     Cloud cc = *c;
     cc.n = nc;
     cc.nnzb = c->nnzb - n_lone;

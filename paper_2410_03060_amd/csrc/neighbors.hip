@@ -470,13 +470,17 @@ __global__ void k_cells(const Wire* __restrict__ wires, const int32_t* __restric
 // 175 us each for 2,000 wires, where few waves hide nothing; this form 153 and
 // 180 us, and 9 us each.
 constexpr int NEAR_WIRES = 8;   // wires per workgroup of 256
+// workgroups per launch: the threads of a launch are counted in 32 bits, and a
+// cloud may hold 2^28 wires of 32 lanes
+constexpr int64_t NEAR_LAUNCH = int64_t{1} << 22;
 template <int WRITE>
 __global__ __launch_bounds__(32 * NEAR_WIRES) void k_near(const Wire* __restrict__ wires,
                                                          const int32_t* __restrict__ wire_cloud,
                                                          const CloudGrid* __restrict__ grids,
                                                          const int32_t* __restrict__ cell_start,
-                                                         const int32_t* __restrict__ cell_end, int64_t n, double dc2,
-                                                         Count2* __restrict__ cnt, const int64_t* __restrict__ row_ptr,
+                                                         const int32_t* __restrict__ cell_end, int64_t n,
+                                                         int64_t block0, double dc2, Count2* __restrict__ cnt,
+                                                         const int64_t* __restrict__ row_ptr,
                                                          const int64_t* __restrict__ pair_ptr,
                                                          int32_t* __restrict__ col_idx, int64_t* __restrict__ diag_pos,
                                                          Pair* __restrict__ pairs) {
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(32 * NEAR_WIRES) void k_near(const Wire* __restrict
     __shared__ int2 run[NEAR_WIRES][32];    // {first candidate, start} of each run, ascending
     const int g = threadIdx.x >> 5, l = threadIdx.x & 31;
     const int shift = (g & 1) * 32;         // this wire's half of the wave's ballots
-    const int64_t i = (int64_t)blockIdx.x * NEAR_WIRES + g;
+    const int64_t i = (block0 + blockIdx.x) * NEAR_WIRES + g;
     const bool live = i < n;
     const Wire& w = wires[live ? i : 0];
     const double ci[3] = {w.cx, w.cy, w.cz};
@@ -631,6 +635,19 @@ static BuildLayout carve_build(void* ws, size_t ws_bytes, int64_t n, int32_t n_c
 
 size_t build_workspace_bytes(int64_t n, int32_t n_clouds, int64_t max_nnzb) {
     return carve_build(nullptr, 0, n, n_clouds, max_nnzb).bytes + 256;
+}
+
+template <int WRITE>
+static chaff_status near_launch(const BuildLayout& L, int64_t n, double dc2, hipStream_t st) {
+    const int64_t blocks = (n + NEAR_WIRES - 1) / NEAR_WIRES;
+    for (int64_t b = 0; b < blocks; b += NEAR_LAUNCH) {
+        hipLaunchKernelGGL(k_near<WRITE>, dim3((unsigned)std::min(NEAR_LAUNCH, blocks - b)), dim3(32 * NEAR_WIRES), 0, st,
+                           (const Wire*)L.wires, (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
+                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, b, dc2, L.cnt,
+                           (const int64_t*)L.row_ptr, (const int64_t*)L.pair_ptr, L.col_idx, L.diag_pos, L.pairs);
+        CHAFF_LAUNCH_CHECK();
+    }
+    return CHAFF_OK;
 }
 
 static int grid1d(int64_t n, int threads = 256, int64_t cap = 65536) {
@@ -781,13 +798,9 @@ chaff_status build_cloud(const chaff_params* p, const int64_t* cloud_off, const 
     const double dc2 = std::isfinite(p->d_c) ? p->d_c * p->d_c : INFINITY;
     {
         ProfScope pc("nbr_count", st);
-        hipLaunchKernelGGL(k_near<0>, dim3((unsigned)((n + NEAR_WIRES - 1) / NEAR_WIRES)), dim3(32 * NEAR_WIRES), 0, st,
-                           (const Wire*)L.wires, (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
-                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, dc2, L.cnt,
-                           (const int64_t*)nullptr, (const int64_t*)nullptr, (int32_t*)nullptr, (int64_t*)nullptr,
-                           (Pair*)nullptr);
+        chaff_status s = near_launch<0>(L, n, dc2, st);
+        if (s != CHAFF_OK) return s;
     }
-    CHAFF_LAUNCH_CHECK();
     Sum2 *d_tot = nullptr, tot{0, 0};
     chaff_status s1 = scan2(L.cnt, n, L.row_ptr, L.pair_ptr, L.sums64, &d_tot, st);
     if (s1 != CHAFF_OK) return s1;
@@ -803,12 +816,9 @@ chaff_status build_cloud(const chaff_params* p, const int64_t* cloud_off, const 
     // --- pass 2: column indices, diagonal positions, unique pairs
     {
         ProfScope pp("nbr_pattern", st);
-        hipLaunchKernelGGL(k_near<1>, dim3((unsigned)((n + NEAR_WIRES - 1) / NEAR_WIRES)), dim3(32 * NEAR_WIRES), 0, st,
-                           (const Wire*)L.wires, (const int32_t*)L.wire_cloud, (const CloudGrid*)L.grids,
-                           (const int32_t*)L.cell_start, (const int32_t*)L.cell_end, n, dc2, (Count2*)nullptr,
-                           (const int64_t*)L.row_ptr, (const int64_t*)L.pair_ptr, L.col_idx, L.diag_pos, L.pairs);
+        chaff_status s = near_launch<1>(L, n, dc2, st);
+        if (s != CHAFF_OK) return s;
     }
-    CHAFF_LAUNCH_CHECK();
     if (n_pairs > 0) {
         hipLaunchKernelGGL(k_pair_transpose, dim3(grid1d(n_pairs)), dim3(256), 0, st, L.pairs, n_pairs,
                            (const int64_t*)L.row_ptr, (const int32_t*)L.col_idx);

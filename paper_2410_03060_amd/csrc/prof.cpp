@@ -45,7 +45,7 @@ int name_id(const char* n) {
 }  // namespace
 
 ProfScope::ProfScope(const char* name, hipStream_t st, ProfWork w) : st_(st) {
-    if (!g_on.load(std::memory_order_relaxed)) return;
+    if (!name || !g_on.load(std::memory_order_relaxed)) return;
     std::lock_guard<std::mutex> lk(g_mu);
     hipEvent_t a = take_event(), b = take_event();
     if (!a || !b) return;

@@ -10,6 +10,7 @@ struct ProfWork {
 };
 class ProfScope {
   public:
+    // name: nullptr for a launch that another scope counts already;
     // work: algorithmic bytes (flops = false) or flops (flops = true) of this launch
     ProfScope(const char* name, hipStream_t st, double work = 0.0, bool flops = false)
         : ProfScope(name, st, flops ? ProfWork{0.0, work} : ProfWork{work, 0.0}) {}
