@@ -359,8 +359,12 @@ chaff_status chaff_spmm(chaff_cloud c, chaff_prec prec, const void* Z, const voi
  * and RHS count on the caller's Z and two [N*NB][s] buffers (contents of Y are
  * overwritten, X is read), and records the fastest in a process-wide table
  * keyed by (N, nnzb, s, prec).  Every later call with variant -1 (chaff_spmm,
- * and the products inside chaff_solve, including the COCG product's tile
- * width and workgroup order) uses the recorded choice.
+ * and the products inside chaff_solve, including the COCG product's workgroup
+ * order; where a solve takes the wires without neighbours out of its iteration,
+ * the choice recorded for the whole cloud) uses the recorded choice.  A small
+ * solve in one launch (see chaff_solve) has no product launch that a recorded
+ * choice could apply to; a variant named in its options keeps it in the lockstep
+ * solver.
  *   best_variant, best_ms [host out, optional].  Synchronises `stream`.
  * chaff_tune_report writes the table as JSON text into buf [host] (at most len
  * bytes, NUL-terminated) and returns the length needed including the NUL. */

@@ -500,6 +500,8 @@ static int cocg_width(int64_t s) {
     return s <= STREAM_COCG ? (int)s : std::max(spmm_tile_width(s), 8);
 }
 
+constexpr int RULE_VARIANT = -2;   // default_variant, whatever the tuning table holds
+
 // block rows per launch of the variants that take up to a wave per row: the
 // threads of a launch are counted in 32 bits, and a cloud may hold 2^28 wires
 constexpr int64_t WAVE_ROWS = int64_t{1} << 25;
@@ -518,8 +520,8 @@ static chaff_status spmm_launch(const int64_t* row_ptr, const int32_t* col_idx, 
                            : ((double)sizeof(CZ) * NB2 + 4.0) * (double)nnzb + 8.0 * (n + 1);
     const double vb = 7.0 * n * s * ((double)sizeof(CX) + sizeof(CY) + (MODE == 0 ? 0.0 : (double)sizeof(CY)));
     ProfScope ps(tag, st, zb + vb, false);
-    if (variant < 0) {
-        const int t = (!DIAG && MODE == 0 && std::is_same<CZ, CX>::value && std::is_same<CX, CY>::value)
+    if (variant < 0) {   // RULE_VARIANT: the table was asked already
+        const int t = (variant != RULE_VARIANT && !DIAG && MODE == 0 && std::is_same<CZ, CX>::value && std::is_same<CX, CY>::value)
                           ? tuned_variant(NB, n, nnzb, s, std::is_same<CZ, c64>::value ? CHAFF_C64 : CHAFF_C128)
                           : -1;
         variant = t >= 0 ? t
@@ -2035,10 +2037,6 @@ static SolveShape solve_shape(const Cloud* c, int m, int64_t s, chaff_prec prec,
     sh.n_groups = 0;
     sh.cocg_st = cocg_width(s);
     sh.cocg_xcd = 1;
-    {   // the COCG product follows the tuned public variant's workgroup order (1, 2, 6: linear)
-        const int v = tuned_variant(NB, c->n, c->nnzb, s, prec);
-        sh.cocg_xcd = (v == 1 || v == 2 || v == 6) ? 0 : 1;
-    }
     sh.tile_w = COCG_TILE_ROWS;
     if (cocg) {
         for (int k = 0; k < c->n_clouds; ++k) {
@@ -2894,6 +2892,7 @@ static chaff_status gcr_cycle(Cloud* c, const chaff_solve_opts* o, const SolveSh
 // system: what solve_impl adds to the norms of the coupled rows it iterates on.
 struct LoneSums {
     std::vector<double> b2, r2;   // [n_clouds * s]
+    int tuned;                    // the whole cloud's entry in the tuning table, -1 if none
 };
 
 template <typename C, typename CZ>
@@ -2904,6 +2903,11 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
     auto t_start = std::chrono::steady_clock::now();
     const int m = o->restart;
     SolveShape sh = solve_shape(c, m, s, (chaff_prec)o->prec, o->method);
+    const int tuned = lone ? lone->tuned : tuned_variant(NB, c->n, c->nnzb, s, o->prec);
+    chaff_solve_opts resolved = *o;
+    if (resolved.spmm_variant < 0) resolved.spmm_variant = tuned >= 0 ? tuned : RULE_VARIANT;
+    o = &resolved;
+    sh.cocg_xcd = (tuned == 1 || tuned == 2 || tuned == 6) ? 0 : 1;   // the COCG product takes its order (these: linear)
     SolveLayout L = carve_solve(ws, ws_bytes, sh);
     if (L.bytes > ws_bytes)
         return fail(CHAFF_EWORKSPACE, "solve workspace too small: need " + std::to_string(L.bytes));
@@ -3536,6 +3540,7 @@ static chaff_status solve_compact(Cloud* c, const chaff_solve_opts* o, const CZ*
     LoneSums sums;
     sums.b2.assign(nsys, 0.0);
     sums.r2.assign(nsys, 0.0);
+    sums.tuned = tuned_variant(NB, n, c->nnzb, s, o->prec);
     if (n_lone > 0) {
         CHAFF_HIP(hipMemcpyAsync(l.chunks, ch.data(), ch.size() * sizeof(Chunk), hipMemcpyHostToDevice, st));
         CHAFF_HIP(hipMemcpyAsync(l.cloud_chunk_off, off.data(), off.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
