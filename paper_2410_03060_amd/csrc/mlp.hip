@@ -408,6 +408,9 @@ __global__ __launch_bounds__(256) void k_train_rows(RowsArgs g) {
 // a layer's weights (16 x 14 of the last), or one bias part[s][off] = sum_m dZT[o][m].
 constexpr int WG_L1 = NF / 16 * (NH / 64), WG_L = NH / 16 * (NH / 64), WG_L4 = NH / 16;
 constexpr int WG_TILES = WG_L1 + 2 * WG_L + WG_L4, WG_UNITS = WG_TILES + NO + 3 * NH;
+// splits per launch: the threads of a launch are counted in 32 bits, and 145,258
+// splits (74 million rows) have more
+constexpr int64_t WG_LAUNCH = 65536;
 
 template <int NT>
 __device__ __forceinline__ void wgrad_tile(const uint16_t* __restrict__ aT, const uint16_t* __restrict__ dZT,
@@ -436,9 +439,9 @@ __device__ __forceinline__ void wgrad_tile(const uint16_t* __restrict__ aT, cons
     }
 }
 
-__global__ __launch_bounds__(64) void k_train_wgrad(RowsArgs g, float* __restrict__ part) {
-    const int64_t s = blockIdx.x / WG_UNITS;
-    int u = (int)(blockIdx.x - s * WG_UNITS);
+__global__ __launch_bounds__(64) void k_train_wgrad(RowsArgs g, int64_t split0, float* __restrict__ part) {
+    const int64_t s = split0 + blockIdx.x / WG_UNITS;
+    int u = (int)(blockIdx.x % WG_UNITS);
     float* dst = part + s * NPARAM;
     if (u < WG_L1) {
         wgrad_tile<4>(g.fT, g.dZT1, g.Mpad, u / 2 * 16, u % 2 * 64, NH, s, dst + OW1);
@@ -1126,8 +1129,11 @@ static chaff_status train_pass(const float* theta, const uint16_t* feat, const f
         default: hipLaunchKernelGGL(k_train_rows<1>, dim3(rows_grid), dim3(256), 0, st, g); break;
     }
     CHAFF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_train_wgrad, dim3((unsigned)(WG_UNITS * nsplit)), dim3(64), 0, st, g, b.part);
-    CHAFF_LAUNCH_CHECK();
+    for (int64_t s0 = 0; s0 < nsplit; s0 += WG_LAUNCH) {
+        hipLaunchKernelGGL(k_train_wgrad, dim3((unsigned)(WG_UNITS * std::min(WG_LAUNCH, nsplit - s0))), dim3(64), 0, st, g,
+                           s0, b.part);
+        CHAFF_LAUNCH_CHECK();
+    }
     const float scale = (float)(1.0 / ((double)M * NO));
     hipLaunchKernelGGL(k_reduce, dim3(nblk(NPARAM, 256) + 1), dim3(256), 0, st, (const float*)b.part, nsplit, scale,
                        grad, (const float*)b.loss_part, (int64_t)rows_grid, loss, ad);

@@ -94,3 +94,26 @@ def test_product(B, s, variant):
     assert err <= 32 * 2.0 ** -24
     assert int((Y.abs().amax((1, 2)) == 0).sum()) == 0
     B.destroy(cl)
+
+
+def test_gradient_of_many_rows(B):
+    """Weight gradients over more splits than one launch counts threads for: a batch repeated whole times
+    has its own gradient; the partial sums are added one after the other in FP32, splits * eps at most."""
+    import torch
+    base, times = 4096, 18176
+    splits = base * times // 512
+    assert splits * 462 * 64 > 1 << 32
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 200 * GB:
+        pytest.skip("needs 200 GB of device memory")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    feat = torch.randn((base, 192), generator=g, device="cuda").to(torch.bfloat16).view(torch.int16)
+    T = torch.randn((base, 14), generator=g, device="cuda")
+    th = torch.as_tensor(W.mlp_init(7).astype(np.float32), device="cuda")
+    one, loss1 = B.mlp_grad(th, feat, T)
+    idx = torch.arange(base, device="cuda").repeat(times)
+    many, loss = B.mlp_grad(th, feat, T, idx)
+    err = ((many - one).double().norm() / one.double().norm()).item()
+    say(f"[many] gradient of {base * times} rows: {err:.1e}")
+    assert err <= splits * 2.0 ** -24
+    assert abs(loss.item() - loss1.item()) <= 1e-5 * loss1.item()
