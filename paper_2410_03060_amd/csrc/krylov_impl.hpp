@@ -2611,7 +2611,7 @@ static chaff_status cocg_cycle(Cloud* c, const chaff_solve_opts* o, const SolveS
         launch_cg_step(cs, Lc, nbhd, mode, flag.p, ++flag.seq, st);
         CHAFF_LAUNCH_CHECK();
         int32_t n_act = 0;
-        const chaff_status fst = flag.wait(L.counter, n_act, st);
+        const chaff_status fst = flag.wait(L.counter, n_act);
         if (fst != CHAFF_OK) return fst;
         if (g_verbose && k % 50 == 0)
             std::fprintf(stderr, "[chaff] cocg step %d: %d of %lld systems above their checkpoint (%lld columns)\n",
@@ -3020,7 +3020,7 @@ static chaff_status solve_impl(Cloud* c, const chaff_solve_opts* o, const CZ* Z,
     std::vector<double> hinv(nsys), hrn(nsys), cocg_scale;
     std::vector<SysState> hsys(nsys);
     c128* const r_buf = L.r;
-    StepFlag flag;
+    StepFlag flag(st);
     for (;;) {
         // true residual r = b - Z x (FP64 accumulation over the stored Z); from zero it is b itself
         const bool zero_start = cycles == 0 && o->use_x0 == 0;

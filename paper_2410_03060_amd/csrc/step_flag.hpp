@@ -10,10 +10,10 @@
 namespace chaff {
 
 // One page of pinned host memory per process, 64 slots: a solve takes a slot for
-// its duration and gives it back once its stream has drained (a call that ends
-// with work in flight keeps it, so that nothing late can be taken for another
-// call's count).  Allocating per call would make every solve wait for every
-// stream of the device when the memory is freed.
+// its duration and gives it back once its stream has drained, also where it ends
+// in an error (only a stream that fails itself keeps its slot, so that nothing
+// late can be taken for another call's count).  Allocating per call would make
+// every solve wait for every stream of the device when the memory is freed.
 class FlagPage {
 public:
     uint64_t* take(int& slot) {
@@ -54,10 +54,18 @@ struct StepFlag {
     uint64_t* p = nullptr;
     uint32_t seq = 0;
     int slot = -1;
+    hipStream_t st;
 
-    StepFlag() = default;
+    explicit StepFlag(hipStream_t stream) : st(stream) {}
     StepFlag(const StepFlag&) = delete;
     StepFlag& operator=(const StepFlag&) = delete;
+    ~StepFlag() {   // a solve that returned early may have steps in flight
+        if (!p) return;
+        if (hipStreamSynchronize(st) == hipSuccess)
+            give();
+        else
+            (void)hipGetLastError();
+    }
     void take() {
         if (!p && (p = g_flag_page.take(slot))) __atomic_store_n(p, 0, __ATOMIC_RELEASE);
     }
@@ -72,7 +80,7 @@ struct StepFlag {
         return (uint32_t)(v >> 32) == seq;
     }
     // the count of the step launched last; ends with the stream's work, in order or in error
-    chaff_status wait(const int32_t* counter, int32_t& n, hipStream_t st) const {
+    chaff_status wait(const int32_t* counter, int32_t& n) const {
         if (!p) {
             CHAFF_HIP(hipMemcpyAsync(&n, counter, sizeof(int32_t), hipMemcpyDeviceToHost, st));
             CHAFF_HIP(hipStreamSynchronize(st));
@@ -81,8 +89,10 @@ struct StepFlag {
         // the stream is asked only now and then: each query submits work of its own,
         // which held a run of 1 ms kernels back by 3%
         for (auto asked = std::chrono::steady_clock::now();;) {
-            for (int i = 0; i < 4096; ++i)
+            for (int i = 0; i < 1024; ++i) {
                 if (read(n)) return CHAFF_OK;
+                __builtin_ia32_pause();   // the core's other thread runs meanwhile
+            }
             const auto now = std::chrono::steady_clock::now();
             if (now - asked < std::chrono::milliseconds(20)) continue;
             asked = now;
