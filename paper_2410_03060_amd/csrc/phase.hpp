@@ -39,10 +39,8 @@ __device__ __forceinline__ void sinccospi_small(double x, double& sr, double& c)
     q = fma(q, t, -0.5);
     c = fma(q, t, 1.0);
 }
-// sin(pi x), cos(pi x) for any finite x (exact quadrant: 2 x - rint(2 x) is exact)
-__device__ __forceinline__ void sincospi_any(double x, double& s, double& c) {
-    const double n = rint(2.0 * x);
-    const double y = fma(-0.5, n, x);
+// sine and cosine of pi (n / 2 + y), n whole, |y| at most a quarter and a little
+__device__ __forceinline__ void sincospi_quarter(double n, double y, double& s, double& c) {
     double sn, cs;
     sinccospi_small(y, sn, cs);
     sn *= PI_H * y;
@@ -50,6 +48,16 @@ __device__ __forceinline__ void sincospi_any(double x, double& s, double& c) {
     const double a = (k & 1) ? cs : sn, b = (k & 1) ? sn : cs;
     s = (k & 2) ? -a : a;
     c = ((k + 1) & 2) ? -b : b;
+}
+// sin(pi x), cos(pi x) for any finite x (exact quadrant: 2 x - rint(2 x) is exact)
+__device__ __forceinline__ void sincospi_any(double x, double& s, double& c) {
+    const double n = rint(2.0 * x);
+    sincospi_quarter(n, fma(-0.5, n, x), s, c);
+}
+// the same of x + lo: a phase and, far below a quarter, the part that its rounding left
+__device__ __forceinline__ void sincospi_sum(double x, double lo, double& s, double& c) {
+    const double n = rint(2.0 * x);
+    sincospi_quarter(n, fma(-0.5, n, x) + lo, s, c);
 }
 
 }  // namespace chaff
