@@ -2119,8 +2119,12 @@ constexpr int64_t LONE_ROWS = 40000;
 static bool lone_wires(const Cloud* c, const chaff_solve_opts* o) {
     // a caller's own guess (use_x0 = 1) is left as it is given; complex128 solves
     // keep one recurrence over every wire, whose iterate at the tolerance is
-    // theirs to 1e-12 and not only to the tolerance
-    return o->prec == CHAFF_C64 && o->precond == CHAFF_PRECOND_BLOCK && o->use_x0 != 1 && c->n * NB >= LONE_ROWS &&
+    // theirs to 1e-12 and not only to the tolerance; COCG_RR's recurrences, carried
+    // over their residual replacements in FP32, break down more often on the coupled
+    // wires alone (2,200 wires of 19 unknowns x 20 columns: 9 of 16 clouds for 3, 5,801 of
+    // 7 x 5: 2 for none)
+    return o->prec == CHAFF_C64 && o->precond == CHAFF_PRECOND_BLOCK && o->use_x0 != 1 && o->method != CHAFF_COCG_RR &&
+           c->n * NB >= LONE_ROWS &&
            2.0 * (double)c->n_pairs <= LONE_SHARE * (double)c->n;
 }
 
