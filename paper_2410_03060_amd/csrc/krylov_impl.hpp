@@ -3551,7 +3551,8 @@ static chaff_status solve_compact(Cloud* c, const chaff_solve_opts* o, const CZ*
         const int w = spmm_tile_width(s);
         const dim3 grid((unsigned)ch.size(), (unsigned)((s + w - 1) / w));
         {
-            ProfScope ps("lone_solve", st, 4.0 * 8.0 * NB2 * (double)n_lone * s, true);
+            // four products per wire and column (one sweep), or one and three of NB columns per wire
+            ProfScope ps("lone_solve", st, 8.0 * NB2 * (double)n_lone * (s > LONE_INV ? s + 3.0 * NB : 4.0 * s), true);
 #define CHAFF_LONE(W)                                                                                            \
     case W:                                                                                                      \
         hipLaunchKernelGGL((k_lone_solve<CZ, W>), grid, dim3(256), 0, st, l, (const Wire*)c->wires,              \
