@@ -608,9 +608,10 @@ __global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
         if (threadIdx.x == 0) A.resume[sys] = now;
         return;
     }
+    // a system that broke down has no solution: an excitation that is not finite would leave its guess
     for (int t = threadIdx.x; t < Y.rows; t += TH) {
         const int ci = t / NB, q = t - ci * NB, i = Y.wire(ci);
-        A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs] = Y.x[i * NB + q];
+        A.X[((int64_t)A.perm[w0 + i] * NB + q) * A.s + rhs] = ok < 0 ? c128{NAN, NAN} : Y.x[i * NB + q];
     }
 }
 
