@@ -32,7 +32,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP32_PEAK_TFLOPS = 157.3       # MI355X FP32 vector (packed) peak, TFLOP/s
 
-# profile name -> (kernel symbol prefix in rocprofv3 output, source file)
+# profile name -> (kernel symbol prefix in rocprofv3 output, source file), for complex64 COCG of many columns
+# with 7 unknowns per wire, the workload that the counter records are of
 KERNEL_SYMBOLS = {
     "spmm": ("chaff::kr7::k_cocg_mfma", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "k_cg_update": ("chaff::kr7::k_cg_update", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
@@ -45,6 +46,28 @@ KERNEL_SYMBOLS = {
     "k_cg_rupd": ("chaff::kr7::k_cg_rupd", "paper_2410_03060_amd/csrc/krylov_impl.hpp"),
     "nbhd_build": ("chaff::k_nbhd_build", "paper_2410_03060_amd/csrc/precond.hip"),
 }
+
+
+def kernel_symbol(name, nb, c64, method, columns, cluster=False):
+    """Symbol (prefix) of the kernel behind a profile name, for solves of `columns` right-hand sides with nb
+    unknowns per wire: the product of a COCG step runs on the matrix cores (complex64, 7 unknowns), as a
+    streaming row product (7 unknowns, up to 4 columns) or in the staged form."""
+    space = f"chaff::kr{nb}::"
+    if name in ("spmm", "spmm_narrow", "nbhd_apply", "nbhd_apply_narrow"):
+        if method not in ("cocg", "cocg_rr"):
+            return space + "k_spmm_"
+        if nb == 7 and columns <= 4:
+            return space + "k_cocg_stream"
+        return space + ("k_cocg_mfma" if nb == 7 and c64 else "k_cocg_spmm")
+    if name == "solve_small":
+        return space + "small::k_solve_small"
+    if name == "lone_solve":
+        return space + ("k_lone_apply" if columns > 32 else "k_lone_solve")
+    if cluster and name in ("k_cg_update", "k_cg_p"):   # the cluster path runs its own update and direction kernels
+        return space + ("k_cg_update_cl" if name == "k_cg_update" else "k_cg_pdir_z")
+    return KERNEL_SYMBOLS.get(name, (name,))[0].replace("chaff::kr7::", space)
+
+
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 
@@ -612,19 +635,16 @@ def main(argv=None) -> int:
     if prof:
         ranked = sorted(prof.items(), key=lambda kv: -kv[1]["total_ms"])
         name, k = ranked[0]
-        # kernels whose complex64 products run on the FP32 matrix cores
-        mfma = {"spmm", "spmm_narrow", "nbhd_apply", "nbhd_apply_narrow"} | ({"k_cg_update"} if pc == "cluster" else set())
-        roof = roofline_of(k, prec == B.C64 and name in mfma)
+        symbol = kernel_symbol(name, wl.cloud.n_seg - 1, prec == B.C64, method, R, pc == "cluster")
+        # products on the FP32 matrix cores
+        mfma = symbol.endswith("k_cocg_mfma") or (prec == B.C64 and symbol.endswith("k_cg_update_cl"))
+        roof = roofline_of(k, mfma)
         roof["traffic"] = measured_traffic(a.config, name)
         mc = measured_mfma(a.config, name)
         if mc is not None:   # matrix-core counters of the same kernel (profiles/mfma_counters.json)
             roof["mfma_busy"] = mc["mfma_busy_fraction"]
             roof["mfma_flop_counted_per_launch"] = mc["mfma_flop"]
-        symbols = dict(KERNEL_SYMBOLS)
-        if pc == "cluster":   # the cluster path runs its own update and direction kernels
-            symbols.update({"k_cg_update": ("chaff::kr7::k_cg_update_cl", KERNEL_SYMBOLS["k_cg_update"][1]),
-                            "k_cg_p": ("chaff::kr7::k_cg_pdir_z", KERNEL_SYMBOLS["k_cg_p"][1])})
-        roof.update({"kernel": name, "symbol": symbols.get(name, (name,))[0], "launches": k["launches"],
+        roof.update({"kernel": name, "symbol": symbol, "launches": k["launches"],
                      "avg_ms": k["total_ms"] / k["launches"],
                      "timing": "HIP events recorded on the launch stream around every launch in the timed steps"})
         kernels = {}

@@ -1478,7 +1478,7 @@ void k_cocg_mfma(const Chunk* __restrict__ tiles, int64_t n_tiles, int col_tiles
     if (threadIdx.x < S && r < s) tpart[t * s + r] = v;
 }
 
-// COCG product of up to STREAM_MAX columns on the streaming row product: the
+// COCG product of up to STREAM_COCG columns on the streaming row product: the
 // same tiles and per-tile p^T q as k_cocg_spmm, one row per wave.
 template <typename CZ, typename C, int S, bool VEC>
 __global__ __launch_bounds__(RB) void k_cocg_stream(const Chunk* __restrict__ tiles, int64_t n_tiles, int xcd_order,
