@@ -51,8 +51,8 @@ struct Out {             // what a system tells the host
     int32_t cycles, ok;  // refinement cycles run; 1 converged, 0 not, -1 broken down, 2 goes on in another launch
 };
 
-// What a system carries from cycle to cycle, and over the end of a launch's share
-// into the next; its vectors lie in the workspace.
+// What a system carries over the end of a launch's share into the next; its
+// vectors lie in the workspace.
 struct Resume {
     double bn, lone2, scale, target, ckpt;
     c128 rho;
@@ -78,7 +78,6 @@ struct Args {
     c128* H;                       // per system [m][m + 1], column by column
     double* lone_e2;               // [wires][s] squared residual of a wire solved by k_lone
     int take_lone;                 // k_lone ran
-    int again;                     // a further launch of the same solve
     Resume* resume;                // per system
     Out* out;
     int32_t* steps;                // per system [max_cycles]
@@ -94,8 +93,19 @@ struct Shared {
     int32_t cnt[NW];
     double val[4];
     int32_t flag;
-    Resume at;                     // written by thread 0
 };
+
+// A value that every thread holds and that lives across the cycles.  In complex64
+// it goes to scalar registers (2,000 wires x 10 COCG steps 230 us, 237 with the
+// spilled registers of the vector form); complex128's loops fill the scalar ones
+// themselves (43 wires x 7 steps 69 us, 73 so).
+template <typename C>
+__device__ __forceinline__ double held(double v) {
+    if (sizeof(C) == sizeof(c128)) return v;
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 
 __device__ __forceinline__ double wave_add(double v) {
 #pragma unroll
@@ -396,31 +406,32 @@ __device__ int gmres_cycle(System<C>& Y, double rn, double target, c128* H) {
     return used;
 }
 
-// One COCG cycle: r in units of S.at.scale, ended below the checkpoint or after m
+// One COCG cycle: r in units of scale, ended below the checkpoint or after m
 // steps; S.flag says whether x_c holds a correction.  Returns its steps, or -1
 // where left, the launch's remaining steps, ran out first: called again, it goes
-// on from S.at.
+// on from pause.
 template <typename C>
-__device__ int cocg_cycle(System<C>& Y, int left) {
+__device__ int cocg_cycle(System<C>& Y, double scale, double target, double ckpt, int k0, int left, Resume* pause) {
     using R = typename real_of<C>::type;
     Shared& S = Y.S;
-    const int rows = Y.rows, k0 = S.at.k;
+    const int rows = Y.rows;
     C *rv = Y.vec(0), *p = Y.vec(1), *q = Y.vec(2), *xc = Y.vec(3);
     if (threadIdx.x == 0) S.flag = k0;   // every step so far added to x_c
     if (k0 == 0)
         for (int t = threadIdx.x; t < rows; t += TH) {
             const int ci = t / NB;
-            rv[t] = ccast<C>(cscale(Y.r[Y.wire(ci) * NB + t - ci * NB], 1.0 / S.at.scale));
+            rv[t] = ccast<C>(cscale(Y.r[Y.wire(ci) * NB + t - ci * NB], 1.0 / scale));
         }
     __syncthreads();
-    c128 rho = S.at.rho, alpha = {0, 0};
+    c128 rho = {0, 0}, alpha = {0, 0};
+    if (k0 > 0) rho = pause->rho;
     int steps;
     for (int k = k0;; ++k) {
         steps = k;
         if (k - k0 >= left) {
             if (threadIdx.x == 0) {
-                S.at.rho = rho;
-                S.at.k = k;
+                pause->rho = rho;
+                pause->k = k;
             }
             steps = -1;
             break;
@@ -439,7 +450,7 @@ __device__ int cocg_cycle(System<C>& Y, int left) {
         block_add(S, rz, rr);
         const double rn = sqrt(fmax(rr.re, 0.0));
         const double dd = rho.re * rho.re + rho.im * rho.im;
-        if (!(rn > S.at.target) || !isfinite(rn) || !(rn > S.at.ckpt) || k == Y.A.m) break;
+        if (!(rn > target) || !isfinite(rn) || !(rn > ckpt) || k == Y.A.m) break;
         const c128 beta = k > 0 && dd > 0.0 ? cmul(rz, c128{rho.re / dd, -rho.im / dd}) : c128{0, 0};
         rho = rz;
         const cplx<R> bt = ccast<cplx<R>>(beta);
@@ -496,7 +507,8 @@ __global__ __launch_bounds__(64) void k_lone(Args<C> A, int64_t n) {
     A.lone_e2[i * A.s + r] = e2;
 }
 
-template <typename C>
+// AGAIN: a further launch of the same solve
+template <typename C, bool AGAIN>
 __global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
     __shared__ Shared S;
     const int cl = (int)(blockIdx.x % A.n_clouds);
@@ -510,26 +522,33 @@ __global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
         if (threadIdx.x == 0) A.out[sys] = Out{0.0, 0, 1};
         return;
     }
-    Resume& now = S.at;
-    if (A.again && A.out[sys].ok != 2) return;   // this system is done
-    if (threadIdx.x == 0) {
-        now = A.again ? A.resume[sys] : Resume{};
-        if (!A.again) now.all = !A.take_lone;
-    }
-    __syncthreads();
-    Y.list_coupled(now.all);
-    if (!A.again) {
-        double b2, lone2;
+    Resume* const pause = A.resume + sys;
+    double bn, lone2 = 0.0, scale = 0.0, target = 0.0, ckpt = 0.0;
+    int cycles = 0, k0 = 0;
+    bool all = !A.take_lone, in_cycle = false;
+    if (AGAIN) {
+        if (A.out[sys].ok != 2) return;   // this system is done
+        bn = held<C>(pause->bn);
+        lone2 = held<C>(pause->lone2);
+        scale = held<C>(pause->scale);
+        target = held<C>(pause->target);
+        ckpt = held<C>(pause->ckpt);
+        cycles = pause->cycles;
+        all = pause->all != 0;
+        in_cycle = pause->in_cycle != 0;
+        k0 = in_cycle ? pause->k : 0;
+        Y.list_coupled(all);
+    } else {
+        Y.list_coupled(all);
+        double b2;
         Y.norms(b2, lone2);
         if (Y.nc < n && !(lone2 <= 0.01 * A.tol * A.tol * b2)) {   // the block inverses do not solve them
             Y.list_coupled(true);
+            all = true;
             lone2 = 0.0;
         }
-        if (threadIdx.x == 0) {
-            now.bn = sqrt(b2);
-            now.lone2 = lone2;
-            now.all = Y.nc == n;
-        }
+        bn = held<C>(sqrt(b2));
+        lone2 = held<C>(lone2);
         Y.excite();
         // initial guess on the rows that are iterated on
         for (int t = threadIdx.x; t < Y.rows; t += TH) {
@@ -548,10 +567,11 @@ __global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
             ok = 2;
             break;
         }
-        int steps;
-        if (!now.in_cycle) {
-            const double bn = now.bn, r2 = Y.residual(now.cycles == 0 && A.use_x0 == 0), rn = sqrt(fmax(r2, 0.0));
-            rel = bn > 0 ? sqrt(r2 + now.lone2) / bn : 0.0;
+        double rn = 0.0;
+        if (!in_cycle) {
+            const double r2 = held<C>(Y.residual(cycles == 0 && A.use_x0 == 0));
+            rn = held<C>(sqrt(fmax(r2, 0.0)));
+            rel = bn > 0 ? sqrt(r2 + lone2) / bn : 0.0;
             if (!isfinite(r2)) {
                 rel = INFINITY;
                 ok = -1;
@@ -561,51 +581,54 @@ __global__ __launch_bounds__(TH) void k_solve_small(Args<C> A) {
                 ok = 1;
                 break;
             }
-            if (now.cycles >= A.max_cycles) break;
+            if (cycles >= A.max_cycles) break;
             --left;
-            if (A.method == CHAFF_GMRES) {
-                const double need = A.tol * bn / rn;
-                const double target = sizeof(C) == sizeof(c64) ? fmax(A.inner_tol, fmin(need, 1.0) * 0.5) : fmin(need * 0.5, 1.0);
-                steps = gmres_cycle<C>(Y, rn, target, H);
-            } else if (threadIdx.x == 0) {
-                if (now.scale <= 0.0) now.scale = rn > 0 ? rn : 1.0;
-                now.target = 0.5 * A.tol * bn / now.scale;
-                now.ckpt = fmax(now.target, A.inner_tol * rn / now.scale);
-                now.k = 0;
-                now.rho = c128{0, 0};
-            }
         }
-        if (A.method != CHAFF_GMRES) {
-            __syncthreads();
-            const int k0 = now.k;
-            steps = cocg_cycle<C>(Y, left);
-            if (threadIdx.x == 0) now.in_cycle = steps < 0;
-            if (steps < 0) {
+        int steps;
+        if (A.method == CHAFF_GMRES) {
+            const double need = A.tol * bn / rn;
+            const double goal = sizeof(C) == sizeof(c64) ? fmax(A.inner_tol, fmin(need, 1.0) * 0.5) : fmin(need * 0.5, 1.0);
+            steps = gmres_cycle<C>(Y, rn, goal, H);
+        } else {
+            if (!in_cycle) {
+                if (scale <= 0.0) scale = rn > 0 ? rn : 1.0;
+                target = held<C>(0.5 * A.tol * bn / scale);
+                ckpt = held<C>(fmax(target, A.inner_tol * rn / scale));
+                k0 = 0;
+            }
+            steps = cocg_cycle<C>(Y, scale, target, ckpt, k0, left, pause);
+            in_cycle = steps < 0;
+            if (in_cycle) {
                 left = 0;
-                __syncthreads();
                 continue;
             }
             left += k0;
             if (S.flag) {   // a correction was formed
                 const C* xc = Y.vec(3);
-                const double scale = now.scale;
                 for (int t = threadIdx.x; t < Y.rows; t += TH) {
                     const int ci = t / NB, a = Y.wire(ci) * NB + t - ci * NB;
                     const c128 v = ccast<c128>(xc[t]);
                     Y.x[a] = c128{Y.x[a].re + scale * v.re, Y.x[a].im + scale * v.im};
                 }
             }
+            __syncthreads();
         }
         left -= steps;
-        if (threadIdx.x == 0) {
-            A.steps[sys * A.max_cycles + now.cycles] = steps;
-            ++now.cycles;
-        }
-        __syncthreads();
+        if (threadIdx.x == 0) A.steps[sys * A.max_cycles + cycles] = steps;
+        ++cycles;
     }
-    if (threadIdx.x == 0) A.out[sys] = Out{rel, now.cycles, ok};
+    if (threadIdx.x == 0) A.out[sys] = Out{rel, cycles, ok};
     if (ok == 2) {
-        if (threadIdx.x == 0) A.resume[sys] = now;
+        if (threadIdx.x == 0) {   // (rho and k: by the cycle that stopped)
+            pause->bn = bn;
+            pause->lone2 = lone2;
+            pause->scale = scale;
+            pause->target = target;
+            pause->ckpt = ckpt;
+            pause->cycles = cycles;
+            pause->all = all;
+            pause->in_cycle = in_cycle;
+        }
         return;
     }
     // a system that broke down has no solution: an excitation that is not finite would leave its guess
@@ -733,17 +756,19 @@ static chaff_status solve_small_impl(Cloud* c, const chaff_solve_opts* o, const 
     std::vector<char> back(head + (size_t)nsys * o->max_cycles * sizeof(int32_t));
     const small::Out* out = reinterpret_cast<const small::Out*>(back.data());
     const int32_t* steps = reinterpret_cast<const int32_t*>(back.data() + head);
-    for (bool more = true; more;) {   // a launch per LAUNCH_STEPS steps of the slowest system
+    for (bool again = false, more = true; more; again = true) {   // a launch per LAUNCH_STEPS steps of the slowest system
         {
             ProfScope ps("solve_small", st);
-            if (a.take_lone && !a.again)
+            if (a.take_lone && !again)
                 hipLaunchKernelGGL(small::k_lone<C>, dim3((unsigned)((c->n * s + 63) / 64)), dim3(64), 0, st, a, c->n);
-            hipLaunchKernelGGL(small::k_solve_small<C>, dim3((unsigned)nsys), dim3(small::TH), 0, st, a);
+            if (again)
+                hipLaunchKernelGGL((small::k_solve_small<C, true>), dim3((unsigned)nsys), dim3(small::TH), 0, st, a);
+            else
+                hipLaunchKernelGGL((small::k_solve_small<C, false>), dim3((unsigned)nsys), dim3(small::TH), 0, st, a);
         }
         CHAFF_LAUNCH_CHECK();
         CHAFF_HIP(hipMemcpyAsync(back.data(), a.out, back.size(), hipMemcpyDeviceToHost, st));
         CHAFF_HIP(hipStreamSynchronize(st));
-        a.again = 1;
         more = false;
         for (int64_t i = 0; i < nsys; ++i) more = more || out[i].ok == 2;
     }
