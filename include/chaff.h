@@ -212,7 +212,7 @@ size_t chaff_solve_workspace_bytes(chaff_cloud c, const chaff_solve_opts* o, int
  *   Host-synchronising: once per Krylov step the host reads back the count
  *   of systems still above their checkpoint (one int32; COCG's comes through a
  *   slot of pinned memory), and once per cycle the FP64 residual norms; a small
- *   solve is one launch and one read back at its end. */
+ *   solve is one launch and one read back per 512 steps of its slowest system. */
 chaff_status chaff_solve(chaff_cloud c, const chaff_solve_opts* o, const void* Z,
                          const void* Pinv, const double* k_hat, const double* e_hat,
                          int64_t n_rhs, void* X, void* ws, size_t ws_bytes,
