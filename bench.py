@@ -31,6 +31,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP32_PEAK_TFLOPS = 157.3       # MI355X FP32 vector (packed) peak, TFLOP/s
+FP64_PEAK_TFLOPS = 78.6        # MI355X FP64 vector peak, TFLOP/s
 
 # profile name -> (kernel symbol prefix in rocprofv3 output, source file), for complex64 COCG of many columns
 # with 7 unknowns per wire, the workload that the counter records are of
@@ -280,27 +281,28 @@ def fill_summary(prof, config=None):
     return out
 
 
-def roofline_of(k, matrix_cores: bool):
+def roofline_of(k, matrix_cores: bool, fp64: bool = False):
     """Roofline of one kernel from its algorithmic bytes B and flops F per launch and its
     measured average launch time t: the bound is whichever of B / 8 TB/s and
-    F / 157.3 TFLOP/s is longer; `achieved` is that resource's rate (B/t or F/t)
+    F / 157.3 TFLOP/s (fp64: 78.6) is longer; `achieved` is that resource's rate (B/t or F/t)
     and `frac` = achieved / peak (= bound time / t)."""
     sec = k["total_ms"] / 1e3 / k["launches"]
     b = k["bytes"] / k["launches"]
     f = k["flops"] / k["launches"]
     t_hbm = b / (HBM_PEAK_GBS * 1e9)
-    t_alu = f / (FP32_PEAK_TFLOPS * 1e12)
+    peak = FP64_PEAK_TFLOPS if fp64 else FP32_PEAK_TFLOPS
+    t_alu = f / (peak * 1e12)
     if t_alu > t_hbm:
         ach = f / sec / 1e12
-        roof = {"bound": "mfma" if matrix_cores else "alu", "achieved": ach, "peak": FP32_PEAK_TFLOPS,
-                "unit": "TFLOP/s", "frac": ach / FP32_PEAK_TFLOPS}
+        roof = {"bound": "mfma" if matrix_cores else "alu", "achieved": ach, "peak": peak,
+                "unit": "TFLOP/s", "frac": ach / peak}
     else:
         ach = b / sec / 1e9
         roof = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": ach / HBM_PEAK_GBS}
     roof.update({"bytes_per_launch": b, "flops_per_launch": f,
                  "intensity_flop_per_byte": (f / b) if b > 0 else None,
-                 "ridge_flop_per_byte": FP32_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9),
+                 "ridge_flop_per_byte": peak * 1e12 / (HBM_PEAK_GBS * 1e9),
                  "hbm_GB/s": b / sec / 1e9, "TFLOP/s": f / sec / 1e12})
     return roof
 
@@ -638,7 +640,7 @@ def main(argv=None) -> int:
         symbol = kernel_symbol(name, wl.cloud.n_seg - 1, prec == B.C64, method, R, pc == "cluster")
         # products on the FP32 matrix cores
         mfma = symbol.endswith("k_cocg_mfma") or (prec == B.C64 and symbol.endswith("k_cg_update_cl"))
-        roof = roofline_of(k, mfma)
+        roof = roofline_of(k, mfma, prec == B.C128 or name in ("lone_solve", "rcs_bistatic", "rcs_mono"))
         roof["traffic"] = measured_traffic(a.config, name)
         mc = measured_mfma(a.config, name)
         if mc is not None:   # matrix-core counters of the same kernel (profiles/mfma_counters.json)

@@ -42,3 +42,10 @@ def test_symbol(bench, args, symbol):
         src = "".join(open(os.path.join(ROOT, "paper_2410_03060_amd", "csrc", f)).read()
                       for f in os.listdir(os.path.join(ROOT, "paper_2410_03060_amd", "csrc")) if f.endswith((".hip", ".hpp")))
         assert re.search(r"__global__[^;{]*\b" + symbol.rsplit("::", 1)[1], src)
+
+
+def test_roofline_of_fp64_work(bench):
+    k = dict(total_ms=2.0, launches=2, bytes=2e6, flops=2 * 39.3e9)
+    assert abs(bench.roofline_of(k, False, True)["frac"] - 0.5) < 1e-12
+    r = bench.roofline_of(k, True)
+    assert abs(r["frac"] - 39.3 / 157.3) < 1e-12 and r["bound"] == "mfma"
